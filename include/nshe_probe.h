@@ -12,8 +12,8 @@
  *   (mod m_k), the dense contraction inside the centred lifts and the
  *   scale-and-round (n_in -> n_out primes: 17 -> 18 or 18 -> 17), on n_coef
  *   coefficients of pseudo-random balanced residues and constants, computed
- *   by the library's split-FMA rows (VALU) and by integer MFMA
- *   (v_mfma_i32_32x32x32_i8 on signed base-256 digits); times are the mean
+ *   by split-FMA rows on the VALU and by integer MFMA as the library's
+ *   kernels do (v_mfma_i32_32x32x32_i8 on signed bytes); times are the mean
  *   over `reps` launches after one warm-up pass, and `mismatches` counts
  *   outputs where the two differ mod m_k (must be 0).
  *

@@ -2,6 +2,7 @@
 // twiddles, relinearization key) and the evaluation entry points.
 #include "../../include/nshe.h"
 
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <functional>
@@ -10,6 +11,7 @@
 #include <string>
 #include <vector>
 
+#include "conv.h"
 #include "kernels.h"
 
 namespace nshe {
@@ -1014,16 +1016,10 @@ int nshe_ctx_create(const nshe_params* pr, int hip_device, nshe_ctx** out) {
     }
   }
   std::vector<u64> qv(q), bv(b);
-  // Base-conversion matrices: each entry M (balanced mod m) split as M =
-  // c1 2^24 + c0 (|c1| <= 2^24, |c0| <= 2^23) for exact FMA accumulation.
-  auto split = [](double* d, u64 M, u64 m) {
-    const double cb = bal(M, m);
-    const double c1v = std::nearbyint(cb * 0x1p-24);
-    d[0] = c1v;
-    d[1] = cb - c1v * 0x1p24;
-  };
-  std::vector<double> q_hat_b_sp((size_t)LB * L * 2), c2_sp((size_t)LB * L * 2),
-      b_hat_q_sp((size_t)L * LB * 2), two24(K), two48(K);
+  // Base-conversion matrices (canonical residues, [input][output]), uploaded
+  // as the matrix-core constants of conv_matrix
+  std::vector<u64> m_lift((size_t)L * LB), m_c2((size_t)L * LB), m_back((size_t)LB * L);
+  std::vector<double> two24(K), two48(K);
   for (int i = 0; i < K; ++i) {
     const u64 m = prime(i), t24 = (1ull << 24) % m;
     two24[i] = bal(t24, m);
@@ -1091,7 +1087,7 @@ int nshe_ctx_create(const nshe_params* pr, int hip_device, nshe_ctx** out) {
     NP_inv_q[L + i] = bal(mulmod(npq, w_last[i], qi), qi);
     // Delta = (Q - (Q mod t)) / t = -(Q mod t) * t^-1 (mod q_i)
     delta_q[i] = bal((qi - mulmod(Qmodt, invmod(c->t % qi, qi), qi)) % qi, qi);
-    for (int k = 0; k < LB; ++k) split(&b_hat_q_sp[((size_t)i * LB + k) * 2], prod_mod(bv, k, qi), qi);
+    for (int k = 0; k < LB; ++k) m_back[(size_t)k * L + i] = prod_mod(bv, k, qi);
     for (int j = 0; j < i; ++j) mrc_inv[(size_t)j * L + i] = bal(invmod(qv[j] % qi, qi), qi);
   }
   for (int k = 0; k < LB; ++k) {
@@ -1105,8 +1101,8 @@ int nshe_ctx_create(const nshe_params* pr, int hip_device, nshe_ctx** out) {
     c1[k] = bal(c1k, bk);
     c1[LB + k] = bal(mulmod(c1k, w_last[L + k], bk), bk);
     for (int i = 0; i < L; ++i) {
-      split(&q_hat_b_sp[((size_t)k * L + i) * 2], prod_mod(qv, i, bk), bk);
-      split(&c2_sp[((size_t)k * L + i) * 2], mulmod(invmod(qv[i] % bk, bk), bhi, bk), bk);
+      m_lift[(size_t)i * LB + k] = prod_mod(qv, i, bk);
+      m_c2[(size_t)i * LB + k] = mulmod(invmod(qv[i] % bk, bk), bhi, bk);
     }
   }
   // mixed-radix digits of (Q-1)/2, whose residue mod q_i is (q_i - 1)/2
@@ -1123,6 +1119,29 @@ int nshe_ctx_create(const nshe_params* pr, int hip_device, nshe_ctx** out) {
       mrc_half[i] = (double)tv;
     }
   }
+  // per-prime constants side by side, padded to steps of four primes
+  auto steps4 = [](int v) { return (size_t)((v + 3) / 4) * 4; };
+  std::vector<double> kq(steps4(L) * 4, 0.0), kb(steps4(LB) * 4, 0.0),
+      km(steps4(L) * alpha, 0.0);
+  for (int i = 0; i < L; ++i) {
+    const double v[4] = {h_p[i], h_pinv[i], q_hat_inv[i], B_q[i]};
+    std::copy(v, v + 4, &kq[(size_t)i * 4]);
+    km[(size_t)i * alpha] = P_inv_q[i];
+    for (int k = 1; k < alpha; ++k) km[(size_t)i * alpha + k] = mr_q[(size_t)(k - 1) * L + i];
+  }
+  for (int k = 0; k < LB; ++k) {
+    const double v[4] = {h_p[L + k], h_pinv[L + k], b_hat_inv[k], Q_b[k]};
+    std::copy(v, v + 4, &kb[(size_t)k * 4]);
+  }
+  // the constants' bytes in the table upload's unit (doubles)
+  auto packed = [](const std::vector<int32_t>& v) {
+    std::vector<double> d((v.size() + 1) / 2, 0.0);
+    std::memcpy(d.data(), v.data(), v.size() * sizeof(int32_t));
+    return d;
+  };
+  const std::vector<double> mx_lift = packed(conv_matrix(m_lift, L, bv)),
+                            mx_c2 = packed(conv_matrix(m_c2, L, bv)),
+                            mx_back = packed(conv_matrix(m_back, LB, qv));
   // --- upload
   std::vector<std::pair<const std::vector<double>*, const double**>> parts = {
       {&h_p, &c->tb.p},           {&h_pinv, &c->tb.pinv},     {&h_pinv, &c->tb.recip},
@@ -1136,7 +1155,8 @@ int nshe_ctx_create(const nshe_params* pr, int hip_device, nshe_ctx** out) {
       {&mrc_inv, &c->tb.mrc_inv}, {&mrc_half, &c->tb.mrc_half}, {&tw_h, &c->tb.tw_half},
       {&tw_h0, &c->tb.tw_half0},  {&tw_cf, &c->tb.tw_cmp_f},  {&tw_ci, &c->tb.tw_cmp_i},
       {&tw_ch, &c->tb.tw_cmp_h},  {&tw_kf, &c->tb.tw_cst_f},  {&tw_ki, &c->tb.tw_cst_i},
-      {&q_hat_b_sp, &c->tb.q_hat_b_sp}, {&c2_sp, &c->tb.c2_sp}, {&b_hat_q_sp, &c->tb.b_hat_q_sp},
+      {&mx_lift, &c->tb.mx_lift}, {&mx_c2, &c->tb.mx_c2}, {&mx_back, &c->tb.mx_back},
+      {&kq, &c->tb.kq},           {&kb, &c->tb.kb},           {&km, &c->tb.km},
       {&two24, &c->tb.two24},     {&two48, &c->tb.two48},
       {&tw_hi, &c->tb.tw_half_inv}, {&tw_chi, &c->tb.tw_cmp_hi},
       {&tw_r1f, &c->tb.tw_r1_f},  {&tw_r1i, &c->tb.tw_r1_i},

@@ -61,12 +61,17 @@ struct Tables {
   const double* c1;          // [2][LB]  [t Q^-1 (B/b_k)^-1 N^-1]_{b_k}
   const double* b_hat_inv;   // [LB]     [(B/b_k)^-1]_{b_k}
   const double* B_q;         // [L]      [B]_{q_i}
-  // the three base-conversion matrices, each balanced entry M split for
-  // exact FMA accumulation as M = c1 2^24 + c0, stored {c1, c0} (see
-  // conv_row), and [2^24]_p, [2^48]_p per prime
-  const double* q_hat_b_sp;  // [LB][L][2]  [Q/q_i]_{b_k}
-  const double* c2_sp;       // [LB][L][2]  [q_i^-1 (B/b_k)^-1]_{b_k}
-  const double* b_hat_q_sp;  // [L][LB][2]  [B/b_k]_{q_i}
+  // the three base conversions' constants for the integer matrix cores
+  // (conv_matrix: int4 entries per tile, step and lane): [Q/q_i]_{b_k},
+  // [q_i^-1 (B/b_k)^-1]_{b_k}, [B/b_k]_{q_i}; and [2^24]_p, [2^48]_p per prime
+  const double* mx_lift;     // L -> LB
+  const double* mx_c2;       // L -> LB
+  const double* mx_back;     // LB -> L
+  // constants of the per-coefficient kernels, one prime's side by side (a few
+  // wide scalar loads), padded to whole steps of four primes
+  const double* kq;          // [L][4]   q, fl(1/q), q_hat_inv, B_q
+  const double* kb;          // [LB][4]  b, fl(1/b), b_hat_inv, Q_b
+  const double* km;          // [L][alpha] P_inv_q, then mr_q of k = 1..alpha-1
   const double* two24;       // [K]
   const double* two48;       // [K]
   // key switching (digits of alpha data primes, alpha special primes; the

@@ -99,6 +99,10 @@ __device__ __forceinline__ const double* opaque_row(const double* p, int off) {
   asm volatile("" : "+s"(r));
   return r;
 }
+// The loads above are issued before anything below: the scheduler otherwise
+// sinks them to their uses, one memory latency each.
+__device__ __forceinline__ void loads_issued() { __builtin_amdgcn_sched_barrier(0); }
+
 __device__ __forceinline__ int cldi(const int* p, int i) { return ((const_iptr)p)[i]; }
 
 // An index the compiler cannot see through (inline asm on a scalar

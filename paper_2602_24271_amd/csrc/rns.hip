@@ -26,8 +26,10 @@
 // a violation would be counted in `fault`).
 //
 // The sums over the other basis (sum_i y_i [Q/q_i]_{b_k} and the like) are
-// matrix-vector products mod b_k; they run as exact FMA accumulations of
-// split operands (conv_row) with one modular reduction per output.
+// matrix products mod b_k; they run on the integer matrix cores over signed
+// bytes (conv_pack, conv_tile) with one modular reduction per output.
+#include <algorithm>
+
 #include "conv.h"
 #include "kernels.h"
 
@@ -77,88 +79,143 @@ __device__ __noinline__ bool mrc_greater_than_half(const double* r, const double
 // Per-poly block mapping of the per-coefficient kernels: block b covers
 // coefficients [(b mod bpp) blockDim, ...) of poly b / bpp, so the poly and
 // its base address are uniform (scalar registers): limb accesses are buffer
-// loads with one per-lane offset and a scalar limb offset.
+// loads with one per-lane offset and a scalar limb offset.  A workgroup takes
+// blocks b, b + gridDim, ... (the conversion constants it holds in LDS serve
+// them all).  Every lane of a wave takes part in the conversions (matrix
+// instructions and lane swaps), also those past the last coefficient of a
+// ring smaller than the block: they repeat coefficient 0 and store nothing
+// (ok).
 struct PolyBlock {
   size_t pc;
   int c;
   bool ok;
 };
 
-__device__ __forceinline__ PolyBlock poly_block(int n, size_t n_poly) {
-  const int bpp = (n + (int)blockDim.x - 1) / (int)blockDim.x;
-  const size_t pc = blockIdx.x / (unsigned)bpp;
-  const int c = (int)(blockIdx.x - pc * bpp) * (int)blockDim.x + (int)threadIdx.x;
-  return PolyBlock{pc, c, pc < n_poly && c < n};
+__device__ __forceinline__ unsigned poly_blocks(int n, size_t n_poly) {
+  return (unsigned)(n_poly * (size_t)((n + (int)blockDim.x - 1) / (int)blockDim.x));
 }
 
-// ------------------------------------------------ split base conversion ---
+__device__ __forceinline__ PolyBlock poly_block(int n, unsigned b) {
+  const unsigned bpp = (unsigned)((n + (int)blockDim.x - 1) / (int)blockDim.x);
+  const size_t pc = b / bpp;
+  const int c = (int)(b - pc * bpp) * (int)blockDim.x + (int)threadIdx.x;
+  return PolyBlock{pc, c < n ? c : 0, c < n};
+}
 
 // ------------------------------------------------------------------ lift ---
+
+// A store of a lane that has a coefficient; the others' offset is past every
+// buffer, where stores are dropped.
+__device__ __forceinline__ unsigned store_off(bool ok, unsigned off) {
+  return ok ? off : 0x7ffffff8u;
+}
+
+// The constants of primes 4s..4s+3 of a basis, four doubles each (kq, kb): a
+// few wide scalar loads, fenced per step so that no later step's are held
+// through it.  (Steps past the last prime read the table's padding.)
+__device__ __forceinline__ const double* step_consts(const double* tab, int s) {
+  return opaque_row(tab, 16 * s);
+}
+
+// Inputs 4s..4s+3 of a conversion (zero past L).
+template <int L>
+__device__ __forceinline__ void pack_step(const double (&y)[L], int s, v4i& g0, v4i& g1) {
+  double q[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) q[j] = 4 * s + j < L ? y[4 * s + j < L ? 4 * s + j : 0] : 0.0;
+  conv_pack(q, L - 4 * s, g0, g1);
+}
+
+// The rest of a lift whose L residues o (balanced) and y_i = [o_i
+// (Q/q_i)^-1]_{q_i} (packed in g0, g1), S = sum_i y_i / q_i are already in
+// registers: the overflow count v (exact decision near a half-integer), then
+// limbs L..2L of rs at vo.  tab: the conversion's constants in LDS.
+// |conv_value| < 0.98 2^49 (m / 2 + 2^47.7), |v Q_b| <= (L / 2 + 1) 2^48: sums
+// below 2^53.
+// The matrix cores take the contraction off the FP64 VALU (15 -> 16 primes: 32
+// matrix instructions and about 380 VALU issue slots per 64 coefficients
+// against 1170 as split FMAs): the int64 lift 18 -> 12 us at one ciphertext,
+// the lift of 2^12-point rings with 17 primes 20 -> 12.5 us.
+template <int L, int SITE>
+__device__ __forceinline__ void lift_tail(const double (&o)[L], const v4i (&g0)[conv_steps(L)],
+                                          const v4i (&g1)[conv_steps(L)], double S,
+                                          __amdgpu_buffer_rsrc_t rs, unsigned vo, unsigned ls,
+                                          bool ok, const v4i* tab, const Tables& tb) {
+  constexpr int LB = L + 1;
+  double v = __builtin_rint(S);
+  if (ok && lift_near_half(S, v, tb)) {
+    double r[L];
+#pragma unroll
+    for (int i = 0; i < L; ++i) r[i] = to_canonical(o[i], cld(tb.p, i));
+    v = __builtin_floor(S) + (mrc_greater_than_half<L>(r, tb.p, tb.pinv, tb.mrc_inv, tb.mrc_half) ? 1.0 : 0.0);
+    atomicAdd(tb.margin + SITE, 1ull);
+  }
+  const unsigned so = store_off(ok, vo);
+#pragma unroll
+  for (int t = 0; t < conv_tiles(LB); ++t) {
+    const double* kb = step_consts(tb.kb, t);
+    ConvSum cs[4];
+    conv_tile<L>(tab + t * conv_steps(L) * 64, g0, g1, cs);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int k = 4 * t + j;
+      if (k >= LB) continue;
+      const double b = cld(kb, 4 * j), binv = cld(kb, 4 * j + 1);
+      const double a = __builtin_fma(-v, cld(kb, 4 * j + 3), conv_value<L>(cs[j], b, binv));
+      buf_store(reduce_bal(a, b, binv), rs, so, (L + k) * ls);
+    }
+  }
+}
 
 // ext: [n_poly][L+LB][N]; limbs 0..L-1 (balanced, coefficient domain) are
 // lifted to limbs L..L+LB-1 (the extension basis) in place.
 template <int L>
-__global__ void __launch_bounds__(256) k_lift(int n, size_t n_poly, double* ext, Tables tb) {
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4)))
+k_lift(int n, size_t n_poly, double* ext, Tables tb) {
   constexpr int LB = L + 1;
-  const PolyBlock pb = poly_block(n, n_poly);
-  if (!pb.ok) return;
-  const auto rs = make_rsrc(ext + pb.pc * (size_t)(L + LB) * n, (unsigned)((L + LB) * n * 8));
-  const unsigned vo = (unsigned)pb.c * 8;
-  const unsigned ls = (unsigned)n * 8;   // bytes per limb
-  double y[L];
-  double S = 0.0;
+  __shared__ v4i tab[conv_entries(L, LB)];
+  conv_table<conv_entries(L, LB)>(tab, tb.mx_lift);
+  __syncthreads();
+  const unsigned nb = poly_blocks(n, n_poly);
+  for (unsigned bk = blockIdx.x; bk < nb; bk += gridDim.x) {
+    const PolyBlock pb = poly_block(n, bk);
+    const auto rs = make_rsrc(ext + pb.pc * (size_t)(L + LB) * n, (unsigned)((L + LB) * n * 8));
+    const unsigned vo = (unsigned)pb.c * 8;
+    const unsigned ls = (unsigned)n * 8;   // bytes per limb
+    double o[L], y[L];
+    double S = 0.0;
 #pragma unroll
-  for (int i = 0; i < L; ++i) {
-    const double pinv = cld(tb.pinv, i);
-    y[i] = mul_bal(buf_load(rs, vo, i * ls), cld(tb.q_hat_inv, i), cld(tb.p, i), pinv);
-    S += y[i] * pinv;
-  }
-  double v = __builtin_rint(S);
-  if (lift_near_half(S, v, tb)) {
-    double r[L];
+    for (int i = 0; i < L; ++i) o[i] = buf_load(rs, vo, i * ls);
+    loads_issued();
+    v4i g0[conv_steps(L)], g1[conv_steps(L)];
 #pragma unroll
-    for (int i = 0; i < L; ++i) r[i] = to_canonical(buf_load(rs, vo, i * ls), cld(tb.p, i));
-    v = __builtin_floor(S) + (mrc_greater_than_half<L>(r, tb.p, tb.pinv, tb.mrc_inv, tb.mrc_half) ? 1.0 : 0.0);
-    atomicAdd(tb.margin + MARGIN_LIFT, 1ull);
-  }
-  // |acc| <= (L / 4 + 7.2 + L/2 + 1) 2^48 < 2^53: reduce_bal is exact there
-  // (its result within p/2 + 4)
-  double yh[L], yl[L];
+    for (int s = 0; s < conv_steps(L); ++s) {
+      const double* kq = step_consts(tb.kq, s);
 #pragma unroll
-  for (int i = 0; i < L; ++i) split24(y[i], yh[i], yl[i]);
-#pragma unroll
-  for (int k = 0; k < LB; ++k) {
-    const double b = cld(tb.p, L + k), binv = cld(tb.pinv, L + k);
-    const double* sp = opaque_row(tb.q_hat_b_sp, k * L * 2);
-    const double acc = conv_row<L>(yh, yl, sp, b, binv) -
-                       v * cld(tb.Q_b, k);
-    buf_store(reduce_bal(acc, b, binv), rs, vo, (L + k) * ls);
+      for (int j = 0; j < 4 && 4 * s + j < L; ++j) {
+        const int i = 4 * s + j;
+        const double qinv = cld(kq, 4 * j + 1);
+        y[i] = mul_bal(o[i], cld(kq, 4 * j + 2), cld(kq, 4 * j), qinv);
+        S += y[i] * qinv;
+      }
+      pack_step<L>(y, s, g0[s], g1[s]);
+    }
+    lift_tail<L, MARGIN_LIFT>(o, g0, g1, S, rs, vo, ls, pb.ok, tab, tb);
   }
 }
 
 // ------------------------------------------------- inverse-transform output ---
 
 // Where a per-coefficient kernel reads coefficient c of a limb written by an
-// inverse transform.  Plain: at c (byte offset v).  After the split inverse
-// of a 2^15-point limb (FUSED) the coefficient is the inverse's last stage
-// applied to the two half outputs U and V of its pair: U + V for the lower
-// half of the coefficients, (U - V) w for the upper (hi), w = the full
-// inverse's last-stage twiddle of the limb's prime.  Every such value is
-// only ever multiplied by a constant, so w is folded into that constant
-// (the "hi" tables) and the load returns U + V or U - V (|.| <= p + 8, as
-// |U|, |V| <= p/2 + 4).  Lanes l and l + 32 of a wave hold the two
-// coefficients of a pair and each loads both U and V (coef_load_both): the
-// second load hits the cache lines of the first, and in the scale-and-round
-// it measured faster than taking the partner lane's value with two lane
-// swaps per value (pair_combine, which the mod-down + lift keeps: there the
-// two loads measured slower).
-struct CoefSrc {
-  unsigned v;      // this lane's position (bytes): where it writes
-  unsigned vu;     // the pair's U and V positions
-  unsigned vv;
-  double sg;       // -1 upper, +1 lower
-  bool hi;
-};
+// inverse transform.  Plain: at c.  After the split inverse of a 2^15-point
+// limb (FUSED) the coefficient is the inverse's last stage applied to the two
+// half outputs U and V of its pair: U + V for the lower half of the
+// coefficients, (U - V) w for the upper, w = the full inverse's last-stage
+// twiddle of the limb's prime.  Every such value is only ever multiplied by a
+// constant, so w is folded into that constant (the tables' second rows) and
+// the kernels form U + V or U - V (|.| <= p + 8, as |U|, |V| <= p/2 + 4).
+// Lanes l and l + 32 of a wave hold the two coefficients of a pair: each loads
+// one of U and V and they trade (pair_combine).
 
 // U + sg V for a pair whose U is in lane l and V in lane l + 32 (sg = +1
 // in the lower lanes, -1 in the upper): a lower lane gets U + V, an upper
@@ -176,34 +233,57 @@ __device__ __forceinline__ double pair_combine(double x, double sg) {
   return __builtin_fma(sg, v, u);
 }
 
-// Coefficient c's value (see CoefSrc; any lane may be inactive).
-template <bool FUSED>
-__device__ __forceinline__ double coef_load_both(__amdgpu_buffer_rsrc_t rs, const CoefSrc& s,
-                                                 unsigned soff) {
-  if constexpr (!FUSED) {
-    return buf_load(rs, s.v, soff);
-  } else {
-    return __builtin_fma(s.sg, buf_load(rs, s.vv, soff), buf_load(rs, s.vu, soff));
+// ----------------------------------------------------------------- scale ---
+
+// The scale-and-round's second conversion and outputs (THIRD: the product's
+// third component, the relinearization digit source).  rw: the destination,
+// at lane offset wo.
+template <int L, int A, bool THIRD>
+__device__ __forceinline__ void scale_out(const v4i (&h0)[conv_steps(L + 1)],
+                                          const v4i (&h1)[conv_steps(L + 1)], double v2,
+                                          __amdgpu_buffer_rsrc_t rw, unsigned wo, unsigned ls,
+                                          const v4i* tab, const Tables& tb) {
+  constexpr int LB = L + 1;
+  double grp[A];   // the current digit group's canonical mixed-radix digits
+#pragma unroll
+  for (int t = 0; t < conv_tiles(L); ++t) {
+    const double* kq = step_consts(tb.kq, t);
+    ConvSum sm[4];
+    conv_tile<LB>(tab + t * conv_steps(LB) * 64, h0, h1, sm);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int i = 4 * t + j;
+      if (i >= L) continue;
+      const double q = cld(kq, 4 * j), qinv = cld(kq, 4 * j + 1);
+      double o = reduce_bal(__builtin_fma(-v2, cld(kq, 4 * j + 3), conv_value<LB>(sm[j], q, qinv)),
+                            q, qinv);
+      // the third component is only read as relinearization digits: its
+      // canonical residues, or with A primes per digit each digit's canonical
+      // mixed-radix digits (Garner: limb g + m of the group starting at g gets
+      // v_m = t_m, t_0 = d_{g+m}, t_{k+1} = [(t_k - v_k) q_{g+k}^-1]_{q_{g+m}};
+      // every difference is below 2^49 < 2 q)
+      if constexpr (THIRD) {
+        o = to_canonical(o, q);
+        if constexpr (A > 1) {
+          const int m = i % A;
+          if (m > 0) {
+            double tt = o;
+#pragma unroll
+            for (int k = 0; k < m; ++k)
+              tt = mul_bal(tt - grp[k], cld(tb.mrc_inv, (i - m + k) * L + i), q, qinv);
+            o = to_canonical(tt, q);
+          }
+          grp[m] = o;
+        }
+      }
+      buf_store(o, rw, wo, i * ls);
+    }
   }
 }
 
-// The constant a coefficient of this lane is multiplied by: entry i of a
-// [2][count] table (lower, then upper = lower times w).  FUSED lanes differ
-// in the half they need, so they read it per lane (a vector load that hits
-// the cache) rather than select between two scalar constants, which would
-// keep both halves' constants in scalar registers.
-template <bool FUSED>
-__device__ __forceinline__ double coef_const(const CoefSrc& s, const double* tab, int i,
-                                             int count) {
-  if constexpr (!FUSED) return cld(tab, i);
-  else return tab[(s.hi ? count : 0) + i];
-}
-
-// ----------------------------------------------------------------- scale ---
-
 // dt: [n_poly][L+LB][N] coefficient domain (balanced).  Writes
 // [round(t d / Q)]_Q into limbs 0..L-1 of the same poly.
-// FUSED: dt holds the split inverse's half outputs (see CoefSrc); each
+// FUSED: dt holds the split inverse's half outputs (see above); each
 // wave takes 32 coefficient pairs (c, c + N/2), lanes 0-31 the lower
 // coefficients and 32-63 the upper, and writes its outputs in place at the
 // positions it alone reads.  A: data primes per key-switching digit (the
@@ -212,138 +292,122 @@ __device__ __forceinline__ double coef_const(const CoefSrc& s, const double* tab
 // ciphertext ct at dig_src + ct 2 (L + A) N (the key-switch sums' stride),
 // limb i at + i N, and coefficient c at position (c mod 2) N/2 + c/2
 // (k_ntt_fwd_par's layout; in place, those positions are read by other
-// waves).  (A table field, read where it is used: a kernel argument stays
-// in scalar registers through the kernel and spills the 17-prime
-// instance's.)
+// waves).
+// Bound by memory traffic at many ciphertexts: 31 limbs in and 15 out per
+// polynomial (15 + 3 primes), 1.16 GB at 32 ciphertexts, in 239 us (4.9 TB/s);
+// the same conversions as split FP64 FMAs (4 per term, on the VALU) took 380.
+// Every limb is loaded at the block's start: loaded as they were needed, the
+// waits of the second half's limbs alone made it 310.  At one ciphertext 20 us
+// (29): there it is latency, six waves per CU.
 template <int L, bool FUSED, int A>
-__global__ void __launch_bounds__(256) k_scale(int n, size_t n_poly, double* dt, Tables tb) {
-  constexpr int LB = L + 1;
-  const PolyBlock pb = poly_block(n, n_poly);
-  // FUSED has a block barrier below: its launcher requires N to be a
-  // multiple of the block, so pb.ok is the same for every thread of a block
-  // and a block returns here as a whole or not at all (returning after the
-  // barrier instead costs 8 VGPRs and a wave per SIMD)
-  if (!pb.ok) return;
-  const auto rs = make_rsrc(dt + pb.pc * (size_t)(L + LB) * n, (unsigned)((L + LB) * n * 8));
-  CoefSrc cs{(unsigned)pb.c * 8, 0u, 0u, 1.0, false};
-  if constexpr (FUSED) {
-    const int t = (int)threadIdx.x, lane = t & 63;
-    const int cp = ((pb.c - t) >> 1) + (t >> 6) * 32 + (lane & 31);
-    cs.hi = lane >= 32;
-    cs.vu = (unsigned)cp * 8;
-    cs.vv = (unsigned)(cp + (n >> 1)) * 8;
-    cs.v = cs.hi ? cs.vv : cs.vu;
-    cs.sg = cs.hi ? -1.0 : 1.0;
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4)))
+k_scale(int n, size_t n_poly, double* dt, Tables tb) {
+  constexpr int LB = L + 1, W = L + LB;
+  __shared__ v4i tab1[conv_entries(L, LB)];
+  __shared__ v4i tab2[conv_entries(LB, L)];
+  // a lane's constants depend on the coefficient's half: both rows of t_qhinv
+  // and c1 in LDS, limb i's at 2 i
+  __shared__ double kl[2 * W];
+  conv_table<conv_entries(L, LB)>(tab1, tb.mx_c2);
+  conv_table<conv_entries(LB, L)>(tab2, tb.mx_back);
+  for (int t = (int)threadIdx.x; t < 2 * W; t += (int)blockDim.x) {
+    const int i = t >> 1, r = t & 1;
+    kl[t] = i < L ? tb.t_qhinv[r * L + i] : tb.c1[r * LB + i - L];
   }
-  // FUSED: the two rows of t_qhinv and c1 copied into LDS once per block,
-  // so that each lane's constant (lower or upper row) is an LDS read that
-  // half a wave shares, not a vector memory load
-  __shared__ double kl[FUSED ? 2 * (L + LB) : 1];
-  if constexpr (FUSED) {
-    const int t = (int)threadIdx.x;
-    if (t < 2 * L) kl[t] = tb.t_qhinv[t];
-    if (t < 2 * LB) kl[2 * L + t] = tb.c1[t];
-    __syncthreads();
-  }
-  const unsigned vo = cs.v;
+  __syncthreads();
+  const int lane = (int)threadIdx.x & 63;
+  const bool hi = FUSED && lane >= 32;
+  const double sg = hi ? -1.0 : 1.0;
+  const double* kc = kl + (hi ? 1 : 0);
   const unsigned ls = (unsigned)n * 8;   // bytes per limb
-  const bool third = pb.pc % 3 == 2;
-  double y[L];
-  double S = 0.0;
+  const unsigned nb = poly_blocks(n, n_poly);
+  for (unsigned bk = blockIdx.x; bk < nb; bk += gridDim.x) {
+    // FUSED: the launcher requires N to be a multiple of the block (pb.ok holds)
+    const PolyBlock pb = poly_block(n, bk);
+    const auto rs = make_rsrc(dt + pb.pc * (size_t)W * n, (unsigned)(W * n * 8));
+    const int t0 = (int)threadIdx.x;
+    const int cp = ((pb.c - t0) >> 1) + (t0 >> 6) * 32 + (lane & 31);
+    const unsigned vo = FUSED ? (unsigned)(cp + (hi ? n >> 1 : 0)) * 8 : (unsigned)pb.c * 8;
+    double x[W];
 #pragma unroll
-  for (int i = 0; i < L; ++i) {
-    const int iq = opaque_idx(i);
-    const double p = cld(tb.p, iq), pinv = cld(tb.pinv, iq);
-    y[i] = mul_bal(coef_load_both<FUSED>(rs, cs, i * ls),
-                   coef_const<FUSED>(cs, FUSED ? kl : tb.t_qhinv, iq, L), p, pinv);
-    S += y[i] * pinv;
-  }
-  double v = __builtin_rint(S);
-  if (lift_near_half(S, v, tb)) {
-    double r[L];
+    for (int i = 0; i < W; ++i) x[i] = buf_load(rs, vo, i * ls);
+    loads_issued();
+    double S = 0.0;
+    v4i g0[conv_steps(L)], g1[conv_steps(L)];
+    {
+      double y[L];
 #pragma unroll
-    for (int i = 0; i < L; ++i) {
-      const double p = cld(tb.p, i), pinv = cld(tb.pinv, i);
-      r[i] = to_canonical(mul_bal(coef_load_both<FUSED>(rs, cs, i * ls),
-                                  coef_const<FUSED>(cs, tb.t_q, i, L), p, pinv),
-                          p);
-    }
-    v = __builtin_floor(S) + (mrc_greater_than_half<L>(r, tb.p, tb.pinv, tb.mrc_inv, tb.mrc_half) ? 1.0 : 0.0);
-    atomicAdd(tb.margin + (FUSED ? MARGIN_SCALE_SPLIT : MARGIN_SCALE), 1ull);
-  }
-  // Split conversions (conv_row).  The base-B residues w_k wait in LDS (this
-  // thread's own slots, [LB][blockDim]) between the two conversions, so
-  // that the split inputs of one and of the other are never live together.
-  // Every sum before a reduction stays below 2^53 (at most (L / 4 + 7.2 +
-  // 1.75 + L/2 + 1) 2^48), where reduce_bal is exact with its result within
-  // p/2 + 4, so |w_k| <= 2^48.
-  extern __shared__ double wpark[];
-  double* wp = wpark + threadIdx.x;
-  const int bs = (int)blockDim.x;
-  double S2 = 0.0;
-  {
-    double yh[L], yl[L];
+      for (int s = 0; s < conv_steps(L); ++s) {
+        const double* kq = step_consts(tb.kq, s);
 #pragma unroll
-    for (int i = 0; i < L; ++i) split24(y[i], yh[i], yl[i]);
-#pragma unroll
-    for (int k = 0; k < LB; ++k) {
-      const int kq = opaque_idx(k), pk = L + kq;
-      const double b = cld(tb.p, pk), binv = cld(tb.pinv, pk);
-      const double* sp = opaque_row(tb.c2_sp, k * L * 2);
-      const double acc = mul_lazy(coef_load_both<FUSED>(rs, cs, (L + k) * ls),
-                                  coef_const<FUSED>(cs, FUSED ? kl + 2 * L : tb.c1, kq, LB), b, binv) +
-                         v * cld(tb.b_hat_inv, kq) -
-                         conv_row<L>(yh, yl, sp, b, binv);
-      const double w = reduce_bal(acc, b, binv);
-      wp[k * bs] = w;
-      S2 += w * binv;
-    }
-  }
-  const double v2 = __builtin_rint(S2);
-  if (__builtin_fabs(S2 - v2) > 0.25) atomicAdd(tb.margin + MARGIN_FAULT, 1ull);
-  double wh[LB], wl[LB];
-#pragma unroll
-  for (int k = 0; k < LB; ++k) split24(wp[k * bs], wh[k], wl[k]);
-  const bool pairs = A > 1 && third;
-  double grp[A];   // the current digit group's canonical mixed-radix digits
-#pragma unroll
-  for (int k = 0; k < A; ++k) grp[k] = 0.0;
-  // where the outputs go: in place, or the digit source's own buffer and
-  // position (see src above).  Every input has been read by now; formed
-  // here, the destination's scalars are live only in this loop.
-  // (three-prime digits only: with 16 or 17 primes the destination's
-  // scalars spill the conversions' constants, measured slower)
-  const bool own = A == 3 && third && tb.dig_src;
-  const auto rw = make_rsrc(own ? tb.dig_src + (pb.pc / 3) * (size_t)(2 * (L + A)) * n
-                                : dt + pb.pc * (size_t)(L + LB) * n,
-                            (unsigned)((own ? L : L + LB) * n * 8));
-  const unsigned wo = own ? (((vo >> 3) & 1u) * (unsigned)(n >> 1) + (vo >> 4)) * 8u : vo;
-#pragma unroll
-  for (int i = 0; i < L; ++i) {
-    const int iq = opaque_idx(i);
-    const double q = cld(tb.p, iq), qinv = cld(tb.pinv, iq);
-    const double* sp = opaque_row(tb.b_hat_q_sp, i * LB * 2);
-    const double acc = conv_row<LB>(wh, wl, sp, q, qinv) -
-                       v2 * cld(tb.B_q, iq);
-    const double r = reduce_bal(acc, q, qinv);
-    // the third component is only read as relinearization digits: its
-    // canonical residues, or with A primes per digit each digit's canonical
-    // mixed-radix digits (Garner: limb g + m of the group starting at g gets
-    // v_m = t_m, t_0 = d_{g+m}, t_{k+1} = [(t_k - v_k) q_{g+k}^-1]_{q_{g+m}};
-    // every difference is below 2^49 < 2 q)
-    double o = third ? to_canonical(r, q) : r;
-    if constexpr (A > 1) {
-      const int m = i % A;
-      if (pairs && m > 0) {
-        double tt = o;
-#pragma unroll
-        for (int k = 0; k < m; ++k)
-          tt = mul_bal(tt - grp[k], cld(tb.mrc_inv, (iq - m + k) * L + iq), q, qinv);
-        o = to_canonical(tt, q);
+        for (int j = 0; j < 4 && 4 * s + j < L; ++j) {
+          const int i = 4 * s + j;
+          const double p = cld(kq, 4 * j), pinv = cld(kq, 4 * j + 1);
+          y[i] = mul_bal(FUSED ? pair_combine(x[i], sg) : x[i], kc[2 * i], p, pinv);
+          S += y[i] * pinv;
+        }
+        pack_step<L>(y, s, g0[s], g1[s]);
       }
-      grp[m] = o;
     }
-    buf_store(o, rw, wo, i * ls);
+    double v = __builtin_rint(S);
+    if (pb.ok && lift_near_half(S, v, tb)) {
+      // (both of a pair's values read again: its other lane may not be here)
+      double r[L];
+      const unsigned vu = FUSED ? (unsigned)cp * 8 : vo;
+#pragma unroll
+      for (int i = 0; i < L; ++i) {
+        const double p = cld(tb.p, i), pinv = cld(tb.pinv, i);
+        const double u = buf_load(rs, vu, i * ls);
+        const double d = FUSED ? __builtin_fma(sg, buf_load(rs, vu + (unsigned)n * 4, i * ls), u) : u;
+        r[i] = to_canonical(mul_bal(d, tb.t_q[(hi ? L : 0) + i], p, pinv), p);
+      }
+      v = __builtin_floor(S) + (mrc_greater_than_half<L>(r, tb.p, tb.pinv, tb.mrc_inv, tb.mrc_half) ? 1.0 : 0.0);
+      atomicAdd(tb.margin + (FUSED ? MARGIN_SCALE_SPLIT : MARGIN_SCALE), 1ull);
+    }
+    // The first conversion's outputs, four base-B residues w_k per tile, are
+    // the second's inputs, four per step: each tile's are packed at once, so
+    // only their bytes are kept.  Every sum before a reduction stays below
+    // 2^53 (a lazy product, |v b_hat_inv| <= (L / 2 + 1) 2^48 and |conv_value|
+    // < 0.98 2^49), where reduce_bal is exact with its result within p/2 + 4,
+    // so |w_k| <= 2^48.
+    double S2 = 0.0;
+    v4i h0[conv_steps(LB)], h1[conv_steps(LB)];
+    static_assert(conv_tiles(LB) == conv_steps(LB), "a tile's outputs are a step's inputs");
+#pragma unroll
+    for (int t = 0; t < conv_tiles(LB); ++t) {
+      const double* kb = step_consts(tb.kb, t);
+      ConvSum sm[4];
+      conv_tile<L>(tab1 + t * conv_steps(L) * 64, g0, g1, sm);
+      double w[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int k = 4 * t + j;
+        w[j] = 0.0;
+        if (k >= LB) continue;
+        const double b = cld(kb, 4 * j), binv = cld(kb, 4 * j + 1);
+        const double d = FUSED ? pair_combine(x[L + k], sg) : x[L + k];
+        const double acc = __builtin_fma(v, cld(kb, 4 * j + 2),
+                                         mul_lazy(d, kc[2 * (L + k)], b, binv)) -
+                           conv_value<L>(sm[j], b, binv);
+        w[j] = reduce_bal(acc, b, binv);
+        S2 += w[j] * binv;
+      }
+      conv_pack(w, LB - 4 * t, h0[t], h1[t]);
+    }
+    const double v2 = __builtin_rint(S2);
+    if (pb.ok && __builtin_fabs(S2 - v2) > 0.25) atomicAdd(tb.margin + MARGIN_FAULT, 1ull);
+    // where the outputs go: in place, or the digit source's own buffer and
+    // position (see above; every input has been read by now)
+    if (pb.pc % 3 != 2) {
+      scale_out<L, A, false>(h0, h1, v2, rs, store_off(pb.ok, vo), ls, tab2, tb);
+    } else {
+      const bool own = A == 3 && tb.dig_src;
+      const auto rw = make_rsrc(own ? tb.dig_src + (pb.pc / 3) * (size_t)(2 * (L + A)) * n
+                                    : dt + pb.pc * (size_t)W * n,
+                                (unsigned)((own ? L : W) * n * 8));
+      const unsigned wo = own ? (((vo >> 3) & 1u) * (unsigned)(n >> 1) + (vo >> 4)) * 8u : vo;
+      scale_out<L, A, true>(h0, h1, v2, rw, store_off(pb.ok, wo), ls, tab2, tb);
+    }
   }
 }
 
@@ -660,37 +724,6 @@ __global__ void __launch_bounds__(256) k_moddown_finish(int n, int n_ct,
   }
 }
 
-// The rest of a lift whose L residues o (balanced) and y_i = [o_i
-// (Q/q_i)^-1]_{q_i}, S = sum_i y_i / q_i are already in registers: the
-// overflow count v (exact fallback near a half-integer, as k_lift), then
-// limbs L..2L of rs at vo.
-template <int L, int SITE>
-__device__ __forceinline__ void lift_tail(const double (&o)[L], const double (&y)[L], double S,
-                                          __amdgpu_buffer_rsrc_t rs, unsigned vo, unsigned ls,
-                                          const Tables& tb) {
-  constexpr int LB = L + 1;
-  double v = __builtin_rint(S);
-  if (lift_near_half(S, v, tb)) {
-    double r[L];
-#pragma unroll
-    for (int i = 0; i < L; ++i) r[i] = to_canonical(o[i], cld(tb.p, i));
-    v = __builtin_floor(S) + (mrc_greater_than_half<L>(r, tb.p, tb.pinv, tb.mrc_inv, tb.mrc_half) ? 1.0 : 0.0);
-    atomicAdd(tb.margin + SITE, 1ull);
-  }
-  double yh[L], yl[L];
-#pragma unroll
-  for (int i = 0; i < L; ++i) split24(y[i], yh[i], yl[i]);
-#pragma unroll
-  for (int k = 0; k < LB; ++k) {
-    const int kq = opaque_idx(k), pk = L + kq;
-    const double bb = cld(tb.p, pk), binv = cld(tb.pinv, pk);
-    const double* sp = opaque_row(tb.q_hat_b_sp, k * L * 2);
-    const double a = conv_row<L>(yh, yl, sp, bb, binv) -
-                     v * cld(tb.Q_b, kq);
-    buf_store(reduce_bal(a, bb, binv), rs, vo, (L + k) * ls);
-  }
-}
-
 // The mod-down of the split inverse's output (k_moddown, FUSED) followed by
 // the lift of its result (k_lift): within the squaring chain the next level
 // lifts exactly what this level's mod-down writes, so one kernel saves
@@ -699,60 +732,80 @@ __device__ __forceinline__ void lift_tail(const double (&o)[L], const double (&y
 // coefficients of a pair (c, c + N/2) and exchange the key-switch sum's half
 // outputs as the scale-and-round does, with the last inverse stage's
 // twiddle folded into the second rows of NP_inv_q and ninv_P.
+// Bound by memory traffic: 33 limbs in and 31 out per polynomial, 1.07 GB at
+// 32 ciphertexts in 204 us (5.3 TB/s; 206 with the lift as split FMAs on the
+// VALU), at one ciphertext 15 us (21).
 template <int L, int A>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
-k_moddown_lift(int n, size_t n_poly,
-                                                      const double* __restrict__ acc,
-                                                      const double* __restrict__ dt,
-                                                      double* __restrict__ ext, Tables tb) {
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4)))
+k_moddown_lift(int n, size_t n_poly, const double* __restrict__ acc,
+               const double* __restrict__ dt, double* __restrict__ ext, Tables tb) {
   constexpr int K = L + A;
   constexpr int W = 2 * L + 1;
-  const PolyBlock pb = poly_block(n, n_poly);   // poly = ct * 2 + b
-  if (!pb.ok) return;
+  __shared__ v4i tab[conv_entries(L, L + 1)];
+  __shared__ double kl[2 * K];   // NP_inv_q's and ninv_P's two rows, limb i's at 2 i
+  conv_table<conv_entries(L, L + 1)>(tab, tb.mx_lift);
   const int t = (int)threadIdx.x, lane = t & 63;
-  const int cp = ((pb.c - t) >> 1) + (t >> 6) * 32 + (lane & 31);
+  if (t < 2 * K) kl[t] = t < 2 * L ? tb.NP_inv_q[(t & 1) * L + (t >> 1)] : tb.ninv_P[t - 2 * L];
+  static_assert(2 * K <= 128, "one entry per thread of the smallest block");
+  __syncthreads();
   const bool hi = lane >= 32;
   const double sg = hi ? -1.0 : 1.0;
-  const int ht = n >> 6;                         // 512: see k_ntt_inv_half
-  const unsigned pos = (unsigned)((cp / ht) * 2 * ht + cp % ht + (hi ? ht : 0)) * 8;
-  const unsigned vo = (unsigned)(cp + (hi ? n >> 1 : 0)) * 8;
-  const unsigned ls = (unsigned)n * 8;
-  const size_t cb = pb.pc, ct = cb >> 1;
-  const int b = (int)(cb & 1);
-  const auto ra = make_rsrc(acc + cb * (size_t)K * n, (unsigned)(K * n * 8));
-  const auto re = make_rsrc(dt + (ct * 3 + b) * (size_t)W * n, (unsigned)(L * n * 8));
-  const auto rs = make_rsrc(ext + cb * (size_t)W * n, (unsigned)(W * n * 8));
-  const int row = hi ? 1 : 0;
-  // [N^-1 acc_Pk]_Pk of this coefficient (balanced), then the centred
-  // residue's mixed-radix digits
-  const int ip = 2 * L + 1;
-  double as[A], kP[A];
+  const double* kc = kl + (hi ? 1 : 0);
+  const unsigned nb = poly_blocks(n, n_poly);
+  for (unsigned bk = blockIdx.x; bk < nb; bk += gridDim.x) {
+    const PolyBlock pb = poly_block(n, bk);   // poly = ct * 2 + b
+    const int cp = ((pb.c - t) >> 1) + (t >> 6) * 32 + (lane & 31);
+    const int ht = n >> 6;                         // 512: see k_ntt_inv_half
+    const unsigned pos = (unsigned)((cp / ht) * 2 * ht + cp % ht + (hi ? ht : 0)) * 8;
+    const unsigned vo = (unsigned)(cp + (hi ? n >> 1 : 0)) * 8;
+    const unsigned ls = (unsigned)n * 8;
+    const size_t cb = pb.pc, ct = cb >> 1;
+    const int b = (int)(cb & 1);
+    const auto ra = make_rsrc(acc + cb * (size_t)K * n, (unsigned)(K * n * 8));
+    const auto re = make_rsrc(dt + (ct * 3 + b) * (size_t)W * n, (unsigned)(L * n * 8));
+    const auto rs = make_rsrc(ext + cb * (size_t)W * n, (unsigned)(W * n * 8));
+    // every load is issued before the first use
+    double xa[K], e[L];
 #pragma unroll
-  for (int m = 0; m < A; ++m) {
-    const double xP = buf_load(ra, pos, (L + m) * ls);
-    as[m] = mul_bal(pair_combine(xP, sg), tb.ninv_P[2 * m + row], cld(tb.p, ip + m),
-                    cld(tb.pinv, ip + m));
+    for (int m = 0; m < A; ++m) xa[L + m] = buf_load(ra, pos, (L + m) * ls);
+#pragma unroll
+    for (int i = 0; i < L; ++i) {
+      xa[i] = buf_load(ra, pos, i * ls);
+      e[i] = buf_load(re, vo, i * ls);
+    }
+    loads_issued();
+    // [N^-1 acc_Pk]_Pk of this coefficient (balanced), then the centred
+    // residue's mixed-radix digits
+    const int ip = 2 * L + 1;
+    double as[A], kP[A];
+#pragma unroll
+    for (int m = 0; m < A; ++m)
+      as[m] = mul_bal(pair_combine(xa[L + m], sg), kc[2 * (L + m)], cld(tb.p, ip + m),
+                      cld(tb.pinv, ip + m));
+    special_digits<A>(as, kP, tb, L);
+    double o[L], y[L];
+    double S = 0.0;
+    v4i g0[conv_steps(L)], g1[conv_steps(L)];
+#pragma unroll
+    for (int s = 0; s < conv_steps(L); ++s) {
+      const double* kq = step_consts(tb.kq, s);
+      const double* km = opaque_row(tb.km, 4 * A * s);
+#pragma unroll
+      for (int j = 0; j < 4 && 4 * s + j < L; ++j) {
+        const int i = 4 * s + j;
+        const double q = cld(kq, 4 * j), qinv = cld(kq, 4 * j + 1);
+        double r = mul_lazy(pair_combine(xa[i], sg), kc[2 * i], q, qinv);
+#pragma unroll
+        for (int m = 0; m < A; ++m) r -= mul_lazy(kP[m], cld(km, A * j + m), q, qinv);
+        o[i] = reduce_bal(e[i] + r, q, qinv);
+        y[i] = mul_bal(o[i], cld(kq, 4 * j + 2), q, qinv);
+        S += y[i] * qinv;
+        buf_store(o[i], rs, vo, i * ls);
+      }
+      pack_step<L>(y, s, g0[s], g1[s]);
+    }
+    lift_tail<L, MARGIN_MODDOWN_LIFT>(o, g0, g1, S, rs, vo, ls, pb.ok, tab, tb);
   }
-  special_digits<A>(as, kP, tb, L);
-  // the new ciphertext's residues are stored only after every load: buffer
-  // stores between them would make each limb's loads wait for the previous
-  // limb's (the compiler cannot tell the buffers apart)
-  double o[L], y[L];
-  double S = 0.0;
-#pragma unroll
-  for (int i = 0; i < L; ++i) {
-    const int iq = opaque_idx(i);
-    const double q = cld(tb.p, iq), qinv = cld(tb.pinv, iq);
-    const double x = buf_load(ra, pos, i * ls);
-    const double r =
-        moddown_term<L, A>(pair_combine(x, sg), tb.NP_inv_q[row * L + iq], kP, iq, q, qinv, tb);
-    o[i] = reduce_bal(buf_load(re, vo, i * ls) + r, q, qinv);
-    y[i] = mul_bal(o[i], cld(tb.q_hat_inv, iq), q, qinv);
-    S += y[i] * qinv;
-  }
-#pragma unroll
-  for (int i = 0; i < L; ++i) buf_store(o[i], rs, vo, i * ls);
-  lift_tail<L, MARGIN_MODDOWN_LIFT>(o, y, S, rs, vo, ls, tb);
 }
 
 // Subtraction z = [x - y]_Q of two ciphertexts (int64, canonical; y one
@@ -762,68 +815,100 @@ k_moddown_lift(int n, size_t n_poly,
 // wt (table not null): a batched wave's ciphertexts, x and y read through
 // the table (a broadcast y is every entry's y).
 template <int L>
-__global__ void __launch_bounds__(256) k_sub_lift(int n, size_t n_poly,
-                                                  const int64_t* __restrict__ xs,
-                                                  const int64_t* __restrict__ ys, int y_bcast,
-                                                  double* __restrict__ ext, Tables tb, WaveTab wt) {
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4)))
+k_sub_lift(int n, size_t n_poly, const int64_t* __restrict__ xs, const int64_t* __restrict__ ys,
+           int y_bcast, double* __restrict__ ext, Tables tb, WaveTab wt) {
   constexpr int W = 2 * L + 1;
-  const PolyBlock pb = poly_block(n, n_poly);   // poly = ct * 2 + b
-  if (!pb.ok) return;
-  const size_t cb = pb.pc;
-  const int b = (int)(cb & 1);
-  const int64_t* xp;
-  const int64_t* yp;
-  if (wt.table) {
-    const CtPtrs e = wt.table[(size_t)(*wt.wave) * wt.stride + (cb >> 1)];
-    xp = e.x + (size_t)b * L * n + pb.c;
-    yp = e.y + (size_t)b * L * n + pb.c;
-  } else {
-    xp = xs + cb * (size_t)L * n + pb.c;
-    yp = (y_bcast ? ys + (size_t)b * L * n : ys + cb * (size_t)L * n) + pb.c;
-  }
-  const auto rs = make_rsrc(ext + cb * (size_t)W * n, (unsigned)(W * n * 8));
-  const unsigned vo = (unsigned)pb.c * 8, ls = (unsigned)n * 8;
-  double o[L], y[L];
-  double S = 0.0;
+  __shared__ v4i tab[conv_entries(L, L + 1)];
+  conv_table<conv_entries(L, L + 1)>(tab, tb.mx_lift);
+  __syncthreads();
+  const unsigned nb = poly_blocks(n, n_poly);
+  for (unsigned bk = blockIdx.x; bk < nb; bk += gridDim.x) {
+    const PolyBlock pb = poly_block(n, bk);   // poly = ct * 2 + b
+    const size_t cb = pb.pc;
+    const int b = (int)(cb & 1);
+    const int64_t* xp;
+    const int64_t* yp;
+    if (wt.table) {
+      const CtPtrs e = wt.table[(size_t)(*wt.wave) * wt.stride + (cb >> 1)];
+      xp = e.x + (size_t)b * L * n + pb.c;
+      yp = e.y + (size_t)b * L * n + pb.c;
+    } else {
+      xp = xs + cb * (size_t)L * n + pb.c;
+      yp = (y_bcast ? ys + (size_t)b * L * n : ys + cb * (size_t)L * n) + pb.c;
+    }
+    const auto rs = make_rsrc(ext + cb * (size_t)W * n, (unsigned)(W * n * 8));
+    const unsigned vo = (unsigned)pb.c * 8, ls = (unsigned)n * 8;
+    int64_t xv[L], yv[L];
 #pragma unroll
-  for (int i = 0; i < L; ++i) {
-    const int iq = opaque_idx(i);
-    const double q = cld(tb.p, iq), qinv = cld(tb.pinv, iq);
-    o[i] = reduce_bal((double)xp[(size_t)i * n] - (double)yp[(size_t)i * n], q, qinv);
-    y[i] = mul_bal(o[i], cld(tb.q_hat_inv, iq), q, qinv);
-    S += y[i] * qinv;
-  }
+    for (int i = 0; i < L; ++i) {
+      xv[i] = xp[(size_t)i * n];
+      yv[i] = yp[(size_t)i * n];
+    }
+    loads_issued();
+    double o[L], y[L];
+    double S = 0.0;
+    const unsigned so = store_off(pb.ok, vo);
+    v4i g0[conv_steps(L)], g1[conv_steps(L)];
 #pragma unroll
-  for (int i = 0; i < L; ++i) buf_store(o[i], rs, vo, i * ls);
-  lift_tail<L, MARGIN_SUB_LIFT>(o, y, S, rs, vo, ls, tb);
+    for (int s = 0; s < conv_steps(L); ++s) {
+      const double* kq = step_consts(tb.kq, s);
+#pragma unroll
+      for (int j = 0; j < 4 && 4 * s + j < L; ++j) {
+        const int i = 4 * s + j;
+        const double q = cld(kq, 4 * j), qinv = cld(kq, 4 * j + 1);
+        o[i] = reduce_bal((double)xv[i] - (double)yv[i], q, qinv);
+        y[i] = mul_bal(o[i], cld(kq, 4 * j + 2), q, qinv);
+        S += y[i] * qinv;
+        buf_store(o[i], rs, so, i * ls);
+      }
+      pack_step<L>(y, s, g0[s], g1[s]);
+    }
+    lift_tail<L, MARGIN_SUB_LIFT>(o, g0, g1, S, rs, vo, ls, pb.ok, tab, tb);
+  }
 }
 
 // Canonical int64 residues of n_poly polynomials ([n_poly][L][N]) into ext
 // limbs 0..L-1 (balanced) and their lift into limbs L..2L: the conversion
 // (k_i64_to_polys) and k_lift in one pass, the same arithmetic.
 template <int L>
-__global__ void __launch_bounds__(256) k_i64_lift(int n, size_t n_poly,
-                                                  const int64_t* __restrict__ in,
-                                                  double* __restrict__ ext, Tables tb) {
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4)))
+k_i64_lift(int n, size_t n_poly, const int64_t* __restrict__ in, double* __restrict__ ext,
+           Tables tb) {
   constexpr int W = 2 * L + 1;
-  const PolyBlock pb = poly_block(n, n_poly);
-  if (!pb.ok) return;
-  const int64_t* ip = in + pb.pc * (size_t)L * n + pb.c;
-  const auto rs = make_rsrc(ext + pb.pc * (size_t)W * n, (unsigned)(W * n * 8));
-  const unsigned vo = (unsigned)pb.c * 8, ls = (unsigned)n * 8;
-  double o[L], y[L];
-  double S = 0.0;
+  __shared__ v4i tab[conv_entries(L, L + 1)];
+  conv_table<conv_entries(L, L + 1)>(tab, tb.mx_lift);
+  __syncthreads();
+  const unsigned nb = poly_blocks(n, n_poly);
+  for (unsigned bk = blockIdx.x; bk < nb; bk += gridDim.x) {
+    const PolyBlock pb = poly_block(n, bk);
+    const int64_t* ip = in + pb.pc * (size_t)L * n + pb.c;
+    const auto rs = make_rsrc(ext + pb.pc * (size_t)W * n, (unsigned)(W * n * 8));
+    const unsigned vo = (unsigned)pb.c * 8, ls = (unsigned)n * 8;
+    int64_t xv[L];
 #pragma unroll
-  for (int i = 0; i < L; ++i) {
-    const int iq = opaque_idx(i);
-    const double q = cld(tb.p, iq), qinv = cld(tb.pinv, iq);
-    o[i] = from_u64(ip[(size_t)i * n], q);
-    y[i] = mul_bal(o[i], cld(tb.q_hat_inv, iq), q, qinv);
-    S += y[i] * qinv;
+    for (int i = 0; i < L; ++i) xv[i] = ip[(size_t)i * n];
+    loads_issued();
+    double o[L], y[L];
+    double S = 0.0;
+    const unsigned so = store_off(pb.ok, vo);
+    v4i g0[conv_steps(L)], g1[conv_steps(L)];
+#pragma unroll
+    for (int s = 0; s < conv_steps(L); ++s) {
+      const double* kq = step_consts(tb.kq, s);
+#pragma unroll
+      for (int j = 0; j < 4 && 4 * s + j < L; ++j) {
+        const int i = 4 * s + j;
+        const double q = cld(kq, 4 * j), qinv = cld(kq, 4 * j + 1);
+        o[i] = from_u64(xv[i], q);
+        y[i] = mul_bal(o[i], cld(kq, 4 * j + 2), q, qinv);
+        S += y[i] * qinv;
+        buf_store(o[i], rs, so, i * ls);
+      }
+      pack_step<L>(y, s, g0[s], g1[s]);
+    }
+    lift_tail<L, MARGIN_I64_LIFT>(o, g0, g1, S, rs, vo, ls, pb.ok, tab, tb);
   }
-#pragma unroll
-  for (int i = 0; i < L; ++i) buf_store(o[i], rs, vo, i * ls);
-  lift_tail<L, MARGIN_I64_LIFT>(o, y, S, rs, vo, ls, tb);
 }
 
 // ------------------------------------------------------ plaintext products ---
@@ -1281,9 +1366,16 @@ __global__ void __launch_bounds__(256) k_check_residues(int n, int L, size_t tot
 
 // ---------------------------------------------------------------- host ---
 
-// grid of the per-poly block mapping (see poly_block)
-static inline dim3 poly_grid(size_t n_poly, int n, int block) {
-  return dim3((unsigned)(n_poly * (size_t)((n + block - 1) / block)));
+// Workgroup and grid of the kernels that hold conversion constants in LDS
+// (see poly_block): twice the tuned block, so that more waves share a copy,
+// and at most POLY_GRID workgroups, which then take several blocks each.
+constexpr size_t POLY_GRID = 4096;
+
+static inline int poly_threads(const Dims& d) { return 2 * d.block; }
+
+static inline dim3 poly_grid(const Dims& d, size_t n_poly) {
+  const size_t nb = n_poly * (size_t)((d.n + poly_threads(d) - 1) / poly_threads(d));
+  return dim3((unsigned)std::min(nb, POLY_GRID));
 }
 
 static inline dim3 grid_for(size_t total, int block = 256) {
@@ -1299,7 +1391,7 @@ hipError_t run_lift(const Dims& d, double* ext, const Tables& tb, hipStream_t st
   const size_t np = (size_t)d.n_ct * 2;
   switch (d.L) {
 #define C_(L_) \
-  case L_: hipLaunchKernelGGL(k_lift<L_>, poly_grid(np, d.n, d.block), dim3(d.block), 0, st, d.n, np, ext, tb); break;
+  case L_: hipLaunchKernelGGL(k_lift<L_>, poly_grid(d, np), dim3(poly_threads(d)), 0, st, d.n, np, ext, tb); break;
     NSHE_L_CASES(C_)
 #undef C_
     default: return hipErrorInvalidValue;
@@ -1350,7 +1442,7 @@ hipError_t run_i64_lift(const Dims& d, const int64_t* in, double* ext, const Tab
   switch (d.L) {
 #define C_(L_)                                                                            \
   case L_:                                                                                \
-    hipLaunchKernelGGL(k_i64_lift<L_>, poly_grid(np, d.n, d.block), dim3(d.block), 0, st, \
+    hipLaunchKernelGGL(k_i64_lift<L_>, poly_grid(d, np), dim3(poly_threads(d)), 0, st, \
                        d.n, np, in, ext, tb);                                             \
     break;
     NSHE_L_CASES(C_)
@@ -1366,7 +1458,7 @@ hipError_t run_sub_lift(const Dims& d, const int64_t* x, const int64_t* y, int y
   switch (d.L) {
 #define C_(L_)                                                                            \
   case L_:                                                                                \
-    hipLaunchKernelGGL(k_sub_lift<L_>, poly_grid(np, d.n, d.block), dim3(d.block), 0, st, \
+    hipLaunchKernelGGL(k_sub_lift<L_>, poly_grid(d, np), dim3(poly_threads(d)), 0, st, \
                        d.n, np, x, y, y_bcast, ext, tb, d.tab);                           \
     break;
     NSHE_L_CASES(C_)
@@ -1378,11 +1470,11 @@ hipError_t run_sub_lift(const Dims& d, const int64_t* x, const int64_t* y, int y
 
 hipError_t run_moddown_lift(const Dims& d, const double* acc, const double* dt, double* ext,
                             const Tables& tb, hipStream_t st) {
-  if (!d.fused) return hipErrorInvalidValue;
+  if (!d.fused || d.n % poly_threads(d)) return hipErrorInvalidValue;
   const size_t np = (size_t)d.n_ct * 2;
 #define C_(L_, A_)                                                                           \
   case L_:                                                                                   \
-    hipLaunchKernelGGL((k_moddown_lift<L_, A_>), poly_grid(np, d.n, d.block), dim3(d.block), \
+    hipLaunchKernelGGL((k_moddown_lift<L_, A_>), poly_grid(d, np), dim3(poly_threads(d)), \
                        0, st, d.n, np, acc, dt, ext, tb);                                    \
     break;
 #define C1_(L_) C_(L_, 1)
@@ -1419,16 +1511,16 @@ hipError_t run_scale(const Dims& d, double* dt, const Tables& tb, hipStream_t st
   const size_t np = (size_t)d.n_ct * 3;
   Tables t = tb;
   t.dig_src = src;
-  // the split-inverse variant's barrier needs whole blocks (see k_scale)
-  if (d.fused && d.n % d.block) return hipErrorInvalidValue;
+  // the split-inverse variant takes whole blocks (see k_scale)
+  if (d.fused && d.n % poly_threads(d)) return hipErrorInvalidValue;
 #define C_(L_, A_) \
   case L_:                                                                                     \
     if (d.fused)                                                                               \
-      hipLaunchKernelGGL((k_scale<L_, true, A_>), poly_grid(np, d.n, d.block), dim3(d.block),  \
-                         (size_t)(L_ + 1) * d.block * 8, st, d.n, np, dt, t);          \
+      hipLaunchKernelGGL((k_scale<L_, true, A_>), poly_grid(d, np), dim3(poly_threads(d)),  \
+                         0, st, d.n, np, dt, t);          \
     else                                                                                       \
-      hipLaunchKernelGGL((k_scale<L_, false, A_>), poly_grid(np, d.n, d.block), dim3(d.block), \
-                         (size_t)(L_ + 1) * d.block * 8, st, d.n, np, dt, t);          \
+      hipLaunchKernelGGL((k_scale<L_, false, A_>), poly_grid(d, np), dim3(poly_threads(d)), \
+                         0, st, d.n, np, dt, t);          \
     break;
 #define C1_(L_) C_(L_, 1)
 #define C2_(L_) C_(L_, 2)
