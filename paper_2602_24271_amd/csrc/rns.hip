@@ -413,6 +413,20 @@ k_scale(int n, size_t n_poly, double* dt, Tables tb) {
 
 // ---------------------------------------------------------- key switching ---
 
+// Digits whose loads are in flight together in the key-switch product, for
+// chunks of ch ciphertexts and `per` loads per digit: as many as keep the
+// loaded values within about 80 registers.  One digit at a time costs one
+// memory latency per digit, which is most of the time at one ciphertext (24 ->
+// 16 us with three-prime digits); from eight ciphertexts on the chunk's own
+// loads fill the pipeline, and one digit at a time, its loads free to move
+// into the products before them, is the faster (2^12-point ring, 8
+// ciphertexts, 17 digits: 22 us against 27 in batches).
+constexpr int mac_batch(int dn, int ch, int per) {
+  const int fit = ch >= 8 || 40 / per < 1 ? 1 : 40 / per;
+  const int rounds = (dn + fit - 1) / fit;
+  return (dn + rounds - 1) / rounds;
+}
+
 // acc[ct][b][i] = sum_j dig[ct][j][i] * evk[j][b][i] (NTT domain) over the
 // L / A digits, limbs i = 0..L+A-1 (the last A mod the special primes).
 // The key is read once per chunk of CH ciphertexts.
@@ -421,6 +435,7 @@ __global__ void __launch_bounds__(256) k_ks_mac(int n, int n_ct, const double* d
                                                 const double* evk, double* acc, Tables tb) {
   constexpr int K = L + A;
   constexpr int DN = L / A;
+  constexpr int UJ = mac_batch(DN, CH, 2 + CH);
   const size_t gid = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (gid >= (size_t)K * n) return;
   const int i = (int)(gid / n);
@@ -431,38 +446,54 @@ __global__ void __launch_bounds__(256) k_ks_mac(int n, int n_ct, const double* d
     double a0[CH], a1[CH];
 #pragma unroll
     for (int u = 0; u < CH; ++u) a0[u] = a1[u] = 0.0;
-    for (int j = 0; j < DN; ++j) {
-      const double e0 = evk[((size_t)(j * 2 + 0) * K + i) * n + c];
-      const double e1 = evk[((size_t)(j * 2 + 1) * K + i) * n + c];
-      // every load of the chunk is issued before the products: past the
-      // last ciphertext the index is clamped (a valid address) and the
-      // result is never stored
-      double dv[CH];
+    auto batch = [&](int j0) {
+      // every load of the chunk and batch is issued before the products: past
+      // the last ciphertext or digit the index is clamped (a valid address)
+      // and the value is not used
+      double e0[UJ], e1[UJ], dv[UJ][CH];
 #pragma unroll
-      for (int u = 0; u < CH; ++u) {
-        const int cu = c0 + u < n_ct ? c0 + u : n_ct - 1;
-        dv[u] = __builtin_nontemporal_load(&dig[((size_t)(cu * DN + j) * K + i) * n + c]);
-      }
-#pragma unroll
-      for (int u = 0; u < CH; ++u) {
-        a0[u] += mul_lazy(dv[u], e0, p, pinv);
-        a1[u] += mul_lazy(dv[u], e1, p, pinv);
-      }
-      // digit transforms are not reduced at their end: |dv| < 15.1 p (at
-      // most ten unreduced stages from inputs below 2.61 p, the bound of a
-      // two-prime digit's value; 13.5 p from one-prime digits below 2 p and
-      // from three-prime digits, reduced to balanced form first;
-      // 6.1 p at N = 2^15), so each product with a balanced key is below
-      // (1/2 + 0.094 x 15.1) p = 1.92 p and eight of them plus a reduced sum
-      // stay below 15.9 p < 2^53 / p (> 16.6 p for p < 2^48.95): reduce the
-      // sums every 8 digits
-      if ((j & 7) == 7) {
+      for (int jj = 0; jj < UJ; ++jj) {
+        const int j = j0 + jj < DN ? j0 + jj : DN - 1;
+        e0[jj] = evk[((size_t)(j * 2 + 0) * K + i) * n + c];
+        e1[jj] = evk[((size_t)(j * 2 + 1) * K + i) * n + c];
 #pragma unroll
         for (int u = 0; u < CH; ++u) {
-          a0[u] = reduce_bal(a0[u], p, pinv);
-          a1[u] = reduce_bal(a1[u], p, pinv);
+          const int cu = c0 + u < n_ct ? c0 + u : n_ct - 1;
+          dv[jj][u] = __builtin_nontemporal_load(&dig[((size_t)(cu * DN + j) * K + i) * n + c]);
         }
       }
+      if constexpr (UJ > 1) loads_issued();
+#pragma unroll
+      for (int jj = 0; jj < UJ; ++jj) {
+        const int j = j0 + jj;
+        if (j >= DN) break;
+#pragma unroll
+        for (int u = 0; u < CH; ++u) {
+          a0[u] += mul_lazy(dv[jj][u], e0[jj], p, pinv);
+          a1[u] += mul_lazy(dv[jj][u], e1[jj], p, pinv);
+        }
+        // digit transforms are not reduced at their end: |dv| < 15.1 p (at
+        // most ten unreduced stages from inputs below 2.61 p, the bound of a
+        // two-prime digit's value; 13.5 p from one-prime digits below 2 p and
+        // from three-prime digits, reduced to balanced form first;
+        // 6.1 p at N = 2^15), so each product with a balanced key is below
+        // (1/2 + 0.094 x 15.1) p = 1.92 p and eight of them plus a reduced sum
+        // stay below 15.9 p < 2^53 / p (> 16.6 p for p < 2^48.95): reduce the
+        // sums every 8 digits
+        if ((j & 7) == 7) {
+#pragma unroll
+          for (int u = 0; u < CH; ++u) {
+            a0[u] = reduce_bal(a0[u], p, pinv);
+            a1[u] = reduce_bal(a1[u], p, pinv);
+          }
+        }
+      }
+    };
+    if constexpr (UJ > 1) {
+#pragma unroll 1
+      for (int j0 = 0; j0 < DN; j0 += UJ) batch(j0);
+    } else {
+      for (int j0 = 0; j0 < DN; ++j0) batch(j0);
     }
 #pragma unroll
     for (int u = 0; u < CH; ++u) {
@@ -490,6 +521,7 @@ __global__ void __launch_bounds__(256) k_ks_mac_par(int n_ct, const double* dig,
                                                     const double* evk, double* acc, Tables tb) {
   constexpr int K = L + A;
   constexpr int DN = L / A;
+  constexpr int UJ = mac_batch(DN, CH, 4 + 2 * CH);
   constexpr int NF = 1 << 15, NH = NF / 2;
   const int gid = blockIdx.x * 256 + threadIdx.x;
   if (gid >= K * NH) return;
@@ -506,39 +538,57 @@ __global__ void __launch_bounds__(256) k_ks_mac_par(int n_ct, const double* dig,
     double a00[CH], a01[CH], a10[CH], a11[CH];
 #pragma unroll
     for (int v = 0; v < CH; ++v) a00[v] = a01[v] = a10[v] = a11[v] = 0.0;
-    for (int j = 0; j < DN; ++j) {
-      const double* kj = evk + ((size_t)(j * 2) * K + i) * NF + p0;
-      const double e00 = kj[0], e01 = kj[1024];
-      const double e10 = kj[(size_t)K * NF], e11 = kj[(size_t)K * NF + 1024];
-      // every load of the chunk is issued before the products: past the
-      // last ciphertext the index is clamped (a valid address) and the
-      // result is never stored
-      double ev[CH], od[CH];
+    auto batch = [&](int j0) {
+      // every load of the chunk and batch is issued before the products: past
+      // the last ciphertext or digit the index is clamped (a valid address)
+      // and the value is not used
+      double e00[UJ], e01[UJ], e10[UJ], e11[UJ], ev[UJ][CH], od[UJ][CH];
 #pragma unroll
-      for (int v = 0; v < CH; ++v) {
-        const int cv = c0 + v < n_ct ? c0 + v : n_ct - 1;
-        const double* dp = dig + ((size_t)(cv * DN + j) * K + i) * NF + pe;
-        ev[v] = __builtin_nontemporal_load(dp);
-        od[v] = __builtin_nontemporal_load(dp + NH);
-      }
-#pragma unroll
-      for (int v = 0; v < CH; ++v) {
-        const double w = mul_lazy(od[v], z, p, pinv);
-        const double x0 = ev[v] + w, x1 = ev[v] - w;
-        a00[v] += mul_lazy(x0, e00, p, pinv);
-        a01[v] += mul_lazy(x1, e01, p, pinv);
-        a10[v] += mul_lazy(x0, e10, p, pinv);
-        a11[v] += mul_lazy(x1, e11, p, pinv);
-      }
-      if ((j & 7) == 7) {
+      for (int jj = 0; jj < UJ; ++jj) {
+        const int j = j0 + jj < DN ? j0 + jj : DN - 1;
+        const double* kj = evk + ((size_t)(j * 2) * K + i) * NF + p0;
+        e00[jj] = kj[0];
+        e01[jj] = kj[1024];
+        e10[jj] = kj[(size_t)K * NF];
+        e11[jj] = kj[(size_t)K * NF + 1024];
 #pragma unroll
         for (int v = 0; v < CH; ++v) {
-          a00[v] = reduce_bal(a00[v], p, pinv);
-          a01[v] = reduce_bal(a01[v], p, pinv);
-          a10[v] = reduce_bal(a10[v], p, pinv);
-          a11[v] = reduce_bal(a11[v], p, pinv);
+          const int cv = c0 + v < n_ct ? c0 + v : n_ct - 1;
+          const double* dp = dig + ((size_t)(cv * DN + j) * K + i) * NF + pe;
+          ev[jj][v] = __builtin_nontemporal_load(dp);
+          od[jj][v] = __builtin_nontemporal_load(dp + NH);
         }
       }
+      if constexpr (UJ > 1) loads_issued();
+#pragma unroll
+      for (int jj = 0; jj < UJ; ++jj) {
+        const int j = j0 + jj;
+        if (j >= DN) break;
+#pragma unroll
+        for (int v = 0; v < CH; ++v) {
+          const double w = mul_lazy(od[jj][v], z, p, pinv);
+          const double x0 = ev[jj][v] + w, x1 = ev[jj][v] - w;
+          a00[v] += mul_lazy(x0, e00[jj], p, pinv);
+          a01[v] += mul_lazy(x1, e01[jj], p, pinv);
+          a10[v] += mul_lazy(x0, e10[jj], p, pinv);
+          a11[v] += mul_lazy(x1, e11[jj], p, pinv);
+        }
+        if ((j & 7) == 7) {
+#pragma unroll
+          for (int v = 0; v < CH; ++v) {
+            a00[v] = reduce_bal(a00[v], p, pinv);
+            a01[v] = reduce_bal(a01[v], p, pinv);
+            a10[v] = reduce_bal(a10[v], p, pinv);
+            a11[v] = reduce_bal(a11[v], p, pinv);
+          }
+        }
+      }
+    };
+    if constexpr (UJ > 1) {
+#pragma unroll 1
+      for (int j0 = 0; j0 < DN; j0 += UJ) batch(j0);
+    } else {
+      for (int j0 = 0; j0 < DN; ++j0) batch(j0);
     }
 #pragma unroll
     for (int v = 0; v < CH; ++v) {
@@ -1554,22 +1604,35 @@ hipError_t run_ks_mac(const Dims& d, const double* dig, const double* evk, doubl
                       const Tables& tb, hipStream_t st) {
   const size_t total = (size_t)(d.L + d.alpha) * d.n;
   // a chunk wider than the ciphertexts present would only repeat its
-  // (clamped) loads and products: halve it down to them
+  // (clamped) loads and products: the narrowest that holds them
   int ch = d.ks_chunk;
-  while (ch > 4 && ch / 2 >= d.n_ct) ch /= 2;
+  while (ch > 1 && ch / 2 >= d.n_ct) ch /= 2;
   if (d.parity) {
     // four sums per ciphertext of a chunk: at most 16 ciphertexts
     if (d.n != (1 << 15)) return hipErrorInvalidValue;
     const size_t tp = (size_t)(d.L + d.alpha) * (d.n / 2);
     if (ch > 16) ch = 16;
+    // as few passes over the key as the widest chunk takes, evenly filled: 11
+    // ciphertexts run 12 wide, 20 as two chunks of 10 (12 wide)
+    const int passes = (d.n_ct + ch - 1) / ch, even = (d.n_ct + passes - 1) / passes;
+    for (int w : {1, 2, 3, 4, 6, 8, 12, 16})
+      if (w >= even) {
+        ch = std::min(ch, w);
+        break;
+      }
+#define P0_(L_, A_, CH_)                                                                         \
+  hipLaunchKernelGGL((k_ks_mac_par<L_, A_, CH_>), grid_for(tp), dim3(256), 0, st, d.n_ct, dig, evk, \
+                     acc, tb);
 #define P_(L_, A_) \
   case L_:                                                                                     \
-    if (ch == 4)                                                                               \
-      hipLaunchKernelGGL((k_ks_mac_par<L_, A_, 4>), grid_for(tp), dim3(256), 0, st, d.n_ct, dig, evk, acc, tb); \
-    else if (ch == 8)                                                                          \
-      hipLaunchKernelGGL((k_ks_mac_par<L_, A_, 8>), grid_for(tp), dim3(256), 0, st, d.n_ct, dig, evk, acc, tb); \
-    else                                                                                       \
-      hipLaunchKernelGGL((k_ks_mac_par<L_, A_, 16>), grid_for(tp), dim3(256), 0, st, d.n_ct, dig, evk, acc, tb); \
+    if (ch == 1) P0_(L_, A_, 1)                                                                \
+    else if (ch == 2) P0_(L_, A_, 2)                                                           \
+    else if (ch == 3) P0_(L_, A_, 3)                                                           \
+    else if (ch == 4) P0_(L_, A_, 4)                                                           \
+    else if (ch == 6) P0_(L_, A_, 6)                                                           \
+    else if (ch == 8) P0_(L_, A_, 8)                                                           \
+    else if (ch == 12) P0_(L_, A_, 12)                                                         \
+    else P0_(L_, A_, 16)                                                                       \
     break;
 #define P1_(L_) P_(L_, 1)
 #define P2_(L_) P_(L_, 2)
@@ -1596,18 +1659,20 @@ hipError_t run_ks_mac(const Dims& d, const double* dig, const double* evk, doubl
 #undef P2_
 #undef P3_
 #undef P_
+#undef P0_
     return hipGetLastError();
   }
+#define C0_(L_, A_, CH_)                                                                         \
+  hipLaunchKernelGGL((k_ks_mac<L_, A_, CH_>), grid_for(total), dim3(256), 0, st, d.n, d.n_ct, dig, \
+                     evk, acc, tb);
 #define C_(L_, A_) \
   case L_:                                                                                     \
-    if (ch == 4)                                                                               \
-      hipLaunchKernelGGL((k_ks_mac<L_, A_, 4>), grid_for(total), dim3(256), 0, st, d.n, d.n_ct, dig, evk, acc, tb); \
-    else if (ch == 8)                                                                          \
-      hipLaunchKernelGGL((k_ks_mac<L_, A_, 8>), grid_for(total), dim3(256), 0, st, d.n, d.n_ct, dig, evk, acc, tb); \
-    else if (ch == 32)                                                                         \
-      hipLaunchKernelGGL((k_ks_mac<L_, A_, 32>), grid_for(total), dim3(256), 0, st, d.n, d.n_ct, dig, evk, acc, tb); \
-    else                                                                                       \
-      hipLaunchKernelGGL((k_ks_mac<L_, A_, 16>), grid_for(total), dim3(256), 0, st, d.n, d.n_ct, dig, evk, acc, tb); \
+    if (ch == 1) C0_(L_, A_, 1)                                                                \
+    else if (ch == 2) C0_(L_, A_, 2)                                                           \
+    else if (ch == 4) C0_(L_, A_, 4)                                                           \
+    else if (ch == 8) C0_(L_, A_, 8)                                                           \
+    else if (ch == 32) C0_(L_, A_, 32)                                                         \
+    else C0_(L_, A_, 16)                                                                       \
     break;
 #define C1_(L_) C_(L_, 1)
 #define C2_(L_) C_(L_, 2)
@@ -1634,6 +1699,7 @@ hipError_t run_ks_mac(const Dims& d, const double* dig, const double* evk, doubl
 #undef C2_
 #undef C3_
 #undef C_
+#undef C0_
   return hipGetLastError();
 }
 
