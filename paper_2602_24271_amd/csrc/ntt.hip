@@ -610,6 +610,32 @@ __device__ __forceinline__ int xcd_item(int count) {
   return (b & 7) * per + (b >> 3);
 }
 
+// Work item of a digit-transform launch: its source (poly) and target limb,
+// `parts` workgroups per pair (the part is the low digit of the item).  The
+// digit transforms read one source limb per (ciphertext, digit) for all L +
+// alpha target primes.  Items run over half of the primes, then the sources,
+// then the half's primes, and each XCD takes an eighth of them: it keeps about
+// half the primes' twiddle tables in its L2, reads each of its sources once
+// and every source is read twice.  The eighths are equal whatever the number
+// of sources: by quarters of the sources, one ciphertext's five left two XCDs
+// idle and gave four of them more workgroups than CUs (34 us, now 22).
+__device__ __forceinline__ bool digit_item(const NttJob& job, int parts, int& poly, int& limb,
+                                           int* part = nullptr) {
+  int item = xcd_item(job.count * parts);
+  if (item >= job.count * parts) return false;
+  if (part) {
+    *part = item % parts;
+    item /= parts;
+  }
+  const int ph = (job.nlimb + 1) >> 1;                 // primes in half 0
+  const bool g = item >= ph * job.npoly;
+  const int np = g ? job.nlimb - ph : ph;
+  if (g) item -= ph * job.npoly;
+  poly = item / np;
+  limb = (g ? ph : 0) + item - poly * np;
+  return true;
+}
+
 template <int LOGN, int MODE>
 __global__ void __launch_bounds__(NttShape<LOGN>::T)
 k_ntt_fwd(NttJob job, Tables tb) {
@@ -617,21 +643,7 @@ k_ntt_fwd(NttJob job, Tables tb) {
   __shared__ uint32_t lds[S::LDS_WORDS];
   int limb, poly;
   if (MODE == NTT_DIGIT || MODE == NTT_DIGIT2 || MODE == NTT_DIGIT3) {
-    // The digit transforms read one source limb per (ciphertext, digit) for
-    // all L + alpha target primes.  Split the (source x prime) grid into 8
-    // blocks, one per XCD: two halves of the primes x four quarters of the
-    // sources.  Each XCD then keeps about half the primes' twiddle tables
-    // in its L2, reads each of its sources once (the half's transforms of
-    // a source are numbered consecutively) and every source is read twice.
-    const int x = blockIdx.x & 7, l = blockIdx.x >> 3;
-    const int ph = (job.nlimb + 1) >> 1;                 // primes in half 0
-    const int g = x & 1;
-    const int np = g ? job.nlimb - ph : ph;
-    const int sq = (job.npoly + 3) >> 2;                  // sources per quarter
-    const int src = (x >> 1) * sq + l / np;
-    if (l / np >= sq || src >= job.npoly) return;
-    poly = src;
-    limb = g * ph + l % np;
+    if (!digit_item(job, 1, poly, limb)) return;
   } else {
     const int item = xcd_item(job.count);
     if (item >= job.count) return;
@@ -993,19 +1005,10 @@ k_ntt_fwd_par(NttJob job, Tables tb) {
   static_assert(MODE == NTT_DIGIT || MODE == NTT_DIGIT2 || MODE == NTT_DIGIT3, "digit modes");
   __shared__ uint32_t lds[S::LDS_WORDS];
   __shared__ double ltw[R1 * LDS_ROW];
-  // the digit transforms' XCD split (k_ntt_fwd), the two parities of a
-  // (source, prime) pair in consecutive workgroups of one XCD
-  const int xc = blockIdx.x & 7, l2 = blockIdx.x >> 3;
-  const int h = l2 & 1;
-  const int l = l2 >> 1;
-  const int ph = (job.nlimb + 1) >> 1;
-  const int g = xc & 1;
-  const int np = g ? job.nlimb - ph : ph;
-  const int sq = (job.npoly + 3) >> 2;
-  const int src = (xc >> 1) * sq + l / np;
-  if (l / np >= sq || src >= job.npoly) return;
-  const int poly = src;
-  const int limb = g * ph + l % np;
+  // the two parities of a (source, prime) pair in consecutive workgroups of
+  // one XCD
+  int poly, limb, h;
+  if (!digit_item(job, 2, poly, limb, &h)) return;
   const int prime = cldi(job.limb_prime, limb);
   const double p = cld(tb.p, prime), pinv = cld(tb.pinv, prime);
   const TwSrc tw{tb.tw_fwd + (size_t)prime * tb.tw_len,
@@ -1324,21 +1327,14 @@ k_ntt_inv_half(NttJob job, Tables tb) {
 
 // Workgroups per XCD for a launch (grid = 8 x this); `halves` = 2 when each
 // limb is split over two workgroups.
-static int per_xcd(const NttJob& job, int dir, int halves) {
-  if (dir == 2) {
-    const int ph = (job.nlimb + 1) >> 1;
-    const int sq = (job.npoly + 3) >> 2;
-    return sq * ph * halves;
-  }
-  return (job.count * halves + 7) >> 3;
-}
+static int per_xcd(const NttJob& job, int halves) { return (job.count * halves + 7) >> 3; }
 
 template <int LOGN>
 static hipError_t launch_ntt(const NttJob& job, const Tables& tb, int dir, hipStream_t st) {
   using S = NttShape<LOGN>;
   if constexpr (LOGN == 15) {
     if ((dir == 1 || dir == 3 || dir == 4) && job.split_inv && tb.tw_half_inv) {
-      dim3 grid(per_xcd(job, dir, 2) * 8), block(512);
+      dim3 grid(per_xcd(job, 2) * 8), block(512);
       if (dir == 1)
         hipLaunchKernelGGL((k_ntt_inv_half<NTT_INPLACE>), grid, block, 0, st, job, tb);
       else if (dir == 4)
@@ -1350,7 +1346,7 @@ static hipError_t launch_ntt(const NttJob& job, const Tables& tb, int dir, hipSt
       return hipGetLastError();
     }
     if (dir == 2 && job.parity && job.split && tb.tw_cmp_par) {
-      dim3 grid(per_xcd(job, dir, 2) * 8), block(512);
+      dim3 grid(per_xcd(job, 2) * 8), block(512);
       // (sources stored by parity: three-prime digits, see the scale-and-round)
       if (job.alpha == 2)
         hipLaunchKernelGGL((k_ntt_fwd_par<NTT_DIGIT2, false>), grid, block, 0, st, job, tb);
@@ -1363,7 +1359,7 @@ static hipError_t launch_ntt(const NttJob& job, const Tables& tb, int dir, hipSt
       return hipGetLastError();
     }
     if (dir == 0 && job.out && job.out != job.base && tb.tw_half && job.split) {
-      dim3 grid(per_xcd(job, dir, 2) * 8), block(512);
+      dim3 grid(per_xcd(job, 2) * 8), block(512);
       hipLaunchKernelGGL((k_ntt_fwd_half<NTT_INPLACE>), grid, block, 0, st, job, tb);
       return hipGetLastError();
     }
@@ -1373,7 +1369,7 @@ static hipError_t launch_ntt(const NttJob& job, const Tables& tb, int dir, hipSt
     if (!job.out || job.out == job.base) return hipErrorInvalidValue;
     dir = 1;
   }
-  const int per = per_xcd(job, dir, 1);
+  const int per = per_xcd(job, 1);
   dim3 grid(per * 8), block(S::T);
   if (dir == 0)
     hipLaunchKernelGGL((k_ntt_fwd<LOGN, NTT_INPLACE>), grid, block, 0, st, job, tb);
