@@ -454,26 +454,13 @@ static int tensor_scale(nshe_ctx* c, const Ws& w, const double* fx_b, int n_ct, 
 }
 
 static int digit_products(nshe_ctx* c, const Ws& w, int n_ct, hipStream_t st, const double* key);
-static int finish_relin(nshe_ctx* c, const Ws& w, int n_ct, hipStream_t st, double* out,
-                        bool lift_out, int64_t* finish_out, int64_t* i64_out, bool accumulate,
-                        const WaveTab* finish_tab);
 
 // Key-switch the third component in dt (limbs 0..L-1: canonical residues,
 // or with several primes per digit each digit's mixed-radix digits) with
-// `key` (the relinearization key unless given) and add the result to the
-// first two: (c0 + k0, c1 + k1) into `out` (ext unless given), limbs 0..L-1.
-// lift_out: also lift the result (limbs L..2L of out), for a squaring that
-// follows at once (only with the split inverse).
-// finish_out: write the result to this int64 buffer with the mask's finish
-// instead (only with the split inverse); i64_out: write it there as it is.
-// accumulate: add the result into out (limbs 0..L-1) instead of storing it.
-// finish_tab: as finish_out, into a batched wave's ciphertexts (its table).
-static int relin(nshe_ctx* c, const Ws& w, int n_ct, hipStream_t st,
-                 const double* key = nullptr, double* out = nullptr, bool lift_out = false,
-                 int64_t* finish_out = nullptr, int64_t* i64_out = nullptr,
-                 bool accumulate = false, const WaveTab* finish_tab = nullptr) {
-  if (!key) key = c->evk;
-  if (!out) out = w.ext;
+// `key` and add the result to the first two, (c0 + k0, c1 + k1), the mod-down
+// leaving it as `md` says (tab: a batched wave's table, for MD_I64).
+static int relin(nshe_ctx* c, const Ws& w, int n_ct, hipStream_t st, const double* key,
+                 const ModDownOut& md, const WaveTab* tab = nullptr) {
   if (ks_fused(c)) {
     NttJob j{};
     j.npoly = n_ct;
@@ -489,8 +476,13 @@ static int relin(nshe_ctx* c, const Ws& w, int n_ct, hipStream_t st,
     int rc0 = digit_products(c, w, n_ct, st, key);
     if (rc0) return rc0;
   }
-  return finish_relin(c, w, n_ct, st, out, lift_out, finish_out, i64_out, accumulate,
-                      finish_tab);
+  int rc = ntt_job_ks(c, w.acc, nullptr, n_ct * 2, 1, st, true);
+  if (rc) return rc;
+  Dims d = dims(c, n_ct);
+  if (tab) d.tab = *tab;
+  Prof pf(c, md.kind == MD_LIFT ? K_MODDOWN_LIFT : K_MODDOWN, st, 2.0 * n_ct * c->n);
+  HIPCHK(run_moddown(d, w.acc, w.dt, md, c->tb, st));
+  return NSHE_OK;
 }
 
 // The digits' transforms (written to w.dig) and their products with the
@@ -529,41 +521,12 @@ static int digit_products(nshe_ctx* c, const Ws& w, int n_ct, hipStream_t st, co
   return NSHE_OK;
 }
 
-// The key-switch sums in w.acc -> inverse transform -> mod-down (see relin).
-static int finish_relin(nshe_ctx* c, const Ws& w, int n_ct, hipStream_t st, double* out,
-                        bool lift_out, int64_t* finish_out, int64_t* i64_out, bool accumulate,
-                        const WaveTab* finish_tab) {
-  Dims d = dims(c, n_ct);
-  int rc = ntt_job_ks(c, w.acc, nullptr, n_ct * 2, 1, st, true);
-  if (rc) return rc;
-  if ((finish_out || finish_tab) && d.fused) {
-    if (finish_tab) d.tab = *finish_tab;
-    Prof pf(c, K_MODDOWN, st, 2.0 * n_ct * c->n);
-    HIPCHK(run_moddown_finish(d, w.acc, w.dt, finish_out, c->tb, st, 1));
-  } else if (i64_out && d.fused) {
-    Prof pf(c, K_MODDOWN, st, 2.0 * n_ct * c->n);
-    HIPCHK(run_moddown_finish(d, w.acc, w.dt, i64_out, c->tb, st, 0));
-  } else if (lift_out && d.fused) {
-    Prof pf(c, K_MODDOWN_LIFT, st, 2.0 * n_ct * c->n);
-    HIPCHK(run_moddown_lift(d, w.acc, w.dt, out, c->tb, st));
-  } else {
-    Prof pf(c, K_MODDOWN, st, 2.0 * n_ct * c->n);
-    HIPCHK(run_moddown(d, w.acc, w.dt, out, c->tb, st, accumulate ? 1 : 0));
-  }
-  return NSHE_OK;
-}
-
-// Relinearize and write the result to the int64 buffer out (canonical): the
-// mod-down writes it directly after the split inverse, else a conversion
-// pass follows.
+// Relinearize and write the result to the int64 buffer out (canonical).
 static int relin_i64(nshe_ctx* c, const Ws& w, int n_ct, hipStream_t st, int64_t* out) {
-  Dims d = dims(c, n_ct);
-  if (d.fused) return relin(c, w, n_ct, st, nullptr, nullptr, false, nullptr, out);
-  int rc = relin(c, w, n_ct, st);
-  if (rc) return rc;
-  const size_t W = W_of(c), N = c->n;
-  HIPCHK(run_polys_to_i64(d, w.ext, 2, 2 * W * N, W * N, out, 0, c->tb, st));
-  return NSHE_OK;
+  ModDownOut md;
+  md.kind = MD_I64;
+  md.out = out;
+  return relin(c, w, n_ct, st, c->evk, md);
 }
 
 // int64 ciphertexts -> lifted into ext ([n_ct][2][W][N]) -> transformed
@@ -578,19 +541,15 @@ static int prepare_i64(nshe_ctx* c, const int64_t* in, double* ext, double* fx, 
   return ntt_job_ext(c, ext, fx, n_ct * 2, 0, st);
 }
 
-// One squaring level on the ciphertexts in ext.  In a chain of squarings
-// (with the split inverse) each level but the last also lifts its result
-// for the next (lift_out), which then skips its own lift (lifted).
-static int square_level(nshe_ctx* c, const Ws& w, int n_ct, hipStream_t st,
-                        bool lifted = false, bool lift_out = false,
-                        int64_t* finish_out = nullptr, const WaveTab* finish_tab = nullptr) {
-  const bool chain = split_inverse(c);
-  int rc = prepare_operand(c, w.ext, w.fx, n_ct, st, lifted && chain);
+// One squaring level on the ciphertexts in ext (lifted: already lifted by
+// the kernel that wrote them), its result left as `md` says.
+static int square_level(nshe_ctx* c, const Ws& w, int n_ct, hipStream_t st, bool lifted,
+                        const ModDownOut& md, const WaveTab* tab = nullptr) {
+  int rc = prepare_operand(c, w.ext, w.fx, n_ct, st, lifted);
   if (rc) return rc;
   rc = tensor_scale(c, w, nullptr, n_ct, st);
   if (rc) return rc;
-  return relin(c, w, n_ct, st, nullptr, nullptr, lift_out && chain,
-               chain ? finish_out : nullptr, nullptr, false, chain ? finish_tab : nullptr);
+  return relin(c, w, n_ct, st, c->evk, md, tab);
 }
 
 static int check_ctx(const nshe_ctx* c) {
@@ -1516,7 +1475,7 @@ int nshe_multiply(nshe_ctx* c, const int64_t* a, const int64_t* b, int64_t* out3
   if (rc) return rc;
   rc = tensor_scale(c, w, fx_second(c, w, n_ct), n_ct, st, nullptr, true);
   if (rc) return rc;
-  HIPCHK(run_polys_to_i64(d, w.dt, 3, 3 * W * N, W * N, out3, 0, c->tb, st));
+  HIPCHK(run_polys_to_i64(d, w.dt, 3, 3 * W * N, W * N, out3, c->tb, st));
   return NSHE_OK;
 }
 
@@ -1535,22 +1494,22 @@ int nshe_relinearize(nshe_ctx* c, const int64_t* in3, int64_t* out, int n_ct, vo
   const DigitSrc ds = digit_src(c, w);
   if (ds.split) HIPCHK(run_digit_split(d, w.dt, ds.p, ds.stride, st));
   if (c->alpha > 1) HIPCHK(run_digit_mrc(d, ds.p, ds.stride, c->tb, st));
-  rc = relin(c, w, n_ct, st);
-  if (rc) return rc;
-  HIPCHK(run_polys_to_i64(d, w.ext, 2, 2 * W * N, W * N, out, 0, c->tb, st));
-  return NSHE_OK;
+  return relin_i64(c, w, n_ct, st, out);
 }
 
-// The EQ chain on ciphertexts already differenced into w.ext.
-// finish_out (with the split inverse): the last level writes the mask to it;
-// finish_tab: to a batched wave's ciphertexts, through its table.
-static int eq_levels(nshe_ctx* c, const Ws& w, int n_ct, hipStream_t st,
-                     bool first_lifted = false, int64_t* finish_out = nullptr,
-                     const WaveTab* finish_tab = nullptr) {
+// The EQ chain on ciphertexts already differenced and lifted into w.ext: each
+// level's mod-down lifts its result for the next, the last writes the mask to
+// finish_out, or to a batched wave's ciphertexts through its table (tab).
+static int eq_levels(nshe_ctx* c, const Ws& w, int n_ct, hipStream_t st, int64_t* finish_out,
+                     const WaveTab* tab = nullptr) {
   for (int k = 0; k < c->squarings; ++k) {
     const bool last = k + 1 == c->squarings;
-    int rc = square_level(c, w, n_ct, st, k > 0 || first_lifted, !last,
-                          last ? finish_out : nullptr, last ? finish_tab : nullptr);
+    ModDownOut md;
+    md.kind = last ? MD_I64 : MD_LIFT;
+    md.ext = w.ext;
+    md.out = finish_out;
+    md.finish = 1;
+    int rc = square_level(c, w, n_ct, st, true, md, last ? tab : nullptr);
     if (rc) return rc;
   }
   return NSHE_OK;
@@ -1628,30 +1587,17 @@ static int eq_mask_impl(nshe_ctx* c, const int64_t* x, const int64_t* y, int64_t
   return eq_run(c, x, y, out, n_ct, y_broadcast, ws, st);
 }
 
-// The EQ chain itself on n_ct ciphertexts (checked by the caller), on st.
+// The EQ chain itself on n_ct ciphertexts (checked by the caller), on st: the
+// subtraction also lifts (the first squaring's operand), like every level's
+// mod-down but the last.
 static int eq_run(nshe_ctx* c, const int64_t* x, const int64_t* y, int64_t* out, int n_ct,
                   int y_broadcast, void* ws, hipStream_t st) {
-  int rc = NSHE_OK;
   Ws w = carve(c, ws, n_ct);
-  Dims d = dims(c, n_ct);
-  const size_t W = W_of(c), N = c->n;
-  // with the split inverse the subtraction also lifts (the first squaring's
-  // operand), like every later level's mod-down
-  const bool chain = split_inverse(c);
   {
     Prof pf(c, K_SUB, st, 2.0 * n_ct * c->L * c->n);
-    if (chain)
-      HIPCHK(run_sub_lift(d, x, y, y_broadcast ? 1 : 0, w.ext, c->tb, st));
-    else
-      HIPCHK(run_sub_to_ext(d, x, y, y_broadcast ? 1 : 0, w.ext, c->tb, st));
+    HIPCHK(run_sub_lift(dims(c, n_ct), x, y, y_broadcast ? 1 : 0, w.ext, c->tb, st));
   }
-  rc = eq_levels(c, w, n_ct, st, chain, chain ? out : nullptr);
-  if (rc) return rc;
-  if (!chain) {
-    Prof pf(c, K_CONVERT, st, 2.0 * n_ct * c->L * c->n);
-    HIPCHK(run_polys_to_i64(d, w.ext, 2, 2 * W * N, W * N, out, 1, c->tb, st));
-  }
-  return NSHE_OK;
+  return eq_levels(c, w, n_ct, st, out);
 }
 
 int nshe_eq_mask(nshe_ctx* c, const int64_t* x, const int64_t* y, int64_t* out, int n_ct,
@@ -1706,33 +1652,18 @@ static BatchArea batch_area(const nshe_ctx* c, void* ws, int wave_ct, long long 
 // One wave of cnt ciphertexts: x - y, the 16 levels and the mask's finish,
 // the wave's ciphertexts read and written through its table; then advance
 // the wave counter by `step` (the number of streams taking turns over the
-// table's waves).  With the split inverse the ends are the plain chain's
-// fused kernels (subtraction + first lift, last mod-down + finish), else a
-// gather, the levels and a scatter.
+// table's waves).
 static int enqueue_wave(nshe_ctx* c, int cnt, int stride, int step, const BatchArea& a,
                         const Ws& w, hipStream_t st) {
   Dims d = dims(c, cnt);
   const WaveTab wt{a.table, a.counter, stride};
-  if (split_inverse(c)) {
-    d.tab = wt;
-    {
-      Prof pf(c, K_SUB, st, 2.0 * cnt * c->L * c->n);
-      HIPCHK(run_sub_lift(d, nullptr, nullptr, 0, w.ext, c->tb, st));
-    }
-    int rc = eq_levels(c, w, cnt, st, true, nullptr, &wt);
-    if (rc) return rc;
-  } else {
-    {
-      Prof pf(c, K_SUB, st, 2.0 * cnt * c->L * c->n);
-      HIPCHK(run_gather_sub(d, stride, a.table, a.counter, w.ext, c->tb, st));
-    }
-    int rc = eq_levels(c, w, cnt, st);
-    if (rc) return rc;
-    {
-      Prof pf(c, K_CONVERT, st, 2.0 * cnt * c->L * c->n);
-      HIPCHK(run_scatter_mask(d, stride, a.table, a.counter, w.ext, c->tb, st));
-    }
+  d.tab = wt;
+  {
+    Prof pf(c, K_SUB, st, 2.0 * cnt * c->L * c->n);
+    HIPCHK(run_sub_lift(d, nullptr, nullptr, 0, w.ext, c->tb, st));
   }
+  int rc = eq_levels(c, w, cnt, st, nullptr, &wt);
+  if (rc) return rc;
   HIPCHK(run_bump_counter(a.counter, step, st));
   return NSHE_OK;
 }
@@ -1936,10 +1867,10 @@ static unsigned inv_mod_2n(const nshe_ctx* c, uint32_t g) {
   return 1;
 }
 
-// One rotation of the ciphertexts in w.ext by Galois element g into `out`
-// ([ct][2][W][N] limbs 0..L-1).
+// One rotation of the ciphertexts in w.ext by Galois element g, its result left
+// as `md` says.
 static int rotate_ext(nshe_ctx* c, const Ws& w, int n_ct, uint32_t g, const double* key,
-                      double* out, hipStream_t st, bool accumulate = false) {
+                      ModDownOut md, hipStream_t st) {
   Dims d = dims(c, n_ct);
   {
     Prof pf(c, K_AUTOMORPH, st, 2.0 * n_ct * c->L * c->n);
@@ -1948,16 +1879,21 @@ static int rotate_ext(nshe_ctx* c, const Ws& w, int n_ct, uint32_t g, const doub
                          ds.stride, ds.split));
     if (c->alpha > 1) HIPCHK(run_digit_mrc(d, ds.p, ds.stride, c->tb, st));
   }
-  return relin(c, w, n_ct, st, key, out, false, nullptr, nullptr, accumulate);
+  return relin(c, w, n_ct, st, key, md);
 }
 
-// ct <- ct + rot_g(ct) over the sum elements, on the ciphertexts in w.ext
+// ct <- ct + rot_g(ct) over the sum elements, on the ciphertexts in w.ext;
+// the last sum to the int64 buffer out
 static int sum_slots_ext(nshe_ctx* c, const Ws& w, int n_ct, const std::vector<uint32_t>& els,
-                         const std::vector<const double*>& keys, hipStream_t st) {
+                         const std::vector<const double*>& keys, int64_t* out, hipStream_t st) {
   // the rotation's mod-down adds its result into the running sum in ext
   // (the automorphism has read ext before)
   for (size_t k = 0; k < els.size(); ++k) {
-    int rc = rotate_ext(c, w, n_ct, els[k], keys[k], w.ext, st, true);
+    ModDownOut md;
+    md.kind = k + 1 == els.size() ? MD_SUM_I64 : MD_SUM;
+    md.ext = w.ext;
+    md.out = out;
+    int rc = rotate_ext(c, w, n_ct, els[k], keys[k], md, st);
     if (rc) return rc;
   }
   return NSHE_OK;
@@ -1998,10 +1934,10 @@ int nshe_rotate(nshe_ctx* c, const int64_t* in, uint32_t g, int64_t* out, int n_
   Dims d = dims(c, n_ct);
   const size_t W = W_of(c), N = c->n;
   HIPCHK(run_i64_to_polys(d, in, 2, w.ext, 2 * W * N, W * N, 2, c->tb, st));
-  rc = rotate_ext(c, w, n_ct, g, key->second, w.fx, st);
-  if (rc) return rc;
-  HIPCHK(run_polys_to_i64(d, w.fx, 2, 2 * W * N, W * N, out, 0, c->tb, st));
-  return NSHE_OK;
+  ModDownOut md;
+  md.kind = MD_I64;
+  md.out = out;
+  return rotate_ext(c, w, n_ct, g, key->second, md, st);
 }
 
 int nshe_sum_slots(nshe_ctx* c, const int64_t* in, int64_t* out, int n_ct, void* ws,
@@ -2023,10 +1959,7 @@ int nshe_sum_slots(nshe_ctx* c, const int64_t* in, int64_t* out, int n_ct, void*
     Dims d = dims(c, cnt);
     const size_t W = W_of(c), N = c->n;
     HIPCHK(run_i64_to_polys(d, in + c0 * ctw, 2, w.ext, 2 * W * N, W * N, 2, c->tb, s));
-    int rc1 = sum_slots_ext(c, w, cnt, els, keys, s);
-    if (rc1) return rc1;
-    HIPCHK(run_polys_to_i64(d, w.ext, 2, 2 * W * N, W * N, out + c0 * ctw, 0, c->tb, s));
-    return NSHE_OK;
+    return sum_slots_ext(c, w, cnt, els, keys, out + c0 * ctw, s);
   };
   // (with the tuning's two streams: the two halves of the ciphertexts on two
   // streams, as the EQ call)
@@ -2104,27 +2037,32 @@ int nshe_mul_plain(nshe_ctx* c, const int64_t* in, const int64_t* pt, int64_t* o
   HIPCHK(run_i64_to_polys(d, in, 2, w.ext, 2 * W * N, W * N, 2, c->tb, st));
   rc = mul_plain_ext(c, w, pt, n_ct, st);
   if (rc) return rc;
-  HIPCHK(run_polys_to_i64(d, w.fx, 2, 2 * W * N, W * N, out, 0, c->tb, st));
+  HIPCHK(run_polys_to_i64(d, w.fx, 2, 2 * W * N, W * N, out, c->tb, st));
   return NSHE_OK;
 }
 
-// Extract (broadcast = 0) or Broadcast (1) of one slot, ciphertexts in w.ext
-// -> w.ext.
-static int extract_ext(nshe_ctx* c, const Ws& w, int slot, int n_ct, int bcast, hipStream_t st) {
+// Extract (broadcast = 0) or Broadcast (1) of one slot of the ciphertexts in
+// w.ext into the int64 buffer out.
+static int extract_ext(nshe_ctx* c, Ws w, int slot, int n_ct, int bcast, int64_t* out,
+                       hipStream_t st) {
   int64_t* pt = reinterpret_cast<int64_t*>(w.acc);
   int rc = basis_plain(c, slot, pt, st);
   if (rc) return rc;
   rc = mul_plain_ext(c, w, pt, n_ct, st);
   if (rc) return rc;
   const size_t W = W_of(c), N = c->n;
-  HIPCHK(hipMemcpyAsync(w.ext, w.fx, (size_t)n_ct * 2 * W * N * sizeof(double),
-                        hipMemcpyDeviceToDevice, st));
-  if (!bcast) return NSHE_OK;
+  if (!bcast) {
+    HIPCHK(run_polys_to_i64(dims(c, n_ct), w.fx, 2, 2 * W * N, W * N, out, c->tb, st));
+    return NSHE_OK;
+  }
   std::vector<uint32_t> els;
   std::vector<const double*> keys;
   rc = sum_keys(c, &els, &keys);
   if (rc) return rc;
-  return sum_slots_ext(c, w, n_ct, els, keys, st);
+  // the running sum is the product, where it is (the rotations use neither
+  // operand's area otherwise)
+  std::swap(w.ext, w.fx);
+  return sum_slots_ext(c, w, n_ct, els, keys, out, st);
 }
 
 int nshe_extract(nshe_ctx* c, const int64_t* in, int slot, int broadcast, int64_t* out,
@@ -2149,10 +2087,7 @@ int nshe_extract(nshe_ctx* c, const int64_t* in, int slot, int broadcast, int64_
   Dims d = dims(c, n_ct);
   const size_t W = W_of(c), N = c->n;
   HIPCHK(run_i64_to_polys(d, in, 2, w.ext, 2 * W * N, W * N, 2, c->tb, st));
-  rc = extract_ext(c, w, slot, n_ct, broadcast ? 1 : 0, st);
-  if (rc) return rc;
-  HIPCHK(run_polys_to_i64(d, w.ext, 2, 2 * W * N, W * N, out, 0, c->tb, st));
-  return NSHE_OK;
+  return extract_ext(c, w, slot, n_ct, broadcast ? 1 : 0, out, st);
 }
 
 // ------------------------------------------------------------------ JOIN
@@ -2582,11 +2517,13 @@ static int time_kinds(nshe_ctx* c, const nshe_tuning& t, const Ws& w, int n_ct, 
                       hipStream_t st, double ms[K_COUNT]) {
   c->tune = t;
   c->prof = false;
-  int rc = square_level(c, w, n_ct, st);
+  ModDownOut md;
+  md.ext = w.ext;
+  int rc = square_level(c, w, n_ct, st, false, md);
   if (rc) return rc;
   c->prof = true;
   for (int i = 0; i < reps; ++i) {
-    rc = square_level(c, w, n_ct, st);
+    rc = square_level(c, w, n_ct, st, false, md);
     if (rc) return rc;
   }
   c->prof = false;
@@ -2595,12 +2532,14 @@ static int time_kinds(nshe_ctx* c, const nshe_tuning& t, const Ws& w, int n_ct, 
 
 // Wall time of one squaring level on n_ct ciphertexts (after one untimed).
 static int time_level(nshe_ctx* c, const Ws& w, int n_ct, hipStream_t st, double* ms) {
-  int rc = square_level(c, w, n_ct, st);
+  ModDownOut md;
+  md.ext = w.ext;
+  int rc = square_level(c, w, n_ct, st, false, md);
   if (rc) return rc;
   hipEvent_t a = take_event(c), b = take_event(c);
   if (!a || !b) return fail(NSHE_EDEVICE, "event creation failed");
   HIPCHK(hipEventRecord(a, st));
-  rc = square_level(c, w, n_ct, st);
+  rc = square_level(c, w, n_ct, st, false, md);
   if (rc) return rc;
   HIPCHK(hipEventRecord(b, st));
   HIPCHK(hipEventSynchronize(b));

@@ -120,10 +120,10 @@ struct Tables {
 
 // Call sites of the exact-lift fallback (index into Tables::margin).
 enum MarginSite {
-  MARGIN_LIFT = 0,          // k_lift: a squaring's operand lift, not fused (no split transforms)
+  MARGIN_LIFT = 0,          // a squaring's operand lift on the levels without the split transforms
   MARGIN_SCALE = 1,         // k_scale: the scale-and-round's lift of [t d]_Q
   MARGIN_SCALE_SPLIT = 2,   // k_scale after the split inverse (N = 2^15)
-  MARGIN_MODDOWN_LIFT = 3,  // k_moddown_lift: the next squaring's operand
+  MARGIN_MODDOWN_LIFT = 3,  // k_moddown with the lift: the next squaring's operand
   MARGIN_SUB_LIFT = 4,      // k_sub_lift: the chain's first operand
   MARGIN_I64_LIFT = 5,      // k_i64_lift: a product's int64 operands
   MARGIN_SITES = 6,
@@ -208,7 +208,7 @@ struct Dims {
   // the digit transforms are by coefficient parity (N = 2^15): the key-switch
   // product applies their last stage (k_ks_mac_par)
   int parity = 0;
-  // a batched wave's table: run_sub_lift reads x and y, run_moddown_finish
+  // a batched wave's table: run_sub_lift reads x and y, run_moddown (MD_I64)
   // writes out, through it (their pointer arguments are then unused)
   WaveTab tab;
 };
@@ -224,27 +224,23 @@ hipError_t run_scale(const Dims& d, double* dt, const Tables& tb, hipStream_t st
                      int digit_pairs = 0, double* src = nullptr);
 hipError_t run_ks_mac(const Dims& d, const double* dig, const double* evk, double* acc,
                       const Tables& tb, hipStream_t st);
-hipError_t run_moddown(const Dims& d, const double* acc, const double* dt, double* ext,
-                       const Tables& tb, hipStream_t st,
-                       int accumulate = 0);
-// the last level's mod-down written to int64 with the mask's finish,
-// (Delta, 0) - z; needs d.fused
-hipError_t run_moddown_finish(const Dims& d, const double* acc, const double* dt, int64_t* out,
-                              const Tables& tb, hipStream_t st,
-                              int finish = 1);
+// What a mod-down's result becomes (see k_moddown).
+enum ModDownKind { MD_EXT = 0, MD_SUM = 1, MD_LIFT = 2, MD_I64 = 3, MD_SUM_I64 = 4 };
+struct ModDownOut {
+  ModDownKind kind = MD_EXT;
+  double* ext = nullptr;    // MD_EXT, MD_SUM, MD_LIFT, MD_SUM_I64
+  int64_t* out = nullptr;   // MD_I64, MD_SUM_I64 (unless the wave's table names it)
+  int finish = 0;           // MD_I64: the mask's (Delta, 0) - z
+  int one_e = 0;            // component 1 of dt is zero and not read
+};
+hipError_t run_moddown(const Dims& d, const double* acc, const double* dt, const ModDownOut& o,
+                       const Tables& tb, hipStream_t st);
 // int64 ciphertexts into ext followed by their lift (a product's operands)
 hipError_t run_i64_lift(const Dims& d, const int64_t* in, double* ext, const Tables& tb,
                         hipStream_t st);
 // subtraction into ext followed by its lift (the first squaring's operand)
 hipError_t run_sub_lift(const Dims& d, const int64_t* x, const int64_t* y, int y_bcast,
                         double* ext, const Tables& tb, hipStream_t st);
-// mod-down of the split inverse's output followed by the lift of the result
-// (the next squaring's operand), one kernel; needs d.fused
-hipError_t run_moddown_lift(const Dims& d, const double* acc, const double* dt, double* ext,
-                            const Tables& tb, hipStream_t st);
-// conversions at the boundary
-hipError_t run_sub_to_ext(const Dims& d, const int64_t* x, const int64_t* y, int y_bcast,
-                          double* ext, const Tables& tb, hipStream_t st);
 // plaintext products: a slot's basis plaintext, a plaintext's limbs (times
 // N^-1), and the pointwise product with the data limbs of transforms
 hipError_t run_basis_plain(int n, uint64_t t, uint64_t zinv, uint64_t ninv_t, int64_t* out,
@@ -290,16 +286,12 @@ hipError_t run_check_residues(int n, int L, size_t n_poly, const int64_t* in, co
 // out = a + sum_{j < k} b[j * stride] (canonical int64 ciphertexts)
 hipError_t run_sum_i64(const Dims& d, const int64_t* a, const int64_t* b, size_t stride, int k,
                        int64_t* out, const Tables& tb, hipStream_t st);
-// batched waves (see k_gather_sub): per-ciphertext pointers of a wave
+// batched waves: per-ciphertext pointers of a wave
 struct CtPtrs {
   const int64_t* x;
   const int64_t* y;
   int64_t* out;
 };
-hipError_t run_gather_sub(const Dims& d, int stride, const CtPtrs* table, const int* wave,
-                          double* ext, const Tables& tb, hipStream_t st);
-hipError_t run_scatter_mask(const Dims& d, int stride, const CtPtrs* table, const int* wave,
-                            const double* ext, const Tables& tb, hipStream_t st);
 // table entries [first, first + n) passed by value (kernel arguments are
 // copied at launch, so the host array may be reused at once)
 struct TableChunk {
@@ -319,8 +311,8 @@ hipError_t run_i64_to_polys(const Dims& d, const int64_t* in, int npoly_in, doub
                             size_t out_ct_stride, size_t out_poly_stride, int canon_from,
                             const Tables& tb, hipStream_t st);
 hipError_t run_polys_to_i64(const Dims& d, const double* in, int npoly, size_t in_ct_stride,
-                            size_t in_poly_stride, int64_t* out, int negate_delta,
-                            const Tables& tb, hipStream_t st);
+                            size_t in_poly_stride, int64_t* out, const Tables& tb,
+                            hipStream_t st);
 hipError_t run_i64_to_dbl_limbs(size_t rows, int n, const int64_t* in, double* out,
                                 const int* row_prime, int nprime_rows, const Tables& tb,
                                 hipStream_t st);

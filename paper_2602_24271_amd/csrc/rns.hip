@@ -29,6 +29,7 @@
 // matrix products mod b_k; they run on the integer matrix cores over signed
 // bytes (conv_pack, conv_tile) with one modular reduction per output.
 #include <algorithm>
+#include <type_traits>
 
 #include "conv.h"
 #include "kernels.h"
@@ -117,6 +118,37 @@ __device__ __forceinline__ const double* step_consts(const double* tab, int s) {
   return opaque_row(tab, 16 * s);
 }
 
+// Touches every cache line of a table of n doubles, together: a kernel's
+// scalar caches start cold, and the steps' loads would otherwise miss one after
+// the other (about half a microsecond each).
+template <int N>
+__device__ __forceinline__ void touch_lines(const double* tab) {
+  constexpr int LINES = (N + 7) / 8;
+  int v[(LINES + 7) / 8 * 8];
+#pragma unroll
+  for (int i = 0; i < (LINES + 7) / 8 * 8; ++i)
+    v[i] = cldi(reinterpret_cast<const int*>(tab), i < LINES ? 16 * i : 0);
+#pragma unroll
+  for (int i = 0; i < LINES; i += 8)
+    asm volatile("" ::"s"(v[i]), "s"(v[i + 1]), "s"(v[i + 2]), "s"(v[i + 3]), "s"(v[i + 4]),
+                 "s"(v[i + 5]), "s"(v[i + 6]), "s"(v[i + 7]));
+}
+
+// A lift kernel's LDS copy of the conversion constants, made behind the first
+// block's loads (mod-down + lift of eight ciphertexts 52 us, 56 before them;
+// the scale-and-round, with twice the limbs and constants, fills its tables
+// first: behind the loads its barrier holds every wave until all of the
+// workgroup's limbs are in, 83 us against 66).
+template <int L>
+__device__ __forceinline__ void lift_setup(v4i* tab, const Tables& tb, bool& first) {
+  if (!first) return;
+  conv_table<conv_entries(L, L + 1)>(tab, tb.mx_lift);
+  touch_lines<conv_steps(L) * 16>(tb.kq);
+  touch_lines<conv_steps(L + 1) * 16>(tb.kb);
+  __syncthreads();
+  first = false;
+}
+
 // Inputs 4s..4s+3 of a conversion (zero past L).
 template <int L>
 __device__ __forceinline__ void pack_step(const double (&y)[L], int s, v4i& g0, v4i& g1) {
@@ -174,8 +206,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4)))
 k_lift(int n, size_t n_poly, double* ext, Tables tb) {
   constexpr int LB = L + 1;
   __shared__ v4i tab[conv_entries(L, LB)];
-  conv_table<conv_entries(L, LB)>(tab, tb.mx_lift);
-  __syncthreads();
+  bool first = true;
   const unsigned nb = poly_blocks(n, n_poly);
   for (unsigned bk = blockIdx.x; bk < nb; bk += gridDim.x) {
     const PolyBlock pb = poly_block(n, bk);
@@ -187,6 +218,7 @@ k_lift(int n, size_t n_poly, double* ext, Tables tb) {
 #pragma unroll
     for (int i = 0; i < L; ++i) o[i] = buf_load(rs, vo, i * ls);
     loads_issued();
+    lift_setup<L>(tab, tb, first);
     v4i g0[conv_steps(L)], g1[conv_steps(L)];
 #pragma unroll
     for (int s = 0; s < conv_steps(L); ++s) {
@@ -314,6 +346,8 @@ k_scale(int n, size_t n_poly, double* dt, Tables tb) {
     const int i = t >> 1, r = t & 1;
     kl[t] = i < L ? tb.t_qhinv[r * L + i] : tb.c1[r * LB + i - L];
   }
+  touch_lines<conv_steps(L) * 16>(tb.kq);
+  touch_lines<conv_steps(LB) * 16>(tb.kb);
   __syncthreads();
   const int lane = (int)threadIdx.x & 63;
   const bool hi = FUSED && lane >= 32;
@@ -604,18 +638,6 @@ __global__ void __launch_bounds__(256) k_ks_mac_par(int n_ct, const double* dig,
   }
 }
 
-// A special limb's residues [N^-1 x]_{P_k} (balanced) at coefficients c and
-// c + N/2 from the split inverse's half outputs U (at a) and V (at a + ht):
-// the inverse's last stage (U + V, (U - V) w) applied here.
-__device__ __forceinline__ void special_pair(const double* a, int ht, int ip, double& lo,
-                                             double& hi, const Tables& tb) {
-  const double pk = cld(tb.p, ip), pkinv = cld(tb.pinv, ip);
-  const double u = a[0], v = a[ht];
-  const double ninvk = cld(tb.ninv, ip);
-  lo = mul_bal(u + v, ninvk, pk, pkinv);
-  hi = mul_bal(mul_lazy(u - v, cld(tb.tw_inv, ip * tb.tw_len + 1), pk, pkinv), ninvk, pk, pkinv);
-}
-
 // The centred residue r = [x]_P of a key-switch sum, P = P_0 ... P_{A-1},
 // in mixed radix r = k_0 + P_0 k_1 + P_0 P_1 k_2 from its balanced residues
 // a_m mod P_m (Garner, every digit balanced): k_0 = a_0,
@@ -639,200 +661,102 @@ __device__ __forceinline__ void special_digits(const double (&a)[A], double (&k)
   }
 }
 
-// (x - r) P^-1 mod q_i up to the factor N^-1 folded into npq: x times
-// [N^-1 P^-1]_{q_i} minus r's mixed-radix digits k_m times
-// [(P_0 ... P_{m-1}) P^-1]_{q_i}.  Each lazy product is below 0.9 q_i
-// (operands below 2 q_i), so the result is below 3.6 q_i.
-template <int L, int A>
-__device__ __forceinline__ double moddown_term(double x, double npq, const double (&k)[A], int i,
-                                               double q, double qinv, const Tables& tb) {
-  double r = mul_lazy(x, npq, q, qinv) - mul_lazy(k[0], cld(tb.P_inv_q, i), q, qinv);
-#pragma unroll
-  for (int m = 1; m < A; ++m) r -= mul_lazy(k[m], cld(tb.mr_q, (m - 1) * L + i), q, qinv);
-  return r;
-}
-
-// new ct (into ext limbs 0..L-1) = e_b + (acc_b - [acc_b]_P) * P^-1, where
-// [acc_b]_P is the centred residue mod P of the special limbs (special_k).
-// Since mul_lazy(a0, .) needs |a0| < 2p only, P_k may exceed q_i (all
-// < 2^49).
+// The mod-down: e_b + (acc_b - [acc_b]_P) P^-1 mod q_i for both components b
+// of each ciphertext (poly = ct * 2 + b), [acc_b]_P the centred residue mod P
+// of the special limbs in mixed-radix digits k_m: per limb, acc_b times
+// [N^-1 P^-1]_{q_i} (an inverse transform returns N times the sum) minus
+// k_m times [(P_0 ... P_{m-1}) P^-1]_{q_i}.  Each lazy product is below
+// 0.9 q_i (operands below 2 q_i: P_k may exceed q_i, all lie below 2^49), so a
+// sum stays below 4.2 q_i.  What becomes of the result z (OUT):
+//   MD_EXT   stored in ext (limbs 0..L-1);
+//   MD_SUM   added to what ext holds there;
+//   MD_LIFT  stored in ext and lifted (limbs L..2L) for the squaring that
+//            follows: the next level of a chain lifts exactly this;
+//   MD_I64   canonical residues in the int64 output, with finish the mask's
+//            (Delta, 0) - z; wt (table not null): a batched wave's ciphertexts,
+//            written through the table's out pointers;
+//   MD_SUM_I64  ext's residues plus z in the int64 output.
+// one_e: component 1's e is zero (a rotation's), not read.
 // FUSED: acc holds the split inverse's in-place half outputs of a 2^15-point
 // limb (U of pair c at (c / 512) 1024 + c mod 512, V 512 further; see
-// k_ntt_inv_half) and a thread produces both coefficients c and c + N/2.
-template <int L, int A, bool FUSED>
-__global__ void __launch_bounds__(256) k_moddown(int n, int n_ct, const double* __restrict__ acc,
-                                                 const double* __restrict__ dt,
-                                                 double* __restrict__ ext, int accumulate,
-                                                 Tables tb) {
+// k_ntt_inv_half): lanes l and l + 32 of a wave hold the two coefficients of a
+// pair (c, c + N/2) and trade half outputs as the scale-and-round does, the
+// last inverse stage's twiddle folded into the second rows of NP_inv_q and
+// ninv_P.
+// Bound by memory traffic: MD_LIFT moves 33 limbs in and 31 out per polynomial
+// (15 + 3 primes), 1.07 GB at 32 ciphertexts in 204 us (5.3 TB/s; 206 with the
+// lift as split FMAs on the VALU).  At one ciphertext it is latency: every
+// limb is loaded up front and the constants' cache lines are touched together
+// (MD_LIFT 21 -> 13 us, MD_I64 12.5 -> 10).
+template <int L, int A, bool FUSED, int OUT>
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(L > 20 ? 2 : 4)))
+k_moddown(int n, size_t n_poly, const double* __restrict__ acc, const double* __restrict__ dt,
+          double* __restrict__ ext, int64_t* __restrict__ out, int finish, int one_e, Tables tb,
+          WaveTab wt) {
   constexpr int K = L + A;
   constexpr int W = 2 * L + 1;
-  const int per = FUSED ? n >> 1 : n;      // threads per (ct, component)
-  const size_t gid = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (gid >= (size_t)n_ct * 2 * per) return;
-  const size_t cb = gid / per;             // ct * 2 + b
-  const int c = (int)(gid - cb * per);
-  const size_t ct = cb >> 1;
-  const int b = (int)(cb & 1);
-  const int ip = 2 * L + 1;
-  const double* e = dt + ((ct * 3 + b) * (size_t)W) * n + c;
-  double* o = ext + cb * (size_t)W * n + c;
-  if constexpr (!FUSED) {
-    const double* a = acc + cb * (size_t)K * n + c;
-    // acc is inverse-transform output (N times the sum): the residues mod
-    // the special primes are [N^-1 acc_Pk]_Pk
-    double as[A], kP[A];
-#pragma unroll
-    for (int m = 0; m < A; ++m)
-      as[m] = mul_bal(a[(size_t)(L + m) * n], cld(tb.ninv, ip + m), cld(tb.p, ip + m),
-                      cld(tb.pinv, ip + m));
-    special_digits<A>(as, kP, tb, L);
-#pragma unroll
-    for (int i = 0; i < L; ++i) {
-      const double q = cld(tb.p, i), qinv = cld(tb.pinv, i);
-      const double r = moddown_term<L, A>(a[(size_t)i * n], cld(tb.NP_inv_q, i), kP, i, q, qinv, tb);
-      const double z = reduce_bal(e[(size_t)i * n] + r, q, qinv);
-      o[(size_t)i * n] = accumulate ? reduce_bal(o[(size_t)i * n] + z, q, qinv) : z;
-    }
-  } else {
-    const int ht = n >> 6;                 // 512: a half transform's threads
-    const double* a = acc + cb * (size_t)K * n + (size_t)(c / ht) * 2 * ht + (c % ht);
-    const size_t hn = (size_t)(n >> 1);
-    double s_lo[A], s_hi[A], k_lo[A], k_hi[A];
-#pragma unroll
-    for (int m = 0; m < A; ++m)
-      special_pair(a + (size_t)(L + m) * n, ht, ip + m, s_lo[m], s_hi[m], tb);
-    special_digits<A>(s_lo, k_lo, tb, L);
-    special_digits<A>(s_hi, k_hi, tb, L);
-#pragma unroll
-    for (int i = 0; i < L; ++i) {
-      const double q = cld(tb.p, i), qinv = cld(tb.pinv, i);
-      const double u = a[(size_t)i * n], v = a[(size_t)i * n + ht];
-      const double lo = u + v;
-      const double hi = mul_lazy(u - v, cld(tb.tw_inv, i * tb.tw_len + 1), q, qinv);
-      const double npq = cld(tb.NP_inv_q, i);
-      const double r_lo = moddown_term<L, A>(lo, npq, k_lo, i, q, qinv, tb);
-      const double r_hi = moddown_term<L, A>(hi, npq, k_hi, i, q, qinv, tb);
-      const double z_lo = reduce_bal(e[(size_t)i * n] + r_lo, q, qinv);
-      const double z_hi = reduce_bal(e[(size_t)i * n + hn] + r_hi, q, qinv);
-      o[(size_t)i * n] = accumulate ? reduce_bal(o[(size_t)i * n] + z_lo, q, qinv) : z_lo;
-      o[(size_t)i * n + hn] = accumulate ? reduce_bal(o[(size_t)i * n + hn] + z_hi, q, qinv) : z_hi;
-    }
-  }
-}
-
-// A mod-down (split inverse, pairs as in k_moddown FUSED) written straight
-// to the caller's int64 output, canonical residues in [0, q_i): with finish,
-// the mask's finish out = (Delta, 0) - z (every residue negated and
-// [Delta]_{q_i} added to the constant coefficient of c0); without, z.
-// wt (table not null): a batched wave's ciphertexts, written through the
-// table's out pointers.
-template <int L, int A>
-__global__ void __launch_bounds__(256) k_moddown_finish(int n, int n_ct,
-                                                        const double* __restrict__ acc,
-                                                        const double* __restrict__ dt,
-                                                        int64_t* __restrict__ out, int finish,
-                                                        Tables tb, WaveTab wt) {
-  constexpr int K = L + A;
-  constexpr int W = 2 * L + 1;
-  const int per = n >> 1;
-  const size_t gid = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (gid >= (size_t)n_ct * 2 * per) return;
-  const size_t cb = gid / per;             // ct * 2 + b
-  const int c = (int)(gid - cb * per);
-  const size_t ct = cb >> 1;
-  const int b = (int)(cb & 1);
-  const int ip = 2 * L + 1;
-  const double* e = dt + ((ct * 3 + b) * (size_t)W) * n + c;
-  int64_t* o = wt.table ? wt.table[(size_t)(*wt.wave) * wt.stride + ct].out + (size_t)b * L * n + c
-                        : out + cb * (size_t)L * n + c;
-  const int ht = n >> 6;
-  const double* a = acc + cb * (size_t)K * n + (size_t)(c / ht) * 2 * ht + (c % ht);
-  const size_t hn = (size_t)(n >> 1);
-  double s_lo[A], s_hi[A], k_lo[A], k_hi[A];
-#pragma unroll
-  for (int m = 0; m < A; ++m)
-    special_pair(a + (size_t)(L + m) * n, ht, ip + m, s_lo[m], s_hi[m], tb);
-  special_digits<A>(s_lo, k_lo, tb, L);
-  special_digits<A>(s_hi, k_hi, tb, L);
-#pragma unroll
-  for (int i = 0; i < L; ++i) {
-    const double q = cld(tb.p, i), qinv = cld(tb.pinv, i);
-    const double u = a[(size_t)i * n], v = a[(size_t)i * n + ht];
-    const double lo = u + v;
-    const double hi = mul_lazy(u - v, cld(tb.tw_inv, i * tb.tw_len + 1), q, qinv);
-    const double npq = cld(tb.NP_inv_q, i);
-    const double r_lo = moddown_term<L, A>(lo, npq, k_lo, i, q, qinv, tb);
-    const double r_hi = moddown_term<L, A>(hi, npq, k_hi, i, q, qinv, tb);
-    // finish: -(e + r), plus Delta at coefficient 0 of c0 (sg = -1 exactly
-    // negates); else e + r
-    const double sg = finish ? -1.0 : 1.0;
-    double z_lo = sg * (e[(size_t)i * n] + r_lo);
-    if (finish && b == 0 && c == 0) z_lo += cld(tb.delta_q, i);
-    const double z_hi = sg * (e[(size_t)i * n + hn] + r_hi);
-    o[(size_t)i * n] = to_i64(reduce_bal(z_lo, q, qinv), q);
-    o[(size_t)i * n + hn] = to_i64(reduce_bal(z_hi, q, qinv), q);
-  }
-}
-
-// The mod-down of the split inverse's output (k_moddown, FUSED) followed by
-// the lift of its result (k_lift): within the squaring chain the next level
-// lifts exactly what this level's mod-down writes, so one kernel saves
-// re-reading it.  One thread per coefficient of each (ct, b) polynomial
-// (blocks mapped like k_lift); lanes l and l + 32 of a wave hold the two
-// coefficients of a pair (c, c + N/2) and exchange the key-switch sum's half
-// outputs as the scale-and-round does, with the last inverse stage's
-// twiddle folded into the second rows of NP_inv_q and ninv_P.
-// Bound by memory traffic: 33 limbs in and 31 out per polynomial, 1.07 GB at
-// 32 ciphertexts in 204 us (5.3 TB/s; 206 with the lift as split FMAs on the
-// VALU), at one ciphertext 15 us (21).
-template <int L, int A>
-__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4)))
-k_moddown_lift(int n, size_t n_poly, const double* __restrict__ acc,
-               const double* __restrict__ dt, double* __restrict__ ext, Tables tb) {
-  constexpr int K = L + A;
-  constexpr int W = 2 * L + 1;
-  __shared__ v4i tab[conv_entries(L, L + 1)];
+  constexpr bool SUM = OUT == MD_SUM || OUT == MD_SUM_I64, I64 = OUT == MD_I64 || OUT == MD_SUM_I64;
+  // the running sum's limbs are loaded up front where the registers allow
+  constexpr bool PRE = SUM && K + 2 * L <= 52;
+  __shared__ v4i tab[OUT == MD_LIFT ? conv_entries(L, L + 1) : 1];
   __shared__ double kl[2 * K];   // NP_inv_q's and ninv_P's two rows, limb i's at 2 i
-  conv_table<conv_entries(L, L + 1)>(tab, tb.mx_lift);
   const int t = (int)threadIdx.x, lane = t & 63;
-  if (t < 2 * K) kl[t] = t < 2 * L ? tb.NP_inv_q[(t & 1) * L + (t >> 1)] : tb.ninv_P[t - 2 * L];
-  static_assert(2 * K <= 128, "one entry per thread of the smallest block");
-  __syncthreads();
-  const bool hi = lane >= 32;
+  const bool hi = FUSED && lane >= 32;
   const double sg = hi ? -1.0 : 1.0;
   const double* kc = kl + (hi ? 1 : 0);
+  const unsigned ls = (unsigned)n * 8;
   const unsigned nb = poly_blocks(n, n_poly);
+  bool first = true;
   for (unsigned bk = blockIdx.x; bk < nb; bk += gridDim.x) {
-    const PolyBlock pb = poly_block(n, bk);   // poly = ct * 2 + b
+    const PolyBlock pb = poly_block(n, bk);
     const int cp = ((pb.c - t) >> 1) + (t >> 6) * 32 + (lane & 31);
     const int ht = n >> 6;                         // 512: see k_ntt_inv_half
-    const unsigned pos = (unsigned)((cp / ht) * 2 * ht + cp % ht + (hi ? ht : 0)) * 8;
-    const unsigned vo = (unsigned)(cp + (hi ? n >> 1 : 0)) * 8;
-    const unsigned ls = (unsigned)n * 8;
+    const unsigned pos =
+        FUSED ? (unsigned)((cp / ht) * 2 * ht + cp % ht + (hi ? ht : 0)) * 8 : (unsigned)pb.c * 8;
+    const int c = FUSED ? cp + (hi ? n >> 1 : 0) : pb.c;
+    const unsigned vo = (unsigned)c * 8;
     const size_t cb = pb.pc, ct = cb >> 1;
     const int b = (int)(cb & 1);
     const auto ra = make_rsrc(acc + cb * (size_t)K * n, (unsigned)(K * n * 8));
-    const auto re = make_rsrc(dt + (ct * 3 + b) * (size_t)W * n, (unsigned)(L * n * 8));
+    // (an empty buffer reads as zeros)
+    const auto re = make_rsrc(dt + (ct * 3 + b) * (size_t)W * n,
+                              one_e && b ? 0u : (unsigned)(L * n * 8));
     const auto rs = make_rsrc(ext + cb * (size_t)W * n, (unsigned)(W * n * 8));
     // every load is issued before the first use
-    double xa[K], e[L];
+    double xa[K], e[L], sum[PRE ? L : 1];
 #pragma unroll
     for (int m = 0; m < A; ++m) xa[L + m] = buf_load(ra, pos, (L + m) * ls);
 #pragma unroll
     for (int i = 0; i < L; ++i) {
       xa[i] = buf_load(ra, pos, i * ls);
       e[i] = buf_load(re, vo, i * ls);
+      if constexpr (PRE) sum[i] = buf_load(rs, vo, i * ls);
     }
     loads_issued();
+    if (first) {
+      if constexpr (OUT == MD_LIFT) conv_table<conv_entries(L, L + 1)>(tab, tb.mx_lift);
+      for (int k = t; k < 2 * K; k += (int)blockDim.x)
+        kl[k] = k < 2 * L ? tb.NP_inv_q[(k & 1) * L + (k >> 1)] : tb.ninv_P[k - 2 * L];
+      touch_lines<conv_steps(L) * 16>(tb.kq);
+      touch_lines<conv_steps(L) * 4 * A>(tb.km);
+      if constexpr (OUT == MD_LIFT) touch_lines<conv_steps(L + 1) * 16>(tb.kb);
+      __syncthreads();
+      first = false;
+    }
     // [N^-1 acc_Pk]_Pk of this coefficient (balanced), then the centred
     // residue's mixed-radix digits
     const int ip = 2 * L + 1;
     double as[A], kP[A];
 #pragma unroll
     for (int m = 0; m < A; ++m)
-      as[m] = mul_bal(pair_combine(xa[L + m], sg), kc[2 * (L + m)], cld(tb.p, ip + m),
-                      cld(tb.pinv, ip + m));
+      as[m] = mul_bal(FUSED ? pair_combine(xa[L + m], sg) : xa[L + m], kc[2 * (L + m)],
+                      cld(tb.p, ip + m), cld(tb.pinv, ip + m));
     special_digits<A>(as, kP, tb, L);
+    const unsigned so = store_off(pb.ok, vo);
+    int64_t* o64 = nullptr;
+    if constexpr (I64)
+      o64 = (wt.table ? wt.table[(size_t)(*wt.wave) * wt.stride + ct].out + (size_t)b * L * n
+                      : out + cb * (size_t)L * n) + c;
     double o[L], y[L];
     double S = 0.0;
     v4i g0[conv_steps(L)], g1[conv_steps(L)];
@@ -844,17 +768,35 @@ k_moddown_lift(int n, size_t n_poly, const double* __restrict__ acc,
       for (int j = 0; j < 4 && 4 * s + j < L; ++j) {
         const int i = 4 * s + j;
         const double q = cld(kq, 4 * j), qinv = cld(kq, 4 * j + 1);
-        double r = mul_lazy(pair_combine(xa[i], sg), kc[2 * i], q, qinv);
+        double r = mul_lazy(FUSED ? pair_combine(xa[i], sg) : xa[i], kc[2 * i], q, qinv);
 #pragma unroll
         for (int m = 0; m < A; ++m) r -= mul_lazy(kP[m], cld(km, A * j + m), q, qinv);
-        o[i] = reduce_bal(e[i] + r, q, qinv);
-        y[i] = mul_bal(o[i], cld(kq, 4 * j + 2), q, qinv);
-        S += y[i] * qinv;
-        buf_store(o[i], rs, vo, i * ls);
+        r += e[i];
+        if constexpr (OUT == MD_I64) {
+          // finish: -z, plus Delta at coefficient 0 of c0
+          if (finish) r = b == 0 && c == 0 ? cld(tb.delta_q, i) - r : -r;
+        }
+        double z = reduce_bal(r, q, qinv);
+        if constexpr (SUM) {
+          if constexpr (PRE) z = reduce_bal(sum[i] + z, q, qinv);
+          else z = reduce_bal(buf_load(rs, vo, i * ls) + z, q, qinv);
+        }
+        if constexpr (I64) {
+          if (pb.ok) o64[(size_t)i * n] = to_i64(z, q);
+        } else {
+          buf_store(z, rs, so, i * ls);
+        }
+        if constexpr (OUT == MD_LIFT) {
+          o[i] = z;
+          y[i] = mul_bal(z, cld(kq, 4 * j + 2), q, qinv);
+          S += y[i] * qinv;
+        }
       }
-      pack_step<L>(y, s, g0[s], g1[s]);
+      if constexpr (OUT == MD_LIFT) pack_step<L>(y, s, g0[s], g1[s]);
     }
-    lift_tail<L, MARGIN_MODDOWN_LIFT>(o, g0, g1, S, rs, vo, ls, pb.ok, tab, tb);
+    if constexpr (OUT == MD_LIFT)
+      lift_tail<L, FUSED ? MARGIN_MODDOWN_LIFT : MARGIN_LIFT>(o, g0, g1, S, rs, vo, ls, pb.ok, tab,
+                                                              tb);
   }
 }
 
@@ -864,14 +806,13 @@ k_moddown_lift(int n, size_t n_poly, const double* __restrict__ acc,
 // thread per coefficient of each (ct, b) polynomial, blocks as in k_lift.
 // wt (table not null): a batched wave's ciphertexts, x and y read through
 // the table (a broadcast y is every entry's y).
-template <int L>
+template <int L, int SITE>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4)))
 k_sub_lift(int n, size_t n_poly, const int64_t* __restrict__ xs, const int64_t* __restrict__ ys,
            int y_bcast, double* __restrict__ ext, Tables tb, WaveTab wt) {
   constexpr int W = 2 * L + 1;
   __shared__ v4i tab[conv_entries(L, L + 1)];
-  conv_table<conv_entries(L, L + 1)>(tab, tb.mx_lift);
-  __syncthreads();
+  bool first = true;
   const unsigned nb = poly_blocks(n, n_poly);
   for (unsigned bk = blockIdx.x; bk < nb; bk += gridDim.x) {
     const PolyBlock pb = poly_block(n, bk);   // poly = ct * 2 + b
@@ -896,6 +837,7 @@ k_sub_lift(int n, size_t n_poly, const int64_t* __restrict__ xs, const int64_t* 
       yv[i] = yp[(size_t)i * n];
     }
     loads_issued();
+    lift_setup<L>(tab, tb, first);
     double o[L], y[L];
     double S = 0.0;
     const unsigned so = store_off(pb.ok, vo);
@@ -914,7 +856,7 @@ k_sub_lift(int n, size_t n_poly, const int64_t* __restrict__ xs, const int64_t* 
       }
       pack_step<L>(y, s, g0[s], g1[s]);
     }
-    lift_tail<L, MARGIN_SUB_LIFT>(o, g0, g1, S, rs, vo, ls, pb.ok, tab, tb);
+    lift_tail<L, SITE>(o, g0, g1, S, rs, vo, ls, pb.ok, tab, tb);
   }
 }
 
@@ -927,8 +869,7 @@ k_i64_lift(int n, size_t n_poly, const int64_t* __restrict__ in, double* __restr
            Tables tb) {
   constexpr int W = 2 * L + 1;
   __shared__ v4i tab[conv_entries(L, L + 1)];
-  conv_table<conv_entries(L, L + 1)>(tab, tb.mx_lift);
-  __syncthreads();
+  bool first = true;
   const unsigned nb = poly_blocks(n, n_poly);
   for (unsigned bk = blockIdx.x; bk < nb; bk += gridDim.x) {
     const PolyBlock pb = poly_block(n, bk);
@@ -939,6 +880,7 @@ k_i64_lift(int n, size_t n_poly, const int64_t* __restrict__ in, double* __restr
 #pragma unroll
     for (int i = 0; i < L; ++i) xv[i] = ip[(size_t)i * n];
     loads_issued();
+    lift_setup<L>(tab, tb, first);
     double o[L], y[L];
     double S = 0.0;
     const unsigned so = store_off(pb.ok, vo);
@@ -1216,25 +1158,6 @@ __global__ void __launch_bounds__(256) k_digit_mrc(int n, int L, int n_ct, doubl
 
 // ------------------------------------------------------------ boundary ---
 
-// ext[ct][b][i] (i < L) = balanced(x - y); y broadcast over ct if y_bcast.
-__global__ void __launch_bounds__(256) k_sub_to_ext(int n, int L, int n_ct, const int64_t* x,
-                                                    const int64_t* y, int y_bcast, double* ext,
-                                                    Tables tb) {
-  const size_t gid = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const size_t per_ct = (size_t)2 * L * n;
-  if (gid >= (size_t)n_ct * per_ct) return;
-  const size_t ct = gid / per_ct;
-  const size_t r = gid - ct * per_ct;       // (b * L + i) * n + c
-  const int i = (int)((r / n) % L);
-  const double p = cld(tb.p, i), pinv = cld(tb.pinv, i);
-  const double xv = (double)x[gid];
-  const double yv = (double)y[y_bcast ? r : gid];
-  const size_t bi = r / n;                  // b * L + i
-  const int b = (int)(bi / L);
-  const int c = (int)(r - bi * n);
-  ext[((ct * 2 + b) * (size_t)(2 * L + 1) + i) * n + c] = reduce_bal(xv - yv, p, pinv);
-}
-
 // out = [a + sum_{j < k} b[j * stride]]_q per residue (BFV addition of
 // canonical residues; each partial sum is kept in [0, q) by one
 // conditional subtraction, so any k is exact).
@@ -1251,48 +1174,6 @@ __global__ void __launch_bounds__(256) k_sum_i64(int n, int L, size_t total, con
     s = s >= q ? s - q : s;
   }
   out[gid] = s;
-}
-
-// Batched waves: the ciphertexts of a wave are named by a device table of
-// per-ciphertext pointers, [wave][stride] entries, and the wave by a device
-// counter, so one captured graph serves every wave of the same size.
-__global__ void __launch_bounds__(256) k_gather_sub(int n, int L, int cnt, int stride,
-                                                    const CtPtrs* table, const int* wave,
-                                                    double* ext, Tables tb) {
-  const size_t gid = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const size_t per_ct = (size_t)2 * L * n;
-  if (gid >= (size_t)cnt * per_ct) return;
-  const size_t ct = gid / per_ct;
-  const size_t r = gid - ct * per_ct;       // (b * L + i) * n + c
-  const CtPtrs e = table[(size_t)(*wave) * stride + ct];
-  const int i = (int)((r / n) % L);
-  const double p = cld(tb.p, i), pinv = cld(tb.pinv, i);
-  const double xv = (double)e.x[r];
-  const double yv = (double)e.y[r];
-  const size_t bi = r / n;
-  const int b = (int)(bi / L);
-  const int c = (int)(r - bi * n);
-  ext[((ct * 2 + b) * (size_t)(2 * L + 1) + i) * n + c] = reduce_bal(xv - yv, p, pinv);
-}
-
-// out = ([-z0 + Delta e_0]_q, [-z1]_q) of the wave's ciphertexts in ext.
-__global__ void __launch_bounds__(256) k_scatter_mask(int n, int L, int cnt, int stride,
-                                                      const CtPtrs* table, const int* wave,
-                                                      const double* ext, Tables tb) {
-  const size_t gid = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const size_t per_ct = (size_t)2 * L * n;
-  if (gid >= (size_t)cnt * per_ct) return;
-  const size_t ct = gid / per_ct;
-  const size_t r = gid - ct * per_ct;
-  const CtPtrs e = table[(size_t)(*wave) * stride + ct];
-  const size_t bi = r / n;
-  const int b = (int)(bi / L);
-  const int i = (int)(bi - (size_t)b * L);
-  const int c = (int)(r - bi * n);
-  const double p = cld(tb.p, i), pinv = cld(tb.pinv, i);
-  double v = -ext[((ct * 2 + b) * (size_t)(2 * L + 1) + i) * n + c];
-  if (b == 0 && c == 0) v = reduce_bal(v + cld(tb.delta_q, i), p, pinv);
-  e.out[r] = to_i64(v, p);
 }
 
 __global__ void k_fill_table(TableChunk ch, CtPtrs* table) {
@@ -1337,12 +1218,11 @@ __global__ void __launch_bounds__(256) k_i64_to_polys(int n, int L, int npoly, s
       poly >= canon_from ? (double)in[gid] : from_u64(in[gid], cld(tb.p, i));
 }
 
-// balanced doubles -> canonical int64 [n_ct][npoly][L][N].  With
-// negate_delta, outputs [-x]_q plus [Delta]_q at coefficient 0 of poly 0.
+// balanced doubles -> canonical int64 [n_ct][npoly][L][N].
 __global__ void __launch_bounds__(256) k_polys_to_i64(int n, int L, int npoly, size_t total,
                                                       const double* in, size_t ct_stride,
                                                       size_t poly_stride, int64_t* out,
-                                                      int negate_delta, Tables tb) {
+                                                      Tables tb) {
   const size_t gid = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (gid >= total) return;
   const size_t row = gid / n;
@@ -1351,13 +1231,7 @@ __global__ void __launch_bounds__(256) k_polys_to_i64(int n, int L, int npoly, s
   const size_t cp = row / L;
   const size_t ct = cp / npoly;
   const int poly = (int)(cp - ct * npoly);
-  const double p = cld(tb.p, i), pinv = cld(tb.pinv, i);
-  double v = in[ct * ct_stride + poly * poly_stride + (size_t)i * n + c];
-  if (negate_delta) {
-    v = -v;
-    if (poly == 0 && c == 0) v = reduce_bal(v + cld(tb.delta_q, i), p, pinv);
-  }
-  out[gid] = to_i64(v, p);
+  out[gid] = to_i64(in[ct * ct_stride + poly * poly_stride + (size_t)i * n + c], cld(tb.p, i));
 }
 
 // rows of int64 residues -> balanced doubles; row r uses prime
@@ -1449,41 +1323,56 @@ hipError_t run_lift(const Dims& d, double* ext, const Tables& tb, hipStream_t st
   return hipGetLastError();
 }
 
-hipError_t run_moddown_finish(const Dims& d, const double* acc, const double* dt, int64_t* out,
-                              const Tables& tb, hipStream_t st, int finish) {
-  if (!d.fused) return hipErrorInvalidValue;
-  const size_t total = (size_t)d.n_ct * 2 * (d.n / 2);
-#define C_(L_, A_)                                                                             \
-  case L_:                                                                                     \
-    hipLaunchKernelGGL((k_moddown_finish<L_, A_>), grid_for(total, d.block), dim3(d.block), 0, \
-                       st, d.n, d.n_ct, acc, dt, out, finish, tb, d.tab);                      \
-    break;
+// f(L, alpha) as integral constants, for the decompositions built.
+template <class F>
+static hipError_t for_digits(int L, int alpha, F f) {
+  using std::integral_constant;
+#define C_(L_, A_) \
+  if (L == L_) return f(integral_constant<int, L_>{}, integral_constant<int, A_>{});
 #define C1_(L_) C_(L_, 1)
 #define C2_(L_) C_(L_, 2)
 #define C3_(L_) C_(L_, 3)
-  if (d.alpha == 1) {
-    switch (d.L) {
-      NSHE_L_CASES(C1_)
-      default: return hipErrorInvalidValue;
-    }
-  } else if (d.alpha == 2) {
-    switch (d.L) {
-      NSHE_L2_CASES(C2_)
-      default: return hipErrorInvalidValue;
-    }
-  } else if (d.alpha == 3) {
-    switch (d.L) {
-      NSHE_L3_CASES(C3_)
-      default: return hipErrorInvalidValue;
-    }
-  } else {
-    return hipErrorInvalidValue;
-  }
+  if (alpha == 1) { NSHE_L_CASES(C1_) }
+  if (alpha == 2) { NSHE_L2_CASES(C2_) }
+  if (alpha == 3) { NSHE_L3_CASES(C3_) }
 #undef C1_
 #undef C2_
 #undef C3_
 #undef C_
-  return hipGetLastError();
+  return hipErrorInvalidValue;
+}
+
+template <int OUT>
+static hipError_t launch_moddown(const Dims& d, const double* acc, const double* dt, double* ext,
+                                 int64_t* out, int finish, int one_e, const Tables& tb,
+                                 hipStream_t st) {
+  const size_t np = (size_t)d.n_ct * 2;
+  // the split inverse's pairs need whole blocks (see k_moddown)
+  if (d.fused && d.n % poly_threads(d)) return hipErrorInvalidValue;
+  return for_digits(d.L, d.alpha, [&](auto l, auto a) {
+    constexpr int L = decltype(l)::value, A = decltype(a)::value;
+    if (d.fused)
+      hipLaunchKernelGGL((k_moddown<L, A, true, OUT>), poly_grid(d, np), dim3(poly_threads(d)), 0,
+                         st, d.n, np, acc, dt, ext, out, finish, one_e, tb, d.tab);
+    else
+      hipLaunchKernelGGL((k_moddown<L, A, false, OUT>), poly_grid(d, np), dim3(poly_threads(d)), 0,
+                         st, d.n, np, acc, dt, ext, out, finish, one_e, tb, d.tab);
+    return hipGetLastError();
+  });
+}
+
+hipError_t run_moddown(const Dims& d, const double* acc, const double* dt, const ModDownOut& o,
+                       const Tables& tb, hipStream_t st) {
+  switch (o.kind) {
+    case MD_EXT: return launch_moddown<MD_EXT>(d, acc, dt, o.ext, nullptr, 0, o.one_e, tb, st);
+    case MD_SUM: return launch_moddown<MD_SUM>(d, acc, dt, o.ext, nullptr, 0, o.one_e, tb, st);
+    case MD_LIFT: return launch_moddown<MD_LIFT>(d, acc, dt, o.ext, nullptr, 0, o.one_e, tb, st);
+    case MD_I64:
+      return launch_moddown<MD_I64>(d, acc, dt, o.ext, o.out, o.finish, o.one_e, tb, st);
+    case MD_SUM_I64:
+      return launch_moddown<MD_SUM_I64>(d, acc, dt, o.ext, o.out, 0, o.one_e, tb, st);
+  }
+  return hipErrorInvalidValue;
 }
 
 hipError_t run_i64_lift(const Dims& d, const int64_t* in, double* ext, const Tables& tb,
@@ -1508,8 +1397,12 @@ hipError_t run_sub_lift(const Dims& d, const int64_t* x, const int64_t* y, int y
   switch (d.L) {
 #define C_(L_)                                                                            \
   case L_:                                                                                \
-    hipLaunchKernelGGL(k_sub_lift<L_>, poly_grid(d, np), dim3(poly_threads(d)), 0, st, \
-                       d.n, np, x, y, y_bcast, ext, tb, d.tab);                           \
+    if (d.fused)                                                                          \
+      hipLaunchKernelGGL((k_sub_lift<L_, MARGIN_SUB_LIFT>), poly_grid(d, np),             \
+                         dim3(poly_threads(d)), 0, st, d.n, np, x, y, y_bcast, ext, tb, d.tab); \
+    else                                                                                  \
+      hipLaunchKernelGGL((k_sub_lift<L_, MARGIN_LIFT>), poly_grid(d, np),                 \
+                         dim3(poly_threads(d)), 0, st, d.n, np, x, y, y_bcast, ext, tb, d.tab); \
     break;
     NSHE_L_CASES(C_)
 #undef C_
@@ -1517,44 +1410,6 @@ hipError_t run_sub_lift(const Dims& d, const int64_t* x, const int64_t* y, int y
   }
   return hipGetLastError();
 }
-
-hipError_t run_moddown_lift(const Dims& d, const double* acc, const double* dt, double* ext,
-                            const Tables& tb, hipStream_t st) {
-  if (!d.fused || d.n % poly_threads(d)) return hipErrorInvalidValue;
-  const size_t np = (size_t)d.n_ct * 2;
-#define C_(L_, A_)                                                                           \
-  case L_:                                                                                   \
-    hipLaunchKernelGGL((k_moddown_lift<L_, A_>), poly_grid(d, np), dim3(poly_threads(d)), \
-                       0, st, d.n, np, acc, dt, ext, tb);                                    \
-    break;
-#define C1_(L_) C_(L_, 1)
-#define C2_(L_) C_(L_, 2)
-#define C3_(L_) C_(L_, 3)
-  if (d.alpha == 1) {
-    switch (d.L) {
-      NSHE_L_CASES(C1_)
-      default: return hipErrorInvalidValue;
-    }
-  } else if (d.alpha == 2) {
-    switch (d.L) {
-      NSHE_L2_CASES(C2_)
-      default: return hipErrorInvalidValue;
-    }
-  } else if (d.alpha == 3) {
-    switch (d.L) {
-      NSHE_L3_CASES(C3_)
-      default: return hipErrorInvalidValue;
-    }
-  } else {
-    return hipErrorInvalidValue;
-  }
-#undef C1_
-#undef C2_
-#undef C3_
-#undef C_
-  return hipGetLastError();
-}
-
 
 hipError_t run_scale(const Dims& d, double* dt, const Tables& tb, hipStream_t st,
                      int digit_pairs, double* src) {
@@ -1703,46 +1558,6 @@ hipError_t run_ks_mac(const Dims& d, const double* dig, const double* evk, doubl
   return hipGetLastError();
 }
 
-hipError_t run_moddown(const Dims& d, const double* acc, const double* dt, double* ext,
-                       const Tables& tb, hipStream_t st, int accumulate) {
-  const size_t total = (size_t)d.n_ct * 2 * (d.fused ? d.n / 2 : d.n);
-#define C_(L_, A_)                                                                              \
-  case L_:                                                                                      \
-    if (d.fused)                                                                                \
-      hipLaunchKernelGGL((k_moddown<L_, A_, true>), grid_for(total, d.block), dim3(d.block), 0, \
-                         st, d.n, d.n_ct, acc, dt, ext, accumulate, tb);                        \
-    else                                                                                        \
-      hipLaunchKernelGGL((k_moddown<L_, A_, false>), grid_for(total, d.block), dim3(d.block),   \
-                         0, st, d.n, d.n_ct, acc, dt, ext, accumulate, tb);                     \
-    break;
-#define C1_(L_) C_(L_, 1)
-#define C2_(L_) C_(L_, 2)
-#define C3_(L_) C_(L_, 3)
-  if (d.alpha == 1) {
-    switch (d.L) {
-      NSHE_L_CASES(C1_)
-      default: return hipErrorInvalidValue;
-    }
-  } else if (d.alpha == 2) {
-    switch (d.L) {
-      NSHE_L2_CASES(C2_)
-      default: return hipErrorInvalidValue;
-    }
-  } else if (d.alpha == 3) {
-    switch (d.L) {
-      NSHE_L3_CASES(C3_)
-      default: return hipErrorInvalidValue;
-    }
-  } else {
-    return hipErrorInvalidValue;
-  }
-#undef C1_
-#undef C2_
-#undef C3_
-#undef C_
-  return hipGetLastError();
-}
-
 hipError_t run_digit_mrc(const Dims& d, double* src, size_t src_stride, const Tables& tb,
                          hipStream_t st) {
   if (d.alpha < 2 || d.alpha > 3 || d.L % d.alpha) return hipErrorInvalidValue;
@@ -1761,14 +1576,6 @@ hipError_t run_digit_split(const Dims& d, const double* dt, double* src, size_t 
   const size_t total = (size_t)d.n_ct * d.L * d.n;
   hipLaunchKernelGGL(k_digit_split, grid_for(total), dim3(256), 0, st, d.n, d.L, d.n_ct, dt, src,
                      src_stride);
-  return hipGetLastError();
-}
-
-hipError_t run_sub_to_ext(const Dims& d, const int64_t* x, const int64_t* y, int y_bcast,
-                          double* ext, const Tables& tb, hipStream_t st) {
-  const size_t total = (size_t)d.n_ct * 2 * d.L * d.n;
-  hipLaunchKernelGGL(k_sub_to_ext, grid_for(total), dim3(256), 0, st, d.n, d.L, d.n_ct, x, y,
-                     y_bcast, ext, tb);
   return hipGetLastError();
 }
 
@@ -1851,22 +1658,6 @@ hipError_t run_sum_i64(const Dims& d, const int64_t* a, const int64_t* b, size_t
   return hipGetLastError();
 }
 
-hipError_t run_gather_sub(const Dims& d, int stride, const CtPtrs* table, const int* wave,
-                          double* ext, const Tables& tb, hipStream_t st) {
-  const size_t total = (size_t)d.n_ct * 2 * d.L * d.n;
-  hipLaunchKernelGGL(k_gather_sub, grid_for(total), dim3(256), 0, st, d.n, d.L, d.n_ct, stride,
-                     table, wave, ext, tb);
-  return hipGetLastError();
-}
-
-hipError_t run_scatter_mask(const Dims& d, int stride, const CtPtrs* table, const int* wave,
-                            const double* ext, const Tables& tb, hipStream_t st) {
-  const size_t total = (size_t)d.n_ct * 2 * d.L * d.n;
-  hipLaunchKernelGGL(k_scatter_mask, grid_for(total), dim3(256), 0, st, d.n, d.L, d.n_ct, stride,
-                     table, wave, ext, tb);
-  return hipGetLastError();
-}
-
 hipError_t run_fill_table(const TableChunk& ch, CtPtrs* table, hipStream_t st) {
   hipLaunchKernelGGL(k_fill_table, dim3(1), dim3(TableChunk::CAP), 0, st, ch, table);
   return hipGetLastError();
@@ -1899,11 +1690,11 @@ hipError_t run_i64_to_polys(const Dims& d, const int64_t* in, int npoly_in, doub
 }
 
 hipError_t run_polys_to_i64(const Dims& d, const double* in, int npoly, size_t in_ct_stride,
-                            size_t in_poly_stride, int64_t* out, int negate_delta,
-                            const Tables& tb, hipStream_t st) {
+                            size_t in_poly_stride, int64_t* out, const Tables& tb,
+                            hipStream_t st) {
   const size_t total = (size_t)d.n_ct * npoly * d.L * d.n;
   hipLaunchKernelGGL(k_polys_to_i64, grid_for(total), dim3(256), 0, st, d.n, d.L, npoly, total,
-                     in, in_ct_stride, in_poly_stride, out, negate_delta, tb);
+                     in, in_ct_stride, in_poly_stride, out, tb);
   return hipGetLastError();
 }
 
