@@ -240,8 +240,9 @@ int nshe_relinearize(nshe_ctx* ctx, const int64_t* in3_dev, int64_t* out_dev,
  * x is [n_ct][2][L][N]; y is the same shape, or one ciphertext broadcast to
  * every x when y_broadcast != 0 (an encrypted predicate constant).  Requires
  * t - 1 = 2^k (k squarings).  out may alias x (not y when broadcast).
- * From 32 ciphertexts on, the call runs its two halves on two streams
- * (tuning streams, see nshe_tuning); it stays ordered on `stream`. */
+ * From two ciphertexts on (four with alpha = 1; 2^15 coefficients in smaller
+ * rings), the call runs its two halves on two streams (tuning streams, see
+ * nshe_tuning); it stays ordered on `stream`. */
 int nshe_eq_mask(nshe_ctx* ctx, const int64_t* x_dev, const int64_t* y_dev,
                  int64_t* out_dev, int n_ct, int y_broadcast, void* ws_dev,
                  size_t ws_bytes, void* stream);
@@ -273,9 +274,9 @@ int nshe_eq_mask_noalloc(nshe_ctx* ctx, const int64_t* x_dev, const int64_t* y_d
  * in the workspace (filled by small kernels at the start of the call), so
  * one graph per wave size serves every wave and every later call with the
  * same workspace and wave size.  Capture runs on a context-owned stream and
- * the graph is launched on `stream` (with tuning streams = 2 and waves of at
- * least 32: half-waves, on `stream` and the context's second stream in
- * turn, one graph per stream and half-wave size).  ws_bytes must cover
+ * the graph is launched on `stream` (with tuning streams = 2: half-waves, on
+ * `stream` and the context's second stream in turn, one graph per stream and
+ * half-wave size).  ws_bytes must cover
  * nshe_batched_workspace_bytes(ctx, wave size, total ciphertexts); with
  * wave_ct = 0 the wave is the tuned one, capped by what ws_bytes holds. */
 typedef struct {
@@ -408,7 +409,8 @@ int nshe_join_sum(nshe_ctx* ctx, const int64_t* a_key_dev, const int64_t* b_key_
  * nshe_sum_slots of a 0/1 mask, SUM nshe_sum_slots of a column times the
  * mask (nshe_mul_relin).  Workspace: nshe_workspace_bytes(ctx, n_ct).
  * NSHE_ENOKEY names a missing Galois key.  nshe_sum_slots runs the two
- * halves of 32 or more ciphertexts on two streams (tuning streams). */
+ * halves of two or more ciphertexts (eight with alpha = 1) on two streams
+ * (tuning streams). */
 int nshe_set_galois_key(nshe_ctx* ctx, uint32_t g, const int64_t* key_dev, size_t n_words,
                         void* stream);
 int nshe_galois_elements(const nshe_ctx* ctx, uint32_t* out_host, int max_out, int* n_out_host);
@@ -436,20 +438,21 @@ int nshe_sum_slots(nshe_ctx* ctx, const int64_t* in_dev, int64_t* out_dev, int n
  *                  product runs fused with the digit transforms (one
  *                  kernel; the digits' transforms are never written),
  *                  0: digit transforms, then the product (two kernels);
- *   streams        2: nshe_eq_mask and nshe_sum_slots with at least 32
- *                  ciphertexts run the first half of them on `stream` and
- *                  the second half on a second stream the context owns
- *                  (non-blocking, default priority), each in its own half
- *                  of the workspace, so
- *                  that one half's kernels fill the GPU while the other's
- *                  drain; nshe_eq_mask_batched with waves of at least 32
- *                  runs half-waves, taking turns between the two streams
- *                  (each with its own half of the wave's workspace).  The
- *                  second stream starts after the work already on `stream`
- *                  and `stream` waits for it at the end (events), so the
- *                  call stays ordered on `stream`.  Not while profiling,
- *                  while `stream` is being captured into a graph, or in
- *                  nshe_eq_mask_noalloc.  1: one stream.
+ *   streams        2: nshe_eq_mask and nshe_sum_slots over two or more
+ *                  ciphertexts (four and eight with alpha = 1),
+ *                  nshe_mul_relin and nshe_square_relin over eight or
+ *                  more (all: 2^15 coefficients or more), run the first half
+ *                  of them on `stream` and the second half on a second
+ *                  stream the context owns (non-blocking, default priority),
+ *                  each in its own half of the workspace, so that one half's
+ *                  kernels fill the GPU while the other's drain;
+ *                  nshe_eq_mask_batched runs half-waves, taking turns
+ *                  between the two streams (each with its own half of the
+ *                  wave's workspace).  The second stream starts after the
+ *                  work already on `stream` and `stream` waits for it at the
+ *                  end (events), so the call stays ordered on `stream`.  Not
+ *                  while profiling, while `stream` is being captured into a
+ *                  graph, or in nshe_eq_mask_noalloc.  1: one stream.
  * A new context starts at {32, 1, 128, 0, 0, 2}.  nshe_set_tuning validates the
  * values (NSHE_EINVAL otherwise) and drops the batched call's cached graphs.
  *
