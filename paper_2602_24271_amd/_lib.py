@@ -105,6 +105,7 @@ SIGNATURES = {
     "nshe_in_workspace_bytes": (_SZ, [_P, _I, _I, _I]),
     "nshe_in_mask": (_I, [_P, _P, _P, _I, _P, _I, _I, _I, _P, _SZ, _P]),
     "nshe_compare_workspace_bytes": (_SZ, [_P, _I]),
+    "nshe_compare_workspace_wide_bytes": (_SZ, [_P, _I]),
     "nshe_compare": (_I, [_P, _P, _P, _I, _I, _P, _I, _P, _SZ, _P]),
     "nshe_between": (_I, [_P, _P, _P, _P, _I, _P, _I, _P, _SZ, _P]),
     "nshe_mul_plain": (_I, [_P, _P, _P, _P, _I, _P, _SZ, _P]),

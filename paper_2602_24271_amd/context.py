@@ -227,7 +227,12 @@ class Context:
         need = int(self._lib.nshe_compare_workspace_bytes(self._h, n))
         if need == 0:
             raise ValueError("comparisons need t = 2^K + 1 prime")
-        return self._workspace_bytes(need)
+        try:
+            # room for batches of the program's products
+            return self._workspace_bytes(
+                int(self._lib.nshe_compare_workspace_wide_bytes(self._h, n)))
+        except torch.OutOfMemoryError:
+            return self._workspace_bytes(need)
 
     def compare(self, x: torch.Tensor, y: torch.Tensor, op: str = "lt") -> torch.Tensor:
         """[x < y] (op "lt") or [x <= y] (op "le") for |x - y| <= (t-1)/2

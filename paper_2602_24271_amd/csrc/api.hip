@@ -425,7 +425,8 @@ static DigitSrc digit_src(const nshe_ctx* c, const Ws& w) {
 }
 
 static int tensor_scale(nshe_ctx* c, const Ws& w, const double* fx_b, int n_ct, hipStream_t st,
-                        const double* fx_a = nullptr, bool residues = false) {
+                        const double* fx_a = nullptr, bool residues = false, int a_mod = 0,
+                        int a_off = 0) {
   Dims d = dims(c, n_ct);
   {
     // the tensor product is formed while the inverse transform loads
@@ -439,6 +440,8 @@ static int tensor_scale(nshe_ctx* c, const Ws& w, const double* fx_b, int n_ct, 
     j.src = fx_a ? fx_a : w.fx;
     j.src_b = fx_b;
     j.src_ct_stride = (size_t)2 * W_of(c) * c->n;
+    j.src_mod = a_mod;   // a first operand shared by several products (NttJob)
+    j.src_off = a_off;
     j.split_inv = d.fused;
     Prof pf(c, K_NTT_INV_TENSOR, st, ntt_work(c, j.count));
     HIPCHK(run_ntt(c->log2n, j, c->tb, 3, st));
@@ -1446,11 +1449,16 @@ static double* fx_second(const nshe_ctx* c, const Ws& w, int n_ct) {
   return w.dig + (size_t)n_ct * 2 * W_of(c) * c->n;
 }
 
+// A product's two operands lifted (into the digit region, which holds both)
+// and transformed in one launch each: a's transform into w.ext, b's into w.fx,
+// which follows it.
 static int load_two(nshe_ctx* c, const Ws& w, const int64_t* a, const int64_t* b, int n_ct,
                     hipStream_t st) {
-  int rc = prepare_i64(c, a, w.ext, w.fx, n_ct, st);
-  if (rc) return rc;
-  return prepare_i64(c, b, w.dig, fx_second(c, w, n_ct), n_ct, st);
+  {
+    Prof pf(c, K_LIFT, st, 4.0 * n_ct * c->n);
+    HIPCHK(run_i64_lift(dims(c, n_ct), a, w.dig, c->tb, st, b));
+  }
+  return ntt_job_ext(c, w.dig, w.ext, n_ct * 4, 0, st);
 }
 
 int nshe_mul_relin(nshe_ctx* c, const int64_t* a, const int64_t* b, int64_t* out, int n_ct,
@@ -1467,7 +1475,7 @@ int nshe_mul_relin(nshe_ctx* c, const int64_t* a, const int64_t* b, int64_t* out
                     [&](int, int c0, int cnt, void* wsh, hipStream_t s) {
     Ws w = carve(c, wsh, cnt);
     int r = load_two(c, w, a + c0 * ctw, b + c0 * ctw, cnt, s);
-    if (!r) r = tensor_scale(c, w, fx_second(c, w, cnt), cnt, s);
+    if (!r) r = tensor_scale(c, w, w.fx, cnt, s, w.ext);
     return r ? r : relin_i64(c, w, cnt, s, out + c0 * ctw);
   });
 }
@@ -1486,7 +1494,7 @@ int nshe_multiply(nshe_ctx* c, const int64_t* a, const int64_t* b, int64_t* out3
   const size_t W = W_of(c), N = c->n;
   rc = load_two(c, w, a, b, n_ct, st);
   if (rc) return rc;
-  rc = tensor_scale(c, w, fx_second(c, w, n_ct), n_ct, st, nullptr, true);
+  rc = tensor_scale(c, w, w.fx, n_ct, st, w.ext, true);
   if (rc) return rc;
   HIPCHK(run_polys_to_i64(d, w.dt, 3, 3 * W * N, W * N, out3, c->tb, st));
   return NSHE_OK;
@@ -2199,6 +2207,18 @@ size_t nshe_compare_workspace_bytes(const nshe_ctx* c, int n_ct) {
          ws_doubles(c, n_ct) * sizeof(double);
 }
 
+// Products whose operands are ready together run as one batch over up to this
+// many ciphertexts (products of n_ct each, at most 16 products), as far as the
+// workspace holds them.
+constexpr int CMP_BATCH_CT = 32;
+static int cmp_batch(int n_ct) { return std::max(1, std::min(16, CMP_BATCH_CT / std::max(n_ct, 1))); }
+
+size_t nshe_compare_workspace_wide_bytes(const nshe_ctx* c, int n_ct) {
+  const size_t base = nshe_compare_workspace_bytes(c, n_ct);
+  if (base == 0) return 0;
+  return base + (size_t)(cmp_batch(n_ct) - 1) * ws_doubles(c, n_ct) * sizeof(double);
+}
+
 struct CmpArea {
   int64_t* slot0;
   size_t U;       // int64 words per slot
@@ -2206,27 +2226,32 @@ struct CmpArea {
   double* dacc;   // the giants' products' summed tensor
   void* mws;      // multiply workspace
   size_t mws_bytes;
+  int batch;      // products it holds at once
   int64_t* slot(int i) const { return slot0 + (size_t)i * U; }
 };
 
-// A product a * b relinearized (as nshe_mul_relin) whose first operand's
-// lift and transform are kept in the area's fx and reused while the next
-// product has the same first operand (`held`): the babies' and giants'
-// products share their power-of-two factor.  Same arithmetic, so the same
-// result as nshe_mul_relin.
-static int mul_shared(nshe_ctx* c, const CmpArea& a, const int64_t** held, const int64_t* x,
-                      const int64_t* y, int64_t* out, int n_ct, hipStream_t st) {
-  Ws w = carve(c, a.mws, n_ct);
-  if (*held != x) {
-    int rc = prepare_i64(c, x, w.ext, a.fx, n_ct, st);
-    if (rc) return rc;
-    *held = x;
+// The products x * y_j -> out_j, j < count, relinearized (as nshe_mul_relin),
+// of one operand x (n_ct ciphertexts) with count operands in consecutive slots
+// from y, into consecutive slots from out: in batches of a.batch products,
+// each batch one pass of the kernels.  x's lift and transform are made once,
+// into the area's fx.  Same arithmetic, so the same results as nshe_mul_relin.
+static int mul_shared(nshe_ctx* c, const CmpArea& a, const int64_t* x, const int64_t* y,
+                      int64_t* out, int count, int n_ct, hipStream_t st) {
+  const size_t ctw = (size_t)2 * c->L * c->n;
+  int rc = prepare_i64(c, x, carve(c, a.mws, n_ct).ext, a.fx, n_ct, st);
+  for (int j = 0; j < count && !rc; j += a.batch) {
+    const int64_t* yj = y + j * a.U;
+    int64_t* oj = out + j * a.U;
+    const int cts = std::min(a.batch, count - j) * n_ct;
+    rc = run_halves(c, cts, PRODUCT_HALVES_FROM, 1, a.mws, st,
+                    [&](int, int c0, int cnt, void* wsh, hipStream_t s) {
+      Ws w = carve(c, wsh, cnt);
+      int r = prepare_i64(c, yj + c0 * ctw, w.dig, fx_second(c, w, cnt), cnt, s);
+      if (!r) r = tensor_scale(c, w, fx_second(c, w, cnt), cnt, s, a.fx, false, n_ct, c0 % n_ct);
+      return r ? r : relin_i64(c, w, cnt, s, oj + c0 * ctw);
+    });
   }
-  int rc = prepare_i64(c, y, w.dig, fx_second(c, w, n_ct), n_ct, st);
-  if (rc) return rc;
-  rc = tensor_scale(c, w, fx_second(c, w, n_ct), n_ct, st, a.fx);
-  if (rc) return rc;
-  return relin_i64(c, w, n_ct, st, out);
+  return rc;
 }
 
 // LT of the differences z (int64, n_ct ciphertexts, not in the area) into
@@ -2247,32 +2272,28 @@ static int lt_core(nshe_ctx* c, const int64_t* z, int64_t* out, int n_ct, const 
     if (rc) return rc;
     lev[i] = a.slot(s_lev + i);
   }
+  // the powers of two among the babies and giants are chain levels: copied to
+  // their slots, so that each round's operands are consecutive
+  auto place = [&](int slot, int level) -> int {
+    HIPCHK(run_sum_i64(d, lev[level], nullptr, 0, 0, a.slot(slot), c->tb, st));
+    return NSHE_OK;
+  };
   BabyPtrs bp{};
   HIPCHK(run_fill_one(d, a.slot(s_bab), c->tb, st));
-  bp.p[0] = a.slot(s_bab);
-  bp.p[1] = lev[1];
-  const int64_t* held = nullptr;   // the operand whose transform a.fx holds
-  for (int i = 2; i < k; ++i) {
-    const int h = 1 << ilog2(i), r = i - h;
-    if (r == 0) {
-      bp.p[i] = lev[ilog2(i) + 1];
-    } else {
-      int rc = mul_shared(c, a, &held, bp.p[h], bp.p[r], a.slot(s_bab + i), n_ct, st);
-      if (rc) return rc;
-      bp.p[i] = a.slot(s_bab + i);
-    }
+  for (int i = 0; i < k; ++i) bp.p[i] = a.slot(s_bab + i);
+  for (int h = 1; h < k; h *= 2) {
+    // B_h is a level; B_(h+r) = B_h B_r, r = 1..h-1
+    int rc = place(s_bab + h, ilog2(h) + 1);
+    if (!rc && h > 1)
+      rc = mul_shared(c, a, bp.p[h], bp.p[1], a.slot(s_bab + h + 1), h - 1, n_ct, st);
+    if (rc) return rc;
   }
-  std::vector<const int64_t*> gi(m, nullptr);
-  if (m > 1) gi[1] = lev[ilog2(k) + 1];
-  for (int j = 2; j < m; ++j) {
-    const int h = 1 << ilog2(j), r = j - h;
-    if (r == 0) {
-      gi[j] = lev[ilog2(k) + ilog2(j) + 1];
-    } else {
-      int rc = mul_shared(c, a, &held, gi[h], gi[r], a.slot(s_gi + j), n_ct, st);
-      if (rc) return rc;
-      gi[j] = a.slot(s_gi + j);
-    }
+  for (int h = 1; h < m; h *= 2) {
+    int rc = place(s_gi + h, ilog2(k) + ilog2(h) + 1);
+    if (!rc && h > 1)
+      rc = mul_shared(c, a, a.slot(s_gi + h), a.slot(s_gi + 1), a.slot(s_gi + h + 1), h - 1, n_ct,
+                      st);
+    if (rc) return rc;
   }
   // g = G_0 + sum_{j>=1} G_j W_j, G_j = sum_i c_(2(jk+i)+1) B_i in chunks of
   // 16.  The products' tensors are summed in the extended basis (exact: Q B
@@ -2285,17 +2306,14 @@ static int lt_core(nshe_ctx* c, const int64_t* z, int64_t* out, int n_ct, const 
       Prof pf(c, K_LINCOMB, st, (double)J * k * n_ct * 2 * c->L * c->n);
       HIPCHK(run_lincomb(d, k, bp, c->lt_coef + (size_t)j0 * k, J, a.slot(s_G), a.U, c->tb, st));
     }
-    for (int jj = 0; jj < J; ++jj) {
-      const int j = j0 + jj;
-      const int64_t* Gj = a.slot(s_G + jj);
-      if (j == 0) {
-        HIPCHK(run_sum_i64(d, Gj, nullptr, 0, 0, g, c->tb, st));
-        continue;
-      }
-      int rc = load_two(c, w, Gj, gi[j], n_ct, st);
+    if (j0 == 0) HIPCHK(run_sum_i64(d, a.slot(s_G), nullptr, 0, 0, g, c->tb, st));
+    for (int jj = j0 == 0 ? 1 : 0; jj < J; jj += a.batch) {
+      const int p = std::min(a.batch, J - jj), j = j0 + jj;
+      Ws wb = carve(c, a.mws, p * n_ct);
+      int rc = load_two(c, wb, a.slot(s_G + jj), a.slot(s_gi + j), p * n_ct, st);
       if (rc) return rc;
-      Prof pf(c, K_TENSOR_MAC, st, 3.0 * n_ct * W_of(c) * c->n);
-      HIPCHK(run_tensor_mac(d, w.fx, fx_second(c, w, n_ct), a.dacc, j == 1 ? 1 : 0, c->tb, st));
+      Prof pf(c, K_TENSOR_MAC, st, 3.0 * p * n_ct * W_of(c) * c->n);
+      HIPCHK(run_tensor_mac(d, p, wb.ext, wb.fx, a.dacc, j == 1 ? 1 : 0, c->tb, st));
     }
   }
   if (m > 1) {
@@ -2356,6 +2374,11 @@ static int cmp_checks(nshe_ctx* c, int n_ct, void* ws, size_t ws_bytes, CmpArea*
   const size_t used = (size_t)cmp_slots(c) * cb + fx_bytes(c, n_ct) + dacc_bytes(c, n_ct);
   a->mws = static_cast<char*>(ws) + used;
   a->mws_bytes = ws_bytes - used;
+  // consecutive slots hold consecutive ciphertexts unless they are padded
+  a->batch = cb == (size_t)n_ct * 2 * c->L * c->n * sizeof(int64_t)
+                 ? (int)std::min<size_t>(cmp_batch(n_ct),
+                                         a->mws_bytes / (ws_doubles(c, n_ct) * sizeof(double)))
+                 : 1;
   return NSHE_OK;
 }
 

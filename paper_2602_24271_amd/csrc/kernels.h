@@ -152,6 +152,10 @@ struct NttJob {
   const double* src;
   const double* src_b;
   size_t src_ct_stride;      // doubles between ciphertexts in src
+  // products with a shared operand: ciphertext ct's first operand is
+  // ciphertext (ct + src_off) mod src_mod of src (src_mod 0: ct)
+  int src_mod = 0;
+  int src_off = 0;
   int digits;                // digits per ciphertext (L / alpha)
   int alpha = 1;             // data primes per digit
   int split = 1;             // 2^15-point forward: two workgroups per limb
@@ -235,9 +239,10 @@ struct ModDownOut {
 };
 hipError_t run_moddown(const Dims& d, const double* acc, const double* dt, const ModDownOut& o,
                        const Tables& tb, hipStream_t st);
-// int64 ciphertexts into ext followed by their lift (a product's operands)
+// int64 ciphertexts into ext followed by their lift (a product's operands);
+// in2 (not null): d.n_ct more ciphertexts, following the first in ext
 hipError_t run_i64_lift(const Dims& d, const int64_t* in, double* ext, const Tables& tb,
-                        hipStream_t st);
+                        hipStream_t st, const int64_t* in2 = nullptr);
 // subtraction into ext followed by its lift (the first squaring's operand)
 hipError_t run_sub_lift(const Dims& d, const int64_t* x, const int64_t* y, int y_bcast,
                         double* ext, const Tables& tb, hipStream_t st);
@@ -256,7 +261,8 @@ struct BabyPtrs {
   static constexpr int CAP = 256;
   const int64_t* p[CAP];
 };
-hipError_t run_tensor_mac(const Dims& d, const double* fa, const double* fb, double* acc,
+// (k products' transforms, one after the other in fa and fb)
+hipError_t run_tensor_mac(const Dims& d, int k, const double* fa, const double* fb, double* acc,
                           int first, const Tables& tb, hipStream_t st);
 hipError_t run_lincomb(const Dims& d, int k, const BabyPtrs& b, const double* coef, int J,
                        int64_t* out, size_t out_stride, const Tables& tb, hipStream_t st);

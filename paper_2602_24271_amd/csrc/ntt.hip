@@ -828,10 +828,12 @@ k_ntt_inv(NttJob job, Tables tb) {
     // would make every load wait for the one before it.
     const int ct = poly / 3;
     const int k = poly - ct * 3;
+    const int ca = job.src_mod ? (ct + job.src_off) % job.src_mod : ct;
+    const size_t a0 = (size_t)ca * job.src_ct_stride + (size_t)limb * S::N;
     const size_t o0 = (size_t)ct * job.src_ct_stride + (size_t)limb * S::N;
     const size_t o1 = o0 + job.src_ct_stride / 2;
-    const auto ra0 = make_rsrc(job.src + o0, S::N * 8);
-    const auto ra1 = make_rsrc(job.src + o1, S::N * 8);
+    const auto ra0 = make_rsrc(job.src + a0, S::N * 8);
+    const auto ra1 = make_rsrc(job.src + a0 + job.src_ct_stride / 2, S::N * 8);
     if constexpr (MODE == INV_TENSOR) {
       if (k == 1)
         tensor_square<LOGN, true>(x, ra0, ra1, vo, p, pinv);
@@ -1281,10 +1283,12 @@ k_ntt_inv_half(NttJob job, Tables tb) {
     // as in k_ntt_inv (same element stride, 1024), from this half's slots
     const int ct = poly / 3;
     const int k = poly - ct * 3;
+    const int ca = job.src_mod ? (ct + job.src_off) % job.src_mod : ct;
+    const size_t a0 = (size_t)ca * job.src_ct_stride + (size_t)limb * NF;
     const size_t o0 = (size_t)ct * job.src_ct_stride + (size_t)limb * NF;
     const size_t o1 = o0 + job.src_ct_stride / 2;
-    const auto ra0 = make_rsrc(job.src + o0, NF * 8);
-    const auto ra1 = make_rsrc(job.src + o1, NF * 8);
+    const auto ra0 = make_rsrc(job.src + a0, NF * 8);
+    const auto ra1 = make_rsrc(job.src + a0 + job.src_ct_stride / 2, NF * 8);
     if constexpr (MODE == INV_TENSOR) {
       if (k == 1)
         tensor_square<15, true, true>(x, ra0, ra1, vi, p, pinv);

@@ -862,18 +862,22 @@ k_sub_lift(int n, size_t n_poly, const int64_t* __restrict__ xs, const int64_t* 
 
 // Canonical int64 residues of n_poly polynomials ([n_poly][L][N]) into ext
 // limbs 0..L-1 (balanced) and their lift into limbs L..2L: the conversion
-// (k_i64_to_polys) and k_lift in one pass, the same arithmetic.
+// (k_i64_to_polys) and k_lift in one pass, the same arithmetic.  The first
+// n_first polynomials come from in, the others from in2 (a product's two
+// operands in one launch).
 template <int L>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4)))
-k_i64_lift(int n, size_t n_poly, const int64_t* __restrict__ in, double* __restrict__ ext,
-           Tables tb) {
+k_i64_lift(int n, size_t n_poly, const int64_t* __restrict__ in,
+           const int64_t* __restrict__ in2, size_t n_first, double* __restrict__ ext, Tables tb) {
   constexpr int W = 2 * L + 1;
   __shared__ v4i tab[conv_entries(L, L + 1)];
   bool first = true;
   const unsigned nb = poly_blocks(n, n_poly);
   for (unsigned bk = blockIdx.x; bk < nb; bk += gridDim.x) {
     const PolyBlock pb = poly_block(n, bk);
-    const int64_t* ip = in + pb.pc * (size_t)L * n + pb.c;
+    const int64_t* ip =
+        (pb.pc < n_first ? in + pb.pc * (size_t)L * n : in2 + (pb.pc - n_first) * (size_t)L * n) +
+        pb.c;
     const auto rs = make_rsrc(ext + pb.pc * (size_t)W * n, (unsigned)(W * n * 8));
     const unsigned vo = (unsigned)pb.c * 8, ls = (unsigned)n * 8;
     int64_t xv[L];
@@ -948,13 +952,13 @@ __global__ void __launch_bounds__(256) k_pointwise_plain(int n, int L, int n_ct,
 
 // ----------------------------------------------------------- comparisons ---
 
-// acc += the tensor of two transformed operands (acc = it when first):
-// per limb of the extended basis, pointwise in the NTT domain, d0 = a0 b0,
-// d1 = a0 b1 + a1 b0, d2 = a1 b1, each running sum kept as a balanced
-// residue.  fa, fb: [n_ct][2][W][N] (balanced transform outputs); acc:
+// acc += the tensors of k products of transformed operands (acc = their sum
+// when first): per limb of the extended basis, pointwise in the NTT domain, d0
+// = a0 b0, d1 = a0 b1 + a1 b0, d2 = a1 b1, each running sum kept as a balanced
+// residue.  fa, fb: [k][n_ct][2][W][N] (balanced transform outputs); acc:
 // [n_ct][3][W][N].  Summing products' tensors before one scale-and-round
 // is exact while the sum stays inside the extended basis' range.
-__global__ void __launch_bounds__(256) k_tensor_mac(int n, int W, size_t total,
+__global__ void __launch_bounds__(256) k_tensor_mac(int n, int W, size_t total, int k,
                                                     const double* __restrict__ fa,
                                                     const double* __restrict__ fb,
                                                     double* __restrict__ acc, int first,
@@ -968,18 +972,22 @@ __global__ void __launch_bounds__(256) k_tensor_mac(int n, int W, size_t total,
   const double* a = fa + ct * 2 * per + r;
   const double* b = fb + ct * 2 * per + r;
   double* o = acc + ct * 3 * per + r;
-  const double a0 = a[0], a1 = a[per], b0 = b[0], b1 = b[per];
-  double d0 = mul_lazy(a0, b0, p, pinv);
-  double d1 = mul_lazy(a0, b1, p, pinv) + mul_lazy(a1, b0, p, pinv);
-  double d2 = mul_lazy(a1, b1, p, pinv);
+  double d0 = 0.0, d1 = 0.0, d2 = 0.0;
   if (!first) {
-    d0 += o[0];
-    d1 += o[per];
-    d2 += o[2 * per];
+    d0 = o[0];
+    d1 = o[per];
+    d2 = o[2 * per];
   }
-  o[0] = reduce_bal(d0, p, pinv);
-  o[per] = reduce_bal(d1, p, pinv);
-  o[2 * per] = reduce_bal(d2, p, pinv);
+#pragma unroll 4
+  for (int j = 0; j < k; ++j, a += 2 * total, b += 2 * total) {
+    const double a0 = a[0], a1 = a[per], b0 = b[0], b1 = b[per];
+    d0 = reduce_bal(d0 + mul_lazy(a0, b0, p, pinv), p, pinv);
+    d1 = reduce_bal(d1 + (mul_lazy(a0, b1, p, pinv) + mul_lazy(a1, b0, p, pinv)), p, pinv);
+    d2 = reduce_bal(d2 + mul_lazy(a1, b1, p, pinv), p, pinv);
+  }
+  o[0] = d0;
+  o[per] = d1;
+  o[2 * per] = d2;
 }
 
 // out[jj * out_stride + r] = [sum_t coef[jj * k + t] * b.p[t][r]]_q per
@@ -1376,13 +1384,13 @@ hipError_t run_moddown(const Dims& d, const double* acc, const double* dt, const
 }
 
 hipError_t run_i64_lift(const Dims& d, const int64_t* in, double* ext, const Tables& tb,
-                        hipStream_t st) {
-  const size_t np = (size_t)d.n_ct * 2;
+                        hipStream_t st, const int64_t* in2) {
+  const size_t first = (size_t)d.n_ct * 2, np = in2 ? 2 * first : first;
   switch (d.L) {
-#define C_(L_)                                                                            \
-  case L_:                                                                                \
-    hipLaunchKernelGGL(k_i64_lift<L_>, poly_grid(d, np), dim3(poly_threads(d)), 0, st, \
-                       d.n, np, in, ext, tb);                                             \
+#define C_(L_)                                                                                 \
+  case L_:                                                                                     \
+    hipLaunchKernelGGL(k_i64_lift<L_>, poly_grid(d, np), dim3(poly_threads(d)), 0, st, d.n, np, \
+                       in, in2, first, ext, tb);                                               \
     break;
     NSHE_L_CASES(C_)
 #undef C_
@@ -1600,12 +1608,12 @@ hipError_t run_pointwise_plain(const Dims& d, double* fx, const double* pt, cons
   return hipGetLastError();
 }
 
-hipError_t run_tensor_mac(const Dims& d, const double* fa, const double* fb, double* acc,
+hipError_t run_tensor_mac(const Dims& d, int k, const double* fa, const double* fb, double* acc,
                           int first, const Tables& tb, hipStream_t st) {
   const int W = 2 * d.L + 1;
   const size_t total = (size_t)d.n_ct * W * d.n;
-  hipLaunchKernelGGL(k_tensor_mac, grid_for(total), dim3(256), 0, st, d.n, W, total, fa, fb, acc,
-                     first, tb);
+  hipLaunchKernelGGL(k_tensor_mac, grid_for(total), dim3(256), 0, st, d.n, W, total, k, fa, fb,
+                     acc, first, tb);
   return hipGetLastError();
 }
 
