@@ -1895,19 +1895,27 @@ static unsigned inv_mod_2n(const nshe_ctx* c, uint32_t g) {
   return x & (2u * (uint32_t)c->n - 1u);
 }
 
-// One rotation of the ciphertexts in w.ext by Galois element g, its result left
-// as `md` says.
+// One rotation of the ciphertexts in w.ext (with their rotation digits) by
+// Galois element g, its result left as `md` says.
 static int rotate_ext(nshe_ctx* c, const Ws& w, int n_ct, uint32_t g, const double* key,
                       ModDownOut md, hipStream_t st) {
-  Dims d = dims(c, n_ct);
   {
     Prof pf(c, K_AUTOMORPH, st, 2.0 * n_ct * c->L * c->n);
     const DigitSrc ds = digit_src(c, w);
-    HIPCHK(run_automorph(d, inv_mod_2n(c, g), w.ext, w.dt, c->tb, st, ds.split ? ds.p : nullptr,
-                         ds.stride, ds.split));
-    if (c->alpha > 1) HIPCHK(run_digit_mrc(d, ds.p, ds.stride, c->tb, st));
+    HIPCHK(run_automorph(dims(c, n_ct), inv_mod_2n(c, g), w.ext, w.dt, c->tb, st, ds.p, ds.stride,
+                         ds.split));
   }
+  md.one_e = 1;
   return relin(c, w, n_ct, st, key, md);
+}
+
+// int64 ciphertexts -> w.ext with their rotation digits.
+static int load_rotation(nshe_ctx* c, const Ws& w, const int64_t* in, int n_ct, hipStream_t st) {
+  const size_t W = W_of(c), N = c->n;
+  const Dims d = dims(c, n_ct);
+  HIPCHK(run_i64_to_polys(d, in, 2, w.ext, 2 * W * N, W * N, 2, c->tb, st));
+  HIPCHK(run_rotation_digits(d, w.ext, c->tb, st));
+  return NSHE_OK;
 }
 
 // ct <- ct + rot_g(ct) for the k-th sum element, on the ciphertexts in w.ext;
@@ -1955,9 +1963,7 @@ int nshe_rotate(nshe_ctx* c, const int64_t* in, uint32_t g, int64_t* out, int n_
   hipStream_t st = static_cast<hipStream_t>(stream);
   if ((rc = check_inputs(c, st, {{in, (size_t)n_ct * 2}}))) return rc;
   Ws w = carve(c, ws, n_ct);
-  Dims d = dims(c, n_ct);
-  const size_t W = W_of(c), N = c->n;
-  HIPCHK(run_i64_to_polys(d, in, 2, w.ext, 2 * W * N, W * N, 2, c->tb, st));
+  if ((rc = load_rotation(c, w, in, n_ct, st))) return rc;
   ModDownOut md;
   md.kind = MD_I64;
   md.out = out;
@@ -1983,9 +1989,7 @@ int nshe_sum_slots(nshe_ctx* c, const int64_t* in, int64_t* out, int n_ct, void*
                     [&](int k, int c0, int cnt, void* wsh, hipStream_t s) -> int {
     Ws w = carve(c, wsh, cnt);
     if (k > 0) return sum_step(c, w, cnt, els, keys, k - 1, out + c0 * ctw, s);
-    const size_t W = W_of(c), N = c->n;
-    HIPCHK(run_i64_to_polys(dims(c, cnt), in + c0 * ctw, 2, w.ext, 2 * W * N, W * N, 2, c->tb, s));
-    return NSHE_OK;
+    return load_rotation(c, w, in + c0 * ctw, cnt, s);
   });
 }
 
@@ -2084,6 +2088,7 @@ static int extract_ext(nshe_ctx* c, Ws w, int slot, int n_ct, int bcast, int64_t
   // the running sum is the product, where it is (the rotations use neither
   // operand's area otherwise)
   std::swap(w.ext, w.fx);
+  HIPCHK(run_rotation_digits(dims(c, n_ct), w.ext, c->tb, st));
   for (size_t k = 0; k < els.size(); ++k)
     if ((rc = sum_step(c, w, n_ct, els, keys, k, out, st))) return rc;
   return NSHE_OK;

@@ -269,11 +269,14 @@ hipError_t run_lincomb(const Dims& d, int k, const BabyPtrs& b, const double* co
 hipError_t run_fill_one(const Dims& d, int64_t* out, const Tables& tb, hipStream_t st);
 hipError_t run_diff_i64(const Dims& d, const int64_t* x, const int64_t* y, int y_bcast,
                         int negate, int64_t* out, const Tables& tb, hipStream_t st);
-// rotations: automorphism of ext into dt's key-switching layout (the third
-// component to src, as in run_scale, when src is not null)
+// rotations: the rotation digits of ext's component 1 (into its limbs
+// L..2L-1), and the automorphism of component 0 into dt's and of the digits
+// into the digit source (ciphertext ct at src + ct src_stride; src_split: by
+// coefficient parity, as run_scale)
+hipError_t run_rotation_digits(const Dims& d, double* ext, const Tables& tb, hipStream_t st);
 hipError_t run_automorph(const Dims& d, unsigned ginv, const double* ext, double* dt,
-                         const Tables& tb, hipStream_t st, double* src = nullptr,
-                         size_t src_stride = 0, int src_split = 0);
+                         const Tables& tb, hipStream_t st, double* src, size_t src_stride,
+                         int src_split);
 // alpha primes per digit (alpha > 1): canonical residues of the digit
 // source (limbs 0..L-1 of ciphertext ct at src + ct src_stride, any
 // coefficient order) into each digit's canonical mixed-radix digits, in place

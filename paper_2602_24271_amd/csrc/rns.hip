@@ -661,6 +661,23 @@ __device__ __forceinline__ void special_digits(const double (&a)[A], double (&k)
   }
 }
 
+// Limb m of a group's digits from the canonical residues o (Garner, as the
+// scale-and-round's), in rotation-digit form; v: the group's plain digits so far.
+template <int A>
+__device__ __forceinline__ double rotation_digit(double o, int m, double (&v)[A], const double* inv,
+                                                 int stride, double q, double qinv) {
+  bool low = true;
+#pragma unroll
+  for (int k = 0; k < A; ++k) {
+    if (k >= m) continue;
+    o = mul_bal(o - v[k], cld(inv, k * stride), q, qinv);
+    low = low && v[k] == 0.0;
+  }
+  if (m > 0) o = to_canonical(o, q);
+  v[m] = o;
+  return m > 0 && low ? -1.0 - o : o;
+}
+
 // The mod-down: e_b + (acc_b - [acc_b]_P) P^-1 mod q_i for both components b
 // of each ciphertext (poly = ct * 2 + b), [acc_b]_P the centred residue mod P
 // of the special limbs in mixed-radix digits k_m: per limb, acc_b times
@@ -669,7 +686,8 @@ __device__ __forceinline__ void special_digits(const double (&a)[A], double (&k)
 // 0.9 q_i (operands below 2 q_i: P_k may exceed q_i, all lie below 2^49), so a
 // sum stays below 4.2 q_i.  What becomes of the result z (OUT):
 //   MD_EXT   stored in ext (limbs 0..L-1);
-//   MD_SUM   added to what ext holds there;
+//   MD_SUM   added to what ext holds there, and component 1's rotation digits
+//            (see rotated_digit) stored in its limbs L..2L-1;
 //   MD_LIFT  stored in ext and lifted (limbs L..2L) for the squaring that
 //            follows: the next level of a chain lifts exactly this;
 //   MD_I64   canonical residues in the int64 output, with finish the mask's
@@ -757,7 +775,7 @@ k_moddown(int n, size_t n_poly, const double* __restrict__ acc, const double* __
     if constexpr (I64)
       o64 = (wt.table ? wt.table[(size_t)(*wt.wave) * wt.stride + ct].out + (size_t)b * L * n
                       : out + cb * (size_t)L * n) + c;
-    double o[L], y[L];
+    double o[L], y[L], grp[A];
     double S = 0.0;
     v4i g0[conv_steps(L)], g1[conv_steps(L)];
 #pragma unroll
@@ -785,6 +803,13 @@ k_moddown(int n, size_t n_poly, const double* __restrict__ acc, const double* __
           if (pb.ok) o64[(size_t)i * n] = to_i64(z, q);
         } else {
           buf_store(z, rs, so, i * ls);
+        }
+        if constexpr (OUT == MD_SUM) {
+          const int m = i % A;
+          if (b)
+            buf_store(rotation_digit<A>(to_canonical(z, q), m, grp, tb.mrc_inv + (i - m) * L + i, L,
+                                        q, qinv),
+                      rs, so, (L + i) * ls);
         }
         if constexpr (OUT == MD_LIFT) {
           o[i] = z;
@@ -1080,37 +1105,142 @@ __global__ void __launch_bounds__(256) k_diff_i64(int n, int L, size_t total, co
 
 // ------------------------------------------------------------- rotations ---
 
-// Ring automorphism a(X) -> a(X^g) of the ciphertexts in ext (limbs
-// 0..L-1, balanced) into the key-switching input layout of dt: component 0
-// gets sigma(c0), component 1 zero, component 2 (the digit source) the
-// canonical residues of sigma(c1).  Output coefficient j of sigma(a) is
-// a_i for i = j g^-1 mod 2N when i < N, else -a_{i-N} (since X^N = -1).
-__global__ void __launch_bounds__(256) k_automorph(int n, int L, int n_ct, unsigned ginv,
-                                                   const double* ext, double* dt, Tables tb,
-                                                   double* dsrc, size_t dsrc_stride,
-                                                   int dsrc_split) {
+// A rotation's input: c0 in ext's component 0 (limbs 0..L-1, balanced) and the
+// digits of c1 in ext's component 1, limbs L..2L-1 (rotation digits, below).
+// The automorphism a(X) -> a(X^g) takes output coefficient j from i = j g^-1
+// mod 2N when i < N, else from i - N with its sign changed (X^N = -1).
+//
+// Rotation digits: each digit group's canonical mixed-radix digits v_0, v_1,
+// v_2 of [c1]_{Q_j} (residues when a digit is one prime), v_m stored as -1 - v_m
+// when every lower digit of the group is zero (m > 0).  The digits of the
+// negated coefficient, Q_j - D, then follow digit by digit: the first nonzero
+// one becomes q_m - v_m, those above it q_m - 1 - v_m, those below stay 0.  So the
+// digits are formed once, before the permutation, by the kernel that makes c1
+// (the mod-down of the previous rotation).
+__device__ __forceinline__ double rotated_digit(double x, bool neg, bool lowest, double q) {
+  const bool low = lowest || x < 0.0;      // no nonzero digit below this one
+  const double v = x < 0.0 ? -1.0 - x : x;
+  const double c = low ? (v == 0.0 ? 0.0 : q - v) : q - 1.0 - v;
+  return neg ? c : v;
+}
+
+// The rotation digits of ext's component 1 (residues in limbs 0..L-1), one
+// thread per (ciphertext, digit group, coefficient).
+template <int A>
+__global__ void __launch_bounds__(256) k_rotation_digits(int n, int L, int n_ct, double* ext,
+                                                         Tables tb) {
+  const int groups = L / A;
+  const size_t gid = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (gid >= (size_t)n_ct * groups * n) return;
+  const size_t row = gid / n;               // ct * groups + j
+  const int c = (int)(gid - row * n);
+  const size_t ct = row / groups;
+  const int g = (int)(row - ct * groups) * A;
+  double* d = ext + ((ct * 2 + 1) * (size_t)(2 * L + 1) + g) * n + c;
+  double r[A], v[A];
+#pragma unroll
+  for (int m = 0; m < A; ++m) r[m] = d[(size_t)m * n];
+#pragma unroll
+  for (int m = 0; m < A; ++m) {
+    const int i = g + m;
+    const double q = cld(tb.p, i), qinv = cld(tb.pinv, i);
+    d[(size_t)(L + m) * n] =
+        rotation_digit<A>(to_canonical(r[m], q), m, v, tb.mrc_inv + g * L + i, L, q, qinv);
+  }
+}
+
+// One limb of a rotation: where it comes from and goes to.
+struct RotLimb {
+  const double* src;
+  double* dst;
+  bool digit;      // a digit limb (else c0's, balanced)
+  bool lowest;     // its group's first
+  bool split;      // stored by coefficient parity
+  double q;
+};
+
+__device__ __forceinline__ RotLimb rot_limb(size_t item, int n, int L, int alpha,
+                                            const double* ext, double* dt, double* dsrc,
+                                            size_t dsrc_stride, int split, const Tables& tb) {
+  const size_t W = (size_t)2 * L + 1;
+  const size_t ct = item / (2 * L);
+  const int r = (int)(item - ct * 2 * L), i = r < L ? r : r - L;
+  RotLimb l;
+  l.digit = r >= L;
+  l.src = ext + (l.digit ? (ct * 2 + 1) * W + L + i : ct * 2 * W + i) * n;
+  l.dst = l.digit ? dsrc + ct * dsrc_stride + (size_t)i * n : dt + (ct * 3 * W + i) * n;
+  l.lowest = i % alpha == 0;
+  l.split = l.digit && split;
+  l.q = cld(tb.p, i);
+  return l;
+}
+
+__device__ __forceinline__ double rot_value(const RotLimb& l, double x, bool neg) {
+  return l.digit ? rotated_digit(x, neg, l.lowest, l.q) : (neg ? -x : x);
+}
+
+// The automorphism into the key-switching input layout: sigma(c0) into dt's
+// component 0 (component 1 is zero and not written: the mod-down's one_e), the
+// digits of sigma(c1) into the digit source.  Each value is read where it lies.
+__global__ void __launch_bounds__(256) k_automorph(int n, int L, int alpha, int n_ct,
+                                                   unsigned ginv, const double* ext, double* dt,
+                                                   double* dsrc, size_t dsrc_stride, int split,
+                                                   Tables tb) {
   const size_t gid = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (gid >= (size_t)n_ct * 2 * L * n) return;
-  const size_t row = gid / n;               // (ct * 2 + b) * L + i
-  const int j = (int)(gid - row * n);
-  const int i = (int)(row % L);
-  const size_t cb = row / L;
-  const size_t ct = cb >> 1;
-  const int b = (int)(cb & 1);
-  const size_t W = (size_t)2 * L + 1;
-  const unsigned src = (unsigned)(((unsigned long long)j * ginv) % (2ull * n));
-  const double* a = ext + (cb * W + i) * n;
-  double v = src < (unsigned)n ? a[src] : -a[src - n];
-  double* d = dt + (ct * 3 * W + i) * n + j;
-  if (b == 0) {
-    d[0] = v;
-    d[W * n] = 0.0;
-  } else if (dsrc) {
-    // the digit source's own buffer (see k_scale)
-    const int jp = dsrc_split ? (j & 1) * (n >> 1) + (j >> 1) : j;
-    dsrc[ct * dsrc_stride + (size_t)i * n + jp] = to_canonical(v, cld(tb.p, i));
-  } else {
-    d[2 * W * n] = to_canonical(v, cld(tb.p, i));
+  const size_t item = gid / n;
+  const int j = (int)(gid - item * n);
+  const RotLimb l = rot_limb(item, n, L, alpha, ext, dt, dsrc, dsrc_stride, split, tb);
+  const unsigned s = ((unsigned)j * ginv) & (2u * n - 1u);
+  l.dst[l.split ? (j & 1) * (n >> 1) + (j >> 1) : j] =
+      rot_value(l, l.src[s & (unsigned)(n - 1)], s >= (unsigned)n);
+}
+
+// The same, one workgroup of 1024 threads per limb (N = 1024 E), staged through
+// LDS as two 32-bit halves: the limb is read and written in order, and the
+// permutation's reads, a stride of g^-1 (odd) words apart, meet no bank twice.
+// Reading each value where it lies touches a cache line per value: 220 us for
+// the column's 32 ciphertexts (15 + 3 primes) and 40 more for the digits, which
+// followed the permutation; staged, with the digits formed before, 118 us
+// (0.5 GB, bound by memory traffic).  Used from 90 limbs on: below that too few
+// CUs hold a workgroup.
+template <int E>
+__global__ void __launch_bounds__(1024) k_automorph_lds(int L, int alpha, unsigned ginv,
+                                                        const double* ext, double* dt,
+                                                        double* dsrc, size_t dsrc_stride,
+                                                        int split, Tables tb) {
+  constexpr int n = 1024 * E;
+  __shared__ uint32_t lds[n];
+  const RotLimb l = rot_limb(blockIdx.x, n, L, alpha, ext, dt, dsrc, dsrc_stride, split, tb);
+  const int tid = threadIdx.x;
+  // (opaque per pass: no element's addresses stay in registers between passes)
+  unsigned s0 = (unsigned)tid * ginv;
+  const unsigned step = 1024u * ginv;
+  const auto rs = make_rsrc(l.src, n * 8), rd = make_rsrc(l.dst, n * 8);
+  const unsigned vo = (l.split ? (tid & 1) * (n >> 1) + (tid >> 1) : tid) * 8;
+  const unsigned eo = l.split ? 4096 : 8192;   // bytes between a thread's elements
+  uint32_t lo[E], hi[E];
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const unsigned long long v = __double_as_longlong(buf_load(rs, tid * 8, e * 8192));
+    lo[e] = (uint32_t)v;
+    hi[e] = (uint32_t)(v >> 32);
+  }
+#pragma unroll
+  for (int e = 0; e < E; ++e) lds[e * 1024 + tid] = lo[e];
+  __syncthreads();
+#pragma unroll
+  for (int e = 0; e < E; ++e) lo[e] = lds[(s0 + e * step) & (n - 1)];
+  __syncthreads();
+#pragma unroll
+  for (int e = 0; e < E; ++e) lds[e * 1024 + tid] = hi[e];
+  __syncthreads();
+  asm volatile("" : "+v"(s0));
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const unsigned s = (s0 + e * step) & (2 * n - 1);
+    const unsigned long long v = ((unsigned long long)lds[s & (n - 1)] << 32) | lo[e];
+    buf_store(rot_value(l, __longlong_as_double(v), s >= (unsigned)n), rd, vo, e * eo);
   }
 }
 
@@ -1648,13 +1778,34 @@ hipError_t run_diff_i64(const Dims& d, const int64_t* x, const int64_t* y, int y
   return hipGetLastError();
 }
 
+hipError_t run_rotation_digits(const Dims& d, double* ext, const Tables& tb, hipStream_t st) {
+  if (d.alpha < 1 || d.alpha > 3 || d.L % d.alpha) return hipErrorInvalidValue;
+  const dim3 grid = grid_for((size_t)d.n_ct * (d.L / d.alpha) * d.n);
+  if (d.alpha == 1)
+    hipLaunchKernelGGL(k_rotation_digits<1>, grid, dim3(256), 0, st, d.n, d.L, d.n_ct, ext, tb);
+  else if (d.alpha == 2)
+    hipLaunchKernelGGL(k_rotation_digits<2>, grid, dim3(256), 0, st, d.n, d.L, d.n_ct, ext, tb);
+  else
+    hipLaunchKernelGGL(k_rotation_digits<3>, grid, dim3(256), 0, st, d.n, d.L, d.n_ct, ext, tb);
+  return hipGetLastError();
+}
+
 hipError_t run_automorph(const Dims& d, unsigned ginv, const double* ext, double* dt,
                          const Tables& tb, hipStream_t st, double* src, size_t src_stride,
                          int src_split) {
-  if (src_split && !src) return hipErrorInvalidValue;
-  const size_t total = (size_t)d.n_ct * 2 * d.L * d.n;
-  hipLaunchKernelGGL(k_automorph, grid_for(total), dim3(256), 0, st, d.n, d.L, d.n_ct, ginv, ext,
-                     dt, tb, src, src_stride, src_split);
+  const size_t items = (size_t)d.n_ct * 2 * d.L;
+  const dim3 grid((unsigned)items);
+#define C_(E_)                                                                                  \
+  case 1024 * E_:                                                                               \
+    hipLaunchKernelGGL(k_automorph_lds<E_>, grid, dim3(1024), 0, st, d.L, d.alpha, ginv, ext, dt, \
+                       src, src_stride, src_split, tb);                                         \
+    return hipGetLastError();
+  if (items >= 90) {
+    switch (d.n) { C_(1) C_(2) C_(4) C_(8) C_(16) C_(32) }
+  }
+#undef C_
+  hipLaunchKernelGGL(k_automorph, grid_for(items * d.n), dim3(256), 0, st, d.n, d.L, d.alpha,
+                     d.n_ct, ginv, ext, dt, src, src_stride, src_split, tb);
   return hipGetLastError();
 }
 
