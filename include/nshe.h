@@ -391,6 +391,11 @@ int nshe_mul_plain(nshe_ctx* ctx, const int64_t* in_dev, const int64_t* pt_dev,
 int nshe_extract(nshe_ctx* ctx, const int64_t* in_dev, int slot, int broadcast,
                  int64_t* out_dev, int n_ct, void* ws_dev, size_t ws_bytes, void* stream);
 size_t nshe_join_workspace_bytes(const nshe_ctx* ctx, int n_ct);
+/* A larger workspace for the same join: with it several of its n_rows rows
+ * run together, up to 32 ciphertexts per pass, the same integers.  Any size
+ * from nshe_join_workspace_bytes on is accepted and used as far as it
+ * reaches. */
+size_t nshe_join_workspace_wide_bytes(const nshe_ctx* ctx, int n_ct, int n_rows);
 int nshe_join_sum(nshe_ctx* ctx, const int64_t* a_key_dev, const int64_t* b_key_dev,
                   const int64_t* b_attr_dev, const int32_t* rows_host, int n_rows,
                   int64_t* out_dev, int n_ct, void* ws_dev, size_t ws_bytes, void* stream);

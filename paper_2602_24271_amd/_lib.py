@@ -111,6 +111,7 @@ SIGNATURES = {
     "nshe_mul_plain": (_I, [_P, _P, _P, _P, _I, _P, _SZ, _P]),
     "nshe_extract": (_I, [_P, _P, _I, _I, _P, _I, _P, _SZ, _P]),
     "nshe_join_workspace_bytes": (_SZ, [_P, _I]),
+    "nshe_join_workspace_wide_bytes": (_SZ, [_P, _I, _I]),
     "nshe_join_sum": (_I, [_P, _P, _P, _P, ctypes.POINTER(ctypes.c_int32), _I, _P, _I, _P, _SZ,
                            _P]),
     "nshe_set_galois_key": (_I, [_P, ctypes.c_uint32, _P, _SZ, _P]),

@@ -108,6 +108,13 @@ class Context:
             self._ws = torch.empty(need, dtype=torch.uint8, device=self.device)
         return self._ws
 
+    def _workspace_wide(self, want: int, need: int) -> torch.Tensor:
+        """`want` bytes, or the call's smallest workspace where they don't fit."""
+        try:
+            return self._workspace_bytes(want)
+        except torch.OutOfMemoryError:
+            return self._workspace_bytes(need)
+
     def _check_ct(self, x: torch.Tensor, comps: int = 2) -> int:
         if x.dtype != torch.int64 or x.device != self.device or not x.is_contiguous():
             raise ValueError("ciphertexts must be contiguous int64 tensors on the context device")
@@ -227,12 +234,9 @@ class Context:
         need = int(self._lib.nshe_compare_workspace_bytes(self._h, n))
         if need == 0:
             raise ValueError("comparisons need t = 2^K + 1 prime")
-        try:
-            # room for batches of the program's products
-            return self._workspace_bytes(
-                int(self._lib.nshe_compare_workspace_wide_bytes(self._h, n)))
-        except torch.OutOfMemoryError:
-            return self._workspace_bytes(need)
+        # (the wide one: room for batches of the program's products)
+        return self._workspace_wide(int(self._lib.nshe_compare_workspace_wide_bytes(self._h, n)),
+                                    need)
 
     def compare(self, x: torch.Tensor, y: torch.Tensor, op: str = "lt") -> torch.Tensor:
         """[x < y] (op "lt") or [x <= y] (op "le") for |x - y| <= (t-1)/2
@@ -296,7 +300,9 @@ class Context:
         d = self._depth_after("join", a_key, b_key, b_attr)
         arr = (ctypes.c_int32 * max(1, len(rows)))(*rows)
         out = torch.empty_like(a_key)
-        ws = self._workspace_bytes(int(self._lib.nshe_join_workspace_bytes(self._h, n)))
+        ws = self._workspace_wide(
+            int(self._lib.nshe_join_workspace_wide_bytes(self._h, n, len(rows))),
+            int(self._lib.nshe_join_workspace_bytes(self._h, n)))
         _lib.check(self._lib.nshe_join_sum(self._h, _ptr(a_key), _ptr(b_key), _ptr(b_attr), arr,
                                            len(rows), _ptr(out), n, _ptr(ws), ws.numel(),
                                            _stream()))

@@ -1995,42 +1995,42 @@ int nshe_sum_slots(nshe_ctx* c, const int64_t* in, int64_t* out, int n_ct, void*
 
 // ------------------------------------------------------ plaintext products
 
-// ct (in w.ext, data limbs) times the plaintext pt (int64 [N] in [0, t)) into
-// w.fx's data limbs: forward transforms of ct and of the plaintext's limbs
-// (times N^-1, in w.dt), pointwise products, inverse transform.
-static int mul_plain_ext(nshe_ctx* c, const Ws& w, const int64_t* pt, int n_ct, hipStream_t st) {
-  Dims d = dims(c, n_ct);
-  const size_t W = W_of(c), N = c->n;
-  HIPCHK(run_plain_limbs(d, (int64_t)c->t, pt, w.dt, c->tb, st));
+// The transform (dir 0) of npoly polynomials' data limbs, W limbs apart, from
+// base into out, or their inverse in place (dir 1).
+static int ntt_job_data(nshe_ctx* c, double* base, double* out, int npoly, int dir,
+                        hipStream_t st) {
   NttJob j{};
   j.split = c->tune.split_forward;
-  j.base = w.dt;
-  j.out = w.dt + W * N;
-  j.poly_stride = W * N;
-  j.npoly = 1;
+  j.base = base;
+  j.out = out;
+  j.poly_stride = (size_t)W_of(c) * c->n;
+  j.npoly = npoly;
   j.nlimb = c->L;
   j.limb_prime = c->lp_ext;
-  j.count = c->L;
-  {
-    Prof pf(c, K_NTT_FWD, st, ntt_work(c, j.count));
-    HIPCHK(run_ntt(c->log2n, j, c->tb, 0, st));
-  }
-  j.base = w.ext;
-  j.out = w.fx;
-  j.npoly = 2 * n_ct;
-  j.count = j.npoly * c->L;
-  {
-    Prof pf(c, K_NTT_FWD, st, ntt_work(c, j.count));
-    HIPCHK(run_ntt(c->log2n, j, c->tb, 0, st));
-  }
-  HIPCHK(run_pointwise_plain(d, w.fx, w.dt + W * N, c->tb, st));
-  j.base = w.fx;
-  j.out = nullptr;
-  {
-    Prof pf(c, K_NTT_INV, st, ntt_work(c, j.count));
-    HIPCHK(run_ntt(c->log2n, j, c->tb, 1, st));
-  }
+  j.count = npoly * c->L;
+  Prof pf(c, dir ? K_NTT_INV : K_NTT_FWD, st, ntt_work(c, j.count));
+  HIPCHK(run_ntt(c->log2n, j, c->tb, dir, st));
   return NSHE_OK;
+}
+
+// The transformed ciphertexts fx times the plaintext pt (int64 [N] in [0, t))
+// into out (may be fx), still transformed: the plaintext's limbs (times N^-1)
+// and their transform pass through tmp (2 W limbs).
+static int mul_plain_ntt(nshe_ctx* c, const double* fx, double* out, const int64_t* pt,
+                         double* tmp, int n_ct, hipStream_t st) {
+  Dims d = dims(c, n_ct);
+  double* ptf = tmp + (size_t)W_of(c) * c->n;
+  HIPCHK(run_plain_limbs(d, (int64_t)c->t, pt, tmp, c->tb, st));
+  if (int rc = ntt_job_data(c, tmp, ptf, 1, 0, st)) return rc;
+  HIPCHK(run_pointwise_plain(d, fx, out, ptf, c->tb, st));
+  return NSHE_OK;
+}
+
+// ct (in w.ext, data limbs) times the plaintext pt into w.fx's data limbs.
+static int mul_plain_ext(nshe_ctx* c, const Ws& w, const int64_t* pt, int n_ct, hipStream_t st) {
+  int rc = ntt_job_data(c, w.ext, w.fx, 2 * n_ct, 0, st);
+  if (!rc) rc = mul_plain_ntt(c, w.fx, w.fx, pt, w.dt, n_ct, st);
+  return rc ? rc : ntt_job_data(c, w.fx, nullptr, 2 * n_ct, 1, st);
 }
 
 // The basis plaintext of `slot` (slot order of the 2 x N/2 layout) into out.
@@ -2038,8 +2038,7 @@ static int basis_plain(nshe_ctx* c, int slot, int64_t* out, hipStream_t st) {
   const u64 t = c->t, two_n = 2ull * c->n;
   const u64 psi = powmod(primitive_root(t), (t - 1) / two_n, t);
   const int half = c->n / 2;
-  u64 e = 1;
-  for (int s = 0; s < slot % half; ++s) e = e * 3 % two_n;
+  u64 e = powmod(3, (u64)(slot % half), two_n);
   if (slot >= half) e = two_n - e;
   const u64 zinv = powmod(psi, two_n - e, t);   // psi^-e
   HIPCHK(run_basis_plain(c->n, t, zinv, invmod((u64)c->n % t, t), out, st));
@@ -2126,6 +2125,58 @@ size_t nshe_join_workspace_bytes(const nshe_ctx* c, int n_ct) {
   return 3 * ct_bytes(c, n_ct) + 2 * ct_bytes(c, 1) + ws_doubles(c, std::max(n_ct, 1)) * sizeof(double);
 }
 
+// Workspace of a join whose reference rows run g at a time: masks, terms and
+// replicated attributes of g n_ct ciphertexts, g pairs of broadcasts, and the
+// area of the broadcasts (2 g ciphertexts) or the masks and products.
+static size_t join_group_bytes(const nshe_ctx* c, int n_ct, int g) {
+  return 3 * ct_bytes(c, g * n_ct) + ct_bytes(c, 2 * g) +
+         std::max(ws_doubles(c, 2 * g) * sizeof(double),
+                  g == 1 ? ws_doubles(c, n_ct) * sizeof(double)
+                         : batched_ws_bytes(c, g * n_ct, g * n_ct));
+}
+
+// Rows at a time for up to JOIN_GROUP_CT ciphertexts per pass.
+constexpr int JOIN_GROUP_CT = 32;
+static int join_group(int n_ct, int n_rows) {
+  return std::max(1, std::min(n_rows, JOIN_GROUP_CT / std::max(2, n_ct)));
+}
+
+size_t nshe_join_workspace_wide_bytes(const nshe_ctx* c, int n_ct, int n_rows) {
+  const size_t base = nshe_join_workspace_bytes(c, n_ct);
+  if (base == 0 || n_ct < 1 || n_rows < 1) return base;
+  return std::max(base, join_group_bytes(c, n_ct, join_group(n_ct, n_rows)));
+}
+
+// Broadcast of slot rows[r] of two ciphertexts (a, b) into out's ciphertexts 2r
+// and 2r + 1, r < g: one transform of the pair, a plaintext product per row, and
+// the rotate-and-add of all 2 g products together.  ws holds 2 g ciphertexts.
+static int broadcast_pairs(nshe_ctx* c, const int64_t* a, const int64_t* b, const int32_t* rows,
+                           int g, int64_t* out, void* ws, hipStream_t st) {
+  std::vector<uint32_t> els;
+  std::vector<const double*> keys;
+  int rc = sum_keys(c, &els, &keys);
+  if (rc) return rc;
+  Ws w = carve(c, ws, 2 * g);
+  const size_t W = W_of(c), N = c->n;
+  const int64_t* in[2] = {a, b};
+  for (int k = 0; k < 2; ++k)
+    HIPCHK(run_i64_to_polys(dims(c, 1), in[k], 2, w.ext + k * 2 * W * N, 2 * W * N, W * N, 2, c->tb,
+                            st));
+  if ((rc = ntt_job_data(c, w.ext, w.dig, 4, 0, st))) return rc;
+  int64_t* pt = reinterpret_cast<int64_t*>(w.acc);
+  for (int r = 0; r < g && !rc; ++r) {
+    rc = basis_plain(c, rows[r], pt, st);
+    if (!rc) rc = mul_plain_ntt(c, w.dig, w.fx + (size_t)r * 4 * W * N, pt, w.dt, 2, st);
+  }
+  if (!rc) rc = ntt_job_data(c, w.fx, nullptr, 4 * g, 1, st);
+  if (rc) return rc;
+  std::swap(w.ext, w.fx);
+  HIPCHK(run_rotation_digits(dims(c, 2 * g), w.ext, c->tb, st));
+  for (size_t k = 0; k < els.size(); ++k)
+    if ((rc = sum_step(c, w, 2 * g, els, keys, k, out, st))) return rc;
+  return NSHE_OK;
+}
+
 int nshe_join_sum(nshe_ctx* c, const int64_t* a_key, const int64_t* b_key, const int64_t* b_attr,
                   const int32_t* rows, int n_rows, int64_t* out, int n_ct, void* ws,
                   size_t ws_bytes, void* stream) {
@@ -2157,27 +2208,51 @@ int nshe_join_sum(nshe_ctx* c, const int64_t* a_key, const int64_t* b_key, const
   if (int rc0 = check_inputs(c, st, {{a_key, (size_t)n_ct * 2}, {b_key, 2}, {b_attr, 2}}))
     return rc0;
   if (n_rows == 0) return nshe_sum(c, nullptr, 0, out, n_ct, stream);
-  const size_t cb = ct_bytes(c, n_ct), cb1 = ct_bytes(c, 1);
+  const size_t ctw = (size_t)2 * c->L * c->n;
   char* p = static_cast<char*>(ws);
+  Dims d = dims(c, n_ct);
+  // as many rows at a time as the workspace holds; too small for one such
+  // group (a single ciphertext in the smallest workspace), the broadcasts run
+  // one by one.  (Padded ciphertext arrays: one row, its pair apart.)
+  int group = join_group(n_ct, n_rows);
+  while (group > 0 && join_group_bytes(c, n_ct, group) > ws_bytes) --group;
+  if (ct_bytes(c, 1) != ctw * sizeof(int64_t)) group = 0;
+  const int g0 = std::max(group, 1);
+  const size_t cb = ct_bytes(c, g0 * n_ct);
   int64_t* mask = reinterpret_cast<int64_t*>(p);
   int64_t* term = reinterpret_cast<int64_t*>(p + cb);
   int64_t* rep = reinterpret_cast<int64_t*>(p + 2 * cb);
-  int64_t* bk = reinterpret_cast<int64_t*>(p + 3 * cb);
-  int64_t* ba = reinterpret_cast<int64_t*>(p + 3 * cb + cb1);
-  void* mws = p + 3 * cb + 2 * cb1;
-  const size_t mws_bytes = ws_bytes - (3 * cb + 2 * cb1);
-  const size_t ctw = (size_t)2 * c->L * c->n;
-  Dims d = dims(c, n_ct);
-  for (int r = 0; r < n_rows; ++r) {
-    int rc = nshe_extract(c, b_key, rows[r], 1, bk, 1, mws, mws_bytes, stream);
-    if (!rc) rc = nshe_extract(c, b_attr, rows[r], 1, ba, 1, mws, mws_bytes, stream);
-    if (!rc) rc = nshe_eq_mask(c, a_key, bk, mask, n_ct, 1, mws, mws_bytes, stream);
+  int64_t* bc = reinterpret_cast<int64_t*>(p + 3 * cb);   // pairs: the row's key, its attribute
+  const size_t pair = ct_bytes(c, 1) / sizeof(int64_t);
+  const size_t used = 3 * cb + (group ? ct_bytes(c, 2 * g0) : 2 * ct_bytes(c, 1));
+  void* mws = p + used;
+  const size_t mws_bytes = ws_bytes - used;
+  for (int r0 = 0; r0 < n_rows; r0 += g0) {
+    const int g = std::min(g0, n_rows - r0);
+    int rc = NSHE_OK;
+    if (group) {
+      rc = broadcast_pairs(c, b_key, b_attr, rows + r0, g, bc, mws, st);
+    } else {
+      rc = nshe_extract(c, b_key, rows[r0], 1, bc, 1, mws, mws_bytes, stream);
+      if (!rc) rc = nshe_extract(c, b_attr, rows[r0], 1, bc + pair, 1, mws, mws_bytes, stream);
+    }
+    if (!rc && g == 1) {
+      rc = nshe_eq_mask(c, a_key, bc, mask, n_ct, 1, mws, mws_bytes, stream);
+    } else if (!rc) {
+      std::vector<nshe_item> items((size_t)g);
+      for (int r = 0; r < g; ++r)
+        items[r] = nshe_item{a_key, bc + 2 * r * pair, mask + (size_t)r * n_ct * ctw, n_ct, 1};
+      rc = nshe_eq_mask_batched(c, items.data(), g, g * n_ct, 0, mws, mws_bytes, stream);
+    }
     if (rc) return rc;
-    for (int k = 0; k < n_ct; ++k)
-      HIPCHK(hipMemcpyAsync(rep + k * ctw, ba, ctw * sizeof(int64_t), hipMemcpyDeviceToDevice, st));
-    rc = nshe_mul_relin(c, mask, rep, r == 0 ? out : term, n_ct, mws, mws_bytes, stream);
+    for (int k = 0; k < g * n_ct; ++k)
+      HIPCHK(hipMemcpyAsync(rep + k * ctw, bc + (2 * (k / n_ct) + 1) * pair, ctw * sizeof(int64_t),
+                            hipMemcpyDeviceToDevice, st));
+    rc = nshe_mul_relin(c, mask, rep, term, g * n_ct, mws, mws_bytes, stream);
     if (rc) return rc;
-    if (r > 0) HIPCHK(run_sum_i64(d, out, term, 0, 1, out, c->tb, st));
+    const size_t words = (size_t)n_ct * ctw;
+    HIPCHK(run_sum_i64(d, r0 ? out : term, r0 ? term : term + words, words, r0 ? g : g - 1, out,
+                       c->tb, st));
   }
   return NSHE_OK;
 }

@@ -252,8 +252,8 @@ hipError_t run_basis_plain(int n, uint64_t t, uint64_t zinv, uint64_t ninv_t, in
                            hipStream_t st);
 hipError_t run_plain_limbs(const Dims& d, int64_t t, const int64_t* pt, double* out,
                            const Tables& tb, hipStream_t st);
-hipError_t run_pointwise_plain(const Dims& d, double* fx, const double* pt, const Tables& tb,
-                               hipStream_t st);
+hipError_t run_pointwise_plain(const Dims& d, const double* fx, double* out, const double* pt,
+                               const Tables& tb, hipStream_t st);
 // comparisons: scalar linear combinations of up to 256 ciphertext arrays
 // (J <= 16 outputs, coefficient rows [J][k]), the trivial encryption of 1,
 // and differences with optional broadcast and sign

@@ -962,9 +962,11 @@ __global__ void __launch_bounds__(256) k_plain_limbs(int n, int L, int64_t t, co
   out[gid] = mul_bal(x, cld(tb.ninv, i), cld(tb.p, i), cld(tb.pinv, i));
 }
 
-// fx[ct][b][i] *= pt[i] (NTT domain, data limbs of [ct][2][W][N]).
-__global__ void __launch_bounds__(256) k_pointwise_plain(int n, int L, int n_ct, double* fx,
-                                                         const double* pt, Tables tb) {
+// out[ct][b][i] = fx[ct][b][i] pt[i] (NTT domain, data limbs of [ct][2][W][N];
+// out may be fx).
+__global__ void __launch_bounds__(256) k_pointwise_plain(int n, int L, int n_ct, const double* fx,
+                                                         double* out, const double* pt,
+                                                         Tables tb) {
   const size_t gid = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (gid >= (size_t)n_ct * 2 * L * n) return;
   const size_t row = gid / n;
@@ -972,7 +974,7 @@ __global__ void __launch_bounds__(256) k_pointwise_plain(int n, int L, int n_ct,
   const int i = (int)(row % L);
   const size_t cb = row / L;
   const size_t off = (cb * (2 * L + 1) + i) * n + c;
-  fx[off] = mul_bal(fx[off], pt[(size_t)i * n + c], cld(tb.p, i), cld(tb.pinv, i));
+  out[off] = mul_bal(fx[off], pt[(size_t)i * n + c], cld(tb.p, i), cld(tb.pinv, i));
 }
 
 // ----------------------------------------------------------- comparisons ---
@@ -1730,11 +1732,11 @@ hipError_t run_plain_limbs(const Dims& d, int64_t t, const int64_t* pt, double* 
   return hipGetLastError();
 }
 
-hipError_t run_pointwise_plain(const Dims& d, double* fx, const double* pt, const Tables& tb,
-                               hipStream_t st) {
+hipError_t run_pointwise_plain(const Dims& d, const double* fx, double* out, const double* pt,
+                               const Tables& tb, hipStream_t st) {
   const size_t total = (size_t)d.n_ct * 2 * d.L * d.n;
-  hipLaunchKernelGGL(k_pointwise_plain, grid_for(total), dim3(256), 0, st, d.n, d.L, d.n_ct, fx, pt,
-                     tb);
+  hipLaunchKernelGGL(k_pointwise_plain, grid_for(total), dim3(256), 0, st, d.n, d.L, d.n_ct, fx, out,
+                     pt, tb);
   return hipGetLastError();
 }
 
