@@ -203,6 +203,8 @@ struct nshe_ctx {
   int lt_K = 0, lt_k = 0, lt_m = 0, lt_top = 0;
   int lt_depth = 0;  // multiplicative depth of the comparison program
   const double* lt_coef = nullptr;  // (exact small integers)
+  bool lt_mx = false;               // lt_coef's matrix in the matrix kernel's form
+  const double* lt_top_coef = nullptr;
   // noise budget (see budget_of): multiplications a fresh ciphertext takes
   int depth_budget = 0;
   double fresh_bits = 0.0, level_bits = 0.0;
@@ -1146,6 +1148,8 @@ int nshe_ctx_create(const nshe_params* pr, int hip_device, nshe_ctx** out) {
       for (int i = 0; i < c->lt_k; ++i)
         lt_coef[(size_t)j * c->lt_k + i] = centred_small(cp[2 * ((size_t)j * c->lt_k + i) + 1], c->t);
     c->lt_top = centred_small(cp[c->t - 1], c->t);
+    c->lt_mx = lincomb_mx_fits(dims(c, 1), c->lt_k, c->lt_m, lt_coef);
+    if (c->lt_mx) lt_coef = lincomb_mx_table(lt_coef);
     lt_coef.push_back(c->lt_top);  // the z^(p-1) coefficient, after the matrix
     c->lt_depth = lt_program_depth(c->lt_K, c->lt_k, c->lt_m);
   }
@@ -1200,6 +1204,7 @@ int nshe_ctx_create(const nshe_params* pr, int hip_device, nshe_ctx** out) {
     e = hipMemcpy(c->lp_ext, lp.data(), lp.size() * sizeof(int), hipMemcpyHostToDevice);
   if (!lt_coef.empty()) {
     c->lt_coef = reinterpret_cast<const double*>(base + off_lt);
+    c->lt_top_coef = c->lt_coef + lt_coef.size() - 1;
     if (e == hipSuccess)
       e = hipMemcpy(base + off_lt, lt_coef.data(), lt_coef.size() * sizeof(double),
                     hipMemcpyHostToDevice);
@@ -2267,9 +2272,13 @@ static int ilog2(int x) {
 
 // Ciphertext-array slots of the comparison workspace (then the multiply
 // workspace): chain levels 1..K (slot 0 unused), babies, giants, 16
-// linear combinations, the core's g, T, S, and the callers' z, LT, and two
+// linear combinations (none in the matrix form, which writes them over the
+// babies), the core's g, T, S, and the callers' z, LT, and two
 // comparison results (the last four).
-static int cmp_slots(const nshe_ctx* c) { return c->lt_K + 1 + c->lt_k + c->lt_m + 16 + 3 + 4; }
+static int lt_sums(const nshe_ctx* c) { return c->lt_mx ? 0 : 16; }
+static int cmp_slots(const nshe_ctx* c) {
+  return c->lt_K + 1 + c->lt_k + c->lt_m + lt_sums(c) + 3 + 4;
+}
 
 // one operand's transform, [n_ct][2][W][N] doubles
 static size_t fx_bytes(const nshe_ctx* c, int n_ct) {
@@ -2342,7 +2351,7 @@ static int lt_core(nshe_ctx* c, const int64_t* z, int64_t* out, int n_ct, const 
                    int* one_slot, hipStream_t st) {
   const int K = c->lt_K, k = c->lt_k, m = c->lt_m;
   void* stv = st;
-  const int s_lev = 0, s_bab = K + 1, s_gi = s_bab + k, s_G = s_gi + m, s_g = s_G + 16,
+  const int s_lev = 0, s_bab = K + 1, s_gi = s_bab + k, s_g = s_gi + m + lt_sums(c),
             s_T = s_g + 1, s_S = s_g + 2;
   Dims d = dims(c, n_ct);
   std::vector<const int64_t*> lev(K + 1);
@@ -2375,16 +2384,21 @@ static int lt_core(nshe_ctx* c, const int64_t* z, int64_t* out, int n_ct, const 
                       st);
     if (rc) return rc;
   }
-  // g = G_0 + sum_{j>=1} G_j W_j, G_j = sum_i c_(2(jk+i)+1) B_i in chunks of
-  // 16.  The products' tensors are summed in the extended basis (exact: Q B
+  // g = G_0 + sum_{j>=1} G_j W_j, G_j = sum_i c_(2(jk+i)+1) B_i: all of them
+  // over the babies 1..m (m < k; baby 0 is the callers') by the matrix form, in
+  // chunks of 16 otherwise.  The products' tensors are summed in the extended basis (exact: Q B
   // exceeds m N Q^2), then scaled, rounded and relinearized once.
   int64_t* g = a.slot(s_g);
   Ws w = carve(c, a.mws, n_ct);
-  for (int j0 = 0; j0 < m; j0 += 16) {
-    const int J = std::min(16, m - j0);
+  const int chunk = c->lt_mx ? m : 16, s_G = c->lt_mx ? s_bab + 1 : s_gi + m;
+  for (int j0 = 0; j0 < m; j0 += chunk) {
+    const int J = std::min(chunk, m - j0);
     {
       Prof pf(c, K_LINCOMB, st, (double)J * k * n_ct * 2 * c->L * c->n);
-      HIPCHK(run_lincomb(d, k, bp, c->lt_coef + (size_t)j0 * k, J, a.slot(s_G), a.U, c->tb, st));
+      if (c->lt_mx)
+        HIPCHK(run_lincomb_mx(d, a.slot(s_bab), a.U, c->lt_coef, a.slot(s_G), a.U, c->tb, st));
+      else
+        HIPCHK(run_lincomb(d, k, bp, c->lt_coef + (size_t)j0 * k, J, a.slot(s_G), a.U, c->tb, st));
     }
     if (j0 == 0) HIPCHK(run_sum_i64(d, a.slot(s_G), nullptr, 0, 0, g, c->tb, st));
     for (int jj = j0 == 0 ? 1 : 0; jj < J; jj += a.batch) {
@@ -2426,7 +2440,7 @@ static int lt_core(nshe_ctx* c, const int64_t* z, int64_t* out, int n_ct, const 
   top.p[0] = lev[K];
   {
     Prof pf(c, K_LINCOMB, st, (double)n_ct * 2 * c->L * c->n);
-    HIPCHK(run_lincomb(d, 1, top, c->lt_coef + (size_t)m * k, 1, a.slot(s_S), a.U, c->tb, st));
+    HIPCHK(run_lincomb(d, 1, top, c->lt_top_coef, 1, a.slot(s_S), a.U, c->tb, st));
   }
   HIPCHK(run_sum_i64(d, a.slot(s_S), a.slot(s_T), 0, 1, out, c->tb, st));
   *one_slot = s_bab;

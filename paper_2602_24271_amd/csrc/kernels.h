@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 #include <cstddef>
 #include <cstdint>
+#include <vector>
 
 #include "modarith.h"
 
@@ -266,6 +267,14 @@ hipError_t run_tensor_mac(const Dims& d, int k, const double* fa, const double* 
                           int first, const Tables& tb, hipStream_t st);
 hipError_t run_lincomb(const Dims& d, int k, const BabyPtrs& b, const double* coef, int J,
                        int64_t* out, size_t out_stride, const Tables& tb, hipStream_t st);
+// The matrix form: LINCOMB_K inputs in_stride apart to LINCOMB_J outputs
+// out_stride apart (outputs may lie on inputs).  _fits: rings and coefficients
+// (row-major, J x K) it takes; _table: their constants.
+constexpr int LINCOMB_K = 256, LINCOMB_J = 128, LINCOMB_BIAS = 127;
+bool lincomb_mx_fits(const Dims& d, int k, int J, const std::vector<double>& c);
+std::vector<double> lincomb_mx_table(const std::vector<double>& c);
+hipError_t run_lincomb_mx(const Dims& d, const int64_t* in, size_t in_stride, const double* tab,
+                          int64_t* out, size_t out_stride, const Tables& tb, hipStream_t st);
 hipError_t run_fill_one(const Dims& d, int64_t* out, const Tables& tb, hipStream_t st);
 hipError_t run_diff_i64(const Dims& d, const int64_t* x, const int64_t* y, int y_bcast,
                         int negate, int64_t* out, const Tables& tb, hipStream_t st);

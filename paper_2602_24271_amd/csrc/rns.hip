@@ -1025,8 +1025,10 @@ __global__ void __launch_bounds__(256) k_tensor_mac(int n, int W, size_t total, 
 // take as they are, with no conversion per use.  Each input v (balanced, |v| <= 2^48) is
 // split once as v = vh 2^24 + vl (split24), so that every product is an
 // exact FMA (|vh c| <= 2^39): two exact sums per output over k <= 256
-// terms (below 2^47), combined once as Wh [2^24]_q + Wl.  JT: J fixed at
-// compile time (16 or 1), or 0 for any J (a branch per output and term).
+// terms (below 2^47), combined once as Wh [2^24]_q + Wl.  For the small
+// plaintext primes' matrices (at most 16 x 16 would fill one pass) and the
+// single top term; JT: J fixed at compile time (1), or 0 for any J (a branch
+// per output and term).
 template <int JT>
 __global__ void __launch_bounds__(256) k_lincomb(int n, int L, size_t per, int k, BabyPtrs b,
                                                  const double* coef, int Jr, int64_t* out,
@@ -1036,9 +1038,10 @@ __global__ void __launch_bounds__(256) k_lincomb(int n, int L, size_t per, int k
   if (gid >= per) return;
   const int i = (int)((gid / n) % L);
   const double p = cld(tb.p, i), pinv = cld(tb.pinv, i);
-  double ah[16], al[16];
+  constexpr int JA = JT ? JT : 16;
+  double ah[JA], al[JA];
 #pragma unroll
-  for (int jj = 0; jj < 16; ++jj) ah[jj] = al[jj] = 0.0;
+  for (int jj = 0; jj < JA; ++jj) ah[jj] = al[jj] = 0.0;
   // babies in groups of G whose loads are all issued before their products
   // (one load per term would leave the loop waiting on memory latency)
   constexpr int G = 4;
@@ -1048,7 +1051,7 @@ __global__ void __launch_bounds__(256) k_lincomb(int n, int L, size_t per, int k
 #pragma unroll
     for (int u = 0; u < G; ++u) split24(from_u64(b.p[t + u][gid], p), vh[u], vl[u]);
 #pragma unroll
-    for (int jj = 0; jj < 16; ++jj) {
+    for (int jj = 0; jj < JA; ++jj) {
       if (jj < J) {
 #pragma unroll
         for (int u = 0; u < G; ++u) {
@@ -1063,7 +1066,7 @@ __global__ void __launch_bounds__(256) k_lincomb(int n, int L, size_t per, int k
     double vh, vl;
     split24(from_u64(b.p[t][gid], p), vh, vl);
 #pragma unroll
-    for (int jj = 0; jj < 16; ++jj) {
+    for (int jj = 0; jj < JA; ++jj) {
       if (jj < J) {
         const double c = cld(coef, jj * k + t);
         ah[jj] = __builtin_fma(vh, c, ah[jj]);
@@ -1073,10 +1076,126 @@ __global__ void __launch_bounds__(256) k_lincomb(int n, int L, size_t per, int k
   }
   const double t24 = cld(tb.two24, i);
 #pragma unroll
-  for (int jj = 0; jj < 16; ++jj)
+  for (int jj = 0; jj < JA; ++jj)
     if (jj < J)
       out[(size_t)jj * out_stride + gid] =
           to_i64(reduce_bal(mul_lazy(ah[jj], t24, p, pinv) + al[jj], p, pinv), p);
+}
+
+// Four values' words -> their bytes 0..3, one word per byte position.
+__device__ __forceinline__ void bytes_across(const unsigned (&w)[4], int (&o)[4]) {
+  const unsigned a = __builtin_amdgcn_perm(w[1], w[0], 0x05010400u);   // b0 b0' b1 b1'
+  const unsigned b = __builtin_amdgcn_perm(w[1], w[0], 0x07030602u);   // b2 b2' b3 b3'
+  const unsigned c = __builtin_amdgcn_perm(w[3], w[2], 0x05010400u);
+  const unsigned e = __builtin_amdgcn_perm(w[3], w[2], 0x07030602u);
+  o[0] = (int)__builtin_amdgcn_perm(c, a, 0x05040100u);
+  o[1] = (int)__builtin_amdgcn_perm(c, a, 0x07060302u);
+  o[2] = (int)__builtin_amdgcn_perm(e, b, 0x05040100u);
+  o[3] = (int)__builtin_amdgcn_perm(e, b, 0x07060302u);
+}
+
+// The same combinations of 256 inputs to 128 outputs, all outputs
+// of 32 residues in one block, on the integer matrix cores.  A canonical value
+// v < 2^49 is seven signed bytes (v + 0x808080808080, bytes 0..5 XOR 0x80; byte
+// 6 is at most 2), and a coefficient's c - LC_BIAS (in [-32895, 32639] for -32768 <= c <= 32766,
+// which the host checks) exactly two.  v_mfma_i32_32x32x32_i8 sums every
+// byte product of equal weight 2^(8s), s < 8, in 32 bits (|A_s| <= 2 256 2^14 =
+// 2^23), and
+//   sum_t c_t v_t = sum_s 2^(8s) A_s + LC_BIAS sum_t v_t
+// is exact in two doubles (below 2^41 and 2^49) whose high one times 2^24 is
+// reduced by one exact FMA.
+// out[j * out_stride + r] may lie on the inputs: a block has read all the
+// values of its residues before it writes any.
+// Bound by HBM (256 values in and 128 out per residue): four waves hold 32
+// residues' bytes in LDS (56 KB, two blocks to a compute unit), each wave loads
+// 64 inputs at once and forms all eight weights of 32 outputs, so one pass
+// reads each input once.  2 ciphertexts of N = 2^15, L = 15 (6.0 GB): 1.57 ms,
+// 3.8 TB/s; eight passes of 16 outputs on the FP64 VALU took 7.0 ms.
+constexpr int LC_K = LINCOMB_K, LC_RES = 32, LC_BIAS = LINCOMB_BIAS;
+__global__ void __launch_bounds__(256, 2) k_lincomb_mx(int n, int L, const int64_t* in,
+                                                       size_t in_stride, const double* coef,
+                                                       int64_t* out, size_t out_stride,
+                                                       Tables tb) {
+  constexpr int STEPS = LC_K / 32;
+  __shared__ v4i dig[STEPS][7][64];
+  __shared__ unsigned long long sums[8][LC_RES];
+  const int lane = (int)threadIdx.x & 63, wave = (int)threadIdx.x >> 6;
+  const int col = lane & 31, half = lane >> 5;
+  const size_t r0 = (size_t)blockIdx.x * LC_RES;
+  const int64_t* src = in + r0 + col + (size_t)(wave * (LC_K / 4) + half * 16) * in_stride;
+  unsigned long long v[2][16], sum = 0;
+#pragma unroll
+  for (int q = 0; q < 2; ++q)
+#pragma unroll
+    for (int u = 0; u < 16; ++u)
+      v[q][u] = (unsigned long long)src[(size_t)(q * 32 + u) * in_stride];
+  loads_issued();
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    v4i o[7];
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      unsigned lo[4], hi[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const unsigned long long x = v[q][4 * g + u];
+        sum += x;
+        const unsigned long long w = x + 0x808080808080ull;
+        lo[u] = (unsigned)w;
+        hi[u] = (unsigned)(w >> 32);
+      }
+      int l[4], h[4];
+      bytes_across(lo, l);
+      bytes_across(hi, h);
+#pragma unroll
+      for (int a = 0; a < 4; ++a) o[a][g] = l[a] ^ (int)0x80808080u;
+      o[4][g] = h[0] ^ (int)0x80808080u;
+      o[5][g] = h[1] ^ (int)0x80808080u;
+      o[6][g] = h[2];
+    }
+#pragma unroll
+    for (int a = 0; a < 7; ++a) dig[wave * 2 + q][a][lane] = o[a];
+  }
+  sums[wave * 2 + half][col] = sum;
+  __syncthreads();
+
+  // this wave's 32 outputs: row j of the coefficients' tile, bytes as written
+  // by the host (step, byte, lane)
+  const v4i* ct = reinterpret_cast<const v4i*>(coef) + (size_t)wave * STEPS * 2 * 64 + lane;
+  v16i acc[8] = {};
+#pragma unroll 2
+  for (int s = 0; s < STEPS; ++s) {
+    const v4i c0 = ct[(s * 2) * 64], c1 = ct[(s * 2 + 1) * 64];
+    v4i d[7];
+#pragma unroll
+    for (int a = 0; a < 7; ++a) d[a] = dig[s][a][lane];
+#pragma unroll
+    for (int a = 0; a < 7; ++a)
+      acc[a] = __builtin_amdgcn_mfma_i32_32x32x32_i8(c0, d[a], acc[a], 0, 0, 0);
+#pragma unroll
+    for (int a = 0; a < 7; ++a)
+      acc[a + 1] = __builtin_amdgcn_mfma_i32_32x32x32_i8(c1, d[a], acc[a + 1], 0, 0, 0);
+  }
+  unsigned long long all = 0;
+#pragma unroll
+  for (int u = 0; u < 8; ++u) all += sums[u][col];
+  const double bl = (double)((int)(all & 0xffffff) * LC_BIAS),
+               bh = (double)(all >> 24) * (double)LC_BIAS;
+  const int i = (int)((r0 / n) % L);
+  const double p = cld(tb.p, i), pinv = cld(tb.pinv, i);
+  int64_t* dst = out + r0 + col + (size_t)(wave * 32 + half * 4) * out_stride;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    double wl = __builtin_fma((double)acc[1][r], 0x1p8, (double)acc[0][r] + bl);
+    wl = __builtin_fma((double)acc[2][r], 0x1p16, wl);
+    double wh = __builtin_fma((double)acc[4][r], 0x1p8, (double)acc[3][r] + bh);
+    wh = __builtin_fma((double)acc[5][r], 0x1p16, wh);
+    wh = __builtin_fma((double)acc[6][r], 0x1p24, wh);
+    wh = __builtin_fma((double)acc[7][r], 0x1p32, wh);
+    const double t = wh * 0x1p24;
+    const double x = __builtin_fma(-__builtin_rint(t * pinv), p, t) + wl;
+    dst[(size_t)(8 * (r / 4) + r % 4) * out_stride] = to_i64(reduce_bal(x, p, pinv), p);
+  }
 }
 
 // The trivial encryption (Delta, 0) of 1 in each of n_ct ciphertexts.
@@ -1754,15 +1873,43 @@ hipError_t run_lincomb(const Dims& d, int k, const BabyPtrs& b, const double* co
   const size_t per = (size_t)d.n_ct * 2 * d.L * d.n;
   if (k < 1 || k > BabyPtrs::CAP || J < 1 || J > 16 || (J > 1 && out_stride < per))
     return hipErrorInvalidValue;
-  if (J == 16)
-    hipLaunchKernelGGL(k_lincomb<16>, grid_for(per), dim3(256), 0, st, d.n, d.L, per, k, b, coef,
-                       J, out, out_stride, tb);
-  else if (J == 1)
+  if (J == 1)
     hipLaunchKernelGGL(k_lincomb<1>, grid_for(per), dim3(256), 0, st, d.n, d.L, per, k, b, coef,
                        J, out, out_stride, tb);
   else
     hipLaunchKernelGGL(k_lincomb<0>, grid_for(per), dim3(256), 0, st, d.n, d.L, per, k, b, coef,
                        J, out, out_stride, tb);
+  return hipGetLastError();
+}
+
+bool lincomb_mx_fits(const Dims& d, int k, int J, const std::vector<double>& c) {
+  if (k != LINCOMB_K || J != LINCOMB_J || d.n % LC_RES) return false;
+  for (double x : c)
+    if (x < LINCOMB_BIAS - 32896 || x > LINCOMB_BIAS + 32639) return false;
+  return true;
+}
+
+std::vector<double> lincomb_mx_table(const std::vector<double>& c) {
+  std::vector<double> tab((size_t)LINCOMB_K * LINCOMB_J * 2 / sizeof(double));
+  int8_t* bytes = reinterpret_cast<int8_t*>(tab.data());
+  for (int j = 0; j < LINCOMB_J; ++j)
+    for (int t = 0; t < LINCOMB_K; ++t) {
+      const int x = (int)c[(size_t)j * LINCOMB_K + t] - LINCOMB_BIAS;
+      const int b0 = ((x + 128) & 255) - 128, b1 = (x - b0) / 256;
+      const int lane = (t / 16 % 2) * 32 + j % 32;
+      const size_t at = (((size_t)(j / 32) * (LINCOMB_K / 32) + t / 32) * 2 * 64 + lane) * 16 + t % 16;
+      bytes[at] = (int8_t)b0;
+      bytes[at + 64 * 16] = (int8_t)b1;
+    }
+  return tab;
+}
+
+hipError_t run_lincomb_mx(const Dims& d, const int64_t* in, size_t in_stride, const double* tab,
+                          int64_t* out, size_t out_stride, const Tables& tb, hipStream_t st) {
+  const size_t per = (size_t)d.n_ct * 2 * d.L * d.n;
+  if (d.n % LC_RES || in_stride < per || out_stride < per) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_lincomb_mx, dim3((unsigned)(per / LC_RES)), dim3(256), 0, st, d.n, d.L, in,
+                     in_stride, tab, out, out_stride, tb);
   return hipGetLastError();
 }
 
