@@ -81,8 +81,9 @@ def kernel_hash() -> str:
 OPS_PER_MODUP = 7
 
 
-# One term y M of a base-conversion row, computed exactly as four FMAs on
-# 24-bit halves (y = y_h 2^24 + y_l, M = c1 2^24 + c0).
+# One term y M of a base-conversion row as exact FP64 arithmetic: four FMAs on
+# 24-bit halves (y = y_h 2^24 + y_l, M = c1 2^24 + c0).  The library forms the
+# conversions on the integer matrix cores; this is what they replace.
 OPS_PER_CONV_TERM = 4
 
 
@@ -103,7 +104,8 @@ def roofline_scale(prof: dict, ctx) -> dict | None:
     """The scale-and-round (FP64 VALU): per coefficient of the tensor product
     (three per ciphertext coefficient) two exact base conversions, L -> L + 1
     and L + 1 -> L primes, L (L + 1) terms each at OPS_PER_CONV_TERM FP64
-    operations; its reductions, modular products and the digits' mixed-radix
+    operations, the cost on the FP64 VALU of what the kernel does on the integer matrix
+    cores; its reductions, modular products and the digits' mixed-radix
     digits are overhead."""
     st = prof.get("scale")
     if not st or not st["launches"] or ctx is None:
@@ -363,7 +365,7 @@ def probes(ctx) -> dict:
     """The ceilings: the exact modular product's chip-wide rate, whether FP64
     MFMA adds FP64 throughput to the VALU, and one base conversion (17 -> 18
     primes over the scale-and-round's 3 x 2^20 coefficients) by split-FMA
-    rows and by integer MFMA."""
+    rows and by integer MFMA, the library's form."""
     import ctypes
     from paper_2602_24271_amd import _lib
     lib = _lib.load()

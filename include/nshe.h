@@ -347,8 +347,8 @@ int nshe_in_mask(nshe_ctx* ctx, const int64_t* x_dev, const int64_t* set_dev, in
  * LE(x, y) = (Delta, 0) - LT(y, x).  nshe_between gives
  * LE(lo, x) * LE(x, hi) (one more multiplication).  y (or lo and hi) may be
  * one ciphertext broadcast over the column.  Workspace:
- * nshe_compare_workspace_bytes(ctx, n_ct) (about K + k + m + 27 ciphertext
- * arrays, one operand's transform, one summed tensor and the multiply
+ * nshe_compare_workspace_bytes(ctx, n_ct) (about K + k + m + 11 ciphertext
+ * arrays, 16 more for t < 65537 or N < 32, one operand's transform, one summed tensor and the multiply
  * workspace; 0 if the context has no comparison polynomial). */
 #define NSHE_CMP_LT 0
 #define NSHE_CMP_LE 1
@@ -434,15 +434,18 @@ int nshe_sum_slots(nshe_ctx* ctx, const int64_t* in_dev, int64_t* out_dev, int n
  * (every kernel computes the same exact integers); only the speed does.
  *   ks_chunk       ciphertexts accumulated per pass over the relinearization
  *                  key in the key-switch inner product: 4, 8, 16 or 32
- *                  (at most 16 are used with digit transforms by parity);
+ *                  (at most 16 are used with digit transforms by parity;
+ *                  fewer ciphertexts, and equal shares of more, take the
+ *                  narrowest width that holds them, down to one);
  *   split_forward  1: each 2^15-point forward transform runs as two
  *                  workgroups: one per output half, and for the key-switch
  *                  digits one per coefficient parity (two 2^14-point
  *                  transforms whose last radix-2 stage the key-switch
  *                  product applies); 0: one workgroup per limb (ignored
  *                  for smaller N);
- *   ew_block       threads per workgroup of the per-coefficient kernels
- *                  (base lift, scale-and-round, mod-down): 64, 128 or 256;
+ *   ew_block       half the threads per workgroup of the per-coefficient
+ *                  kernels (base lift, scale-and-round, mod-down): 64, 128
+ *                  or 256;
  *   wave_ct        ciphertexts per wave of nshe_eq_mask_batched when its
  *                  wave_ct argument is 0 (0: as many as the workspace holds);
  *   ks_fused       1: at N = 32768 with split_forward, the key-switch

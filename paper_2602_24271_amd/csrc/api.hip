@@ -983,11 +983,10 @@ int nshe_ctx_create(const nshe_params* pr, int hip_device, nshe_ctx** out) {
   // Base-conversion matrices (canonical residues, [input][output]), uploaded
   // as the matrix-core constants of conv_matrix
   std::vector<u64> m_lift((size_t)L * LB), m_c2((size_t)L * LB), m_back((size_t)LB * L);
-  std::vector<double> two24(K), two48(K);
+  std::vector<double> two24(K);
   for (int i = 0; i < K; ++i) {
     const u64 m = prime(i), t24 = (1ull << 24) % m;
     two24[i] = bal(t24, m);
-    two48[i] = bal(mulmod(t24, t24, m), m);
   }
   // t_qhinv, t_q, c1: a second row times the inverse's last-stage twiddle
   std::vector<double> q_hat_inv(L), Q_b(LB), t_qhinv(2 * L), t_q(2 * L),
@@ -1108,20 +1107,18 @@ int nshe_ctx_create(const nshe_params* pr, int hip_device, nshe_ctx** out) {
                             mx_back = packed(conv_matrix(m_back, LB, qv));
   // --- upload
   std::vector<std::pair<const std::vector<double>*, const double**>> parts = {
-      {&h_p, &c->tb.p},           {&h_pinv, &c->tb.pinv},     {&h_pinv, &c->tb.recip},
+      {&h_p, &c->tb.p},           {&h_pinv, &c->tb.pinv},
       {&h_ninv, &c->tb.ninv},     {&tw_f, &c->tb.tw_fwd},     {&tw_i, &c->tb.tw_inv},
-      {&q_hat_inv, &c->tb.q_hat_inv}, {&Q_b, &c->tb.Q_b},
       {&t_qhinv, &c->tb.t_qhinv}, {&t_q, &c->tb.t_q},         {&c1, &c->tb.c1},
-      {&b_hat_inv, &c->tb.b_hat_inv},
-      {&B_q, &c->tb.B_q},         {&P_inv_q, &c->tb.P_inv_q}, {&NP_inv_q, &c->tb.NP_inv_q},
-      {&ninv_P, &c->tb.ninv_P},   {&mr_q, &c->tb.mr_q},       {&dig_c, &c->tb.dig_c},
+      {&NP_inv_q, &c->tb.NP_inv_q},
+      {&ninv_P, &c->tb.ninv_P},   {&dig_c, &c->tb.dig_c},
       {&delta_q, &c->tb.delta_q},
       {&mrc_inv, &c->tb.mrc_inv}, {&mrc_half, &c->tb.mrc_half}, {&tw_h, &c->tb.tw_half},
       {&tw_h0, &c->tb.tw_half0},  {&tw_cf, &c->tb.tw_cmp_f},  {&tw_ci, &c->tb.tw_cmp_i},
       {&tw_ch, &c->tb.tw_cmp_h},  {&tw_kf, &c->tb.tw_cst_f},  {&tw_ki, &c->tb.tw_cst_i},
       {&mx_lift, &c->tb.mx_lift}, {&mx_c2, &c->tb.mx_c2}, {&mx_back, &c->tb.mx_back},
       {&kq, &c->tb.kq},           {&kb, &c->tb.kb},           {&km, &c->tb.km},
-      {&two24, &c->tb.two24},     {&two48, &c->tb.two48},
+      {&two24, &c->tb.two24},
       {&tw_hi, &c->tb.tw_half_inv}, {&tw_chi, &c->tb.tw_cmp_hi},
       {&tw_r1f, &c->tb.tw_r1_f},  {&tw_r1i, &c->tb.tw_r1_i},
       {&tw_cp, &c->tb.tw_cmp_par}, {&tw_r1p, &c->tb.tw_r1_par}, {&tw_last, &c->tb.tw_last}};

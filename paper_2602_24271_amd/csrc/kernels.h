@@ -20,9 +20,6 @@ constexpr int MAX_PRIMES = 2 * MAX_L + 1 + MAX_ALPHA;
 struct Tables {
   const double* p;           // [K]
   const double* pinv;        // [K] fl(1/p)
-  const double* recip;       // [K] fl(1/p), the same values as pinv: no kernel reads it
-                             // any more (pinv serves the CRT estimates); kept so that
-                             // the struct's layout, and the kernels' registers, stay put
   const double* ninv;        // [K] balanced N^-1
   const double* tw_fwd;      // [K][tw_len] round-0 twiddles (slot 2^k + j)
   const double* tw_inv;      // [K][tw_len]
@@ -48,9 +45,6 @@ struct Tables {
   // slot 2^k + j of row u the twiddle of the round's stage k, block j
   const double* tw_r1_f;
   const double* tw_r1_i;
-  // centred lift Q -> B
-  const double* q_hat_inv;   // [L]      [(Q/q_i)^-1]_{q_i}
-  const double* Q_b;         // [LB]     [Q]_{b_k}
   // scale and round, then B -> Q
   // (the scale-and-round reads inverse-transform output, which carries a
   // factor N: its constants include N^-1)
@@ -60,24 +54,21 @@ struct Tables {
   const double* t_qhinv;     // [2][L]   [t (Q/q_i)^-1 N^-1]_{q_i}
   const double* t_q;         // [2][L]   [t N^-1]_{q_i}
   const double* c1;          // [2][LB]  [t Q^-1 (B/b_k)^-1 N^-1]_{b_k}
-  const double* b_hat_inv;   // [LB]     [(B/b_k)^-1]_{b_k}
-  const double* B_q;         // [L]      [B]_{q_i}
   // the three base conversions' constants for the integer matrix cores
   // (conv_matrix: int4 entries per tile, step and lane): [Q/q_i]_{b_k},
-  // [q_i^-1 (B/b_k)^-1]_{b_k}, [B/b_k]_{q_i}; and [2^24]_p, [2^48]_p per prime
+  // [q_i^-1 (B/b_k)^-1]_{b_k}, [B/b_k]_{q_i}
   const double* mx_lift;     // L -> LB
   const double* mx_c2;       // L -> LB
   const double* mx_back;     // LB -> L
   // constants of the per-coefficient kernels, one prime's side by side (a few
   // wide scalar loads), padded to whole steps of four primes
-  const double* kq;          // [L][4]   q, fl(1/q), q_hat_inv, B_q
-  const double* kb;          // [LB][4]  b, fl(1/b), b_hat_inv, Q_b
-  const double* km;          // [L][alpha] P_inv_q, then mr_q of k = 1..alpha-1
-  const double* two24;       // [K]
-  const double* two48;       // [K]
+  const double* kq;          // [L][4]   q_i, fl(1/q_i), [(Q/q_i)^-1]_{q_i}, [B]_{q_i}
+  const double* kb;          // [LB][4]  b_k, fl(1/b_k), [(B/b_k)^-1]_{b_k}, [Q]_{b_k}
+  const double* km;          // [L][alpha] [P^-1]_{q_i}, then (alpha > 1, see p_inv_p)
+                             //          [(P_0 ... P_{k-1}) P^-1]_{q_i}, k = 1..alpha-1
+  const double* two24;       // [K]      [2^24]_p
   // key switching (digits of alpha data primes, alpha special primes; the
   // tables for several primes per digit are at the end of the struct)
-  const double* P_inv_q;     // [L]      [P^-1]_{q_i}
   const double* NP_inv_q;    // [2][L]   [N^-1 P^-1]_{q_i}; second row times w_i
   const double* ninv_P;      // [alpha][2] [N^-1]_{P_k}, times w_{P_k} (w: the 2^15-point
                              //          inverse's last-stage twiddle of the prime)
@@ -97,7 +88,6 @@ struct Tables {
   // alpha > 1: the centred residue mod P = P_0 ... P_{alpha-1} in mixed
   // radix, a_0 + P_0 k_1 + P_0 P_1 k_2 with balanced digits (Garner:
   // k_1 = [(a_1 - a_0) P_0^-1]_{P_1}, k_2 = [((a_2 - a_0) P_0^-1 - k_1) P_1^-1]_{P_2})
-  const double* mr_q;        // [alpha-1][L] [(P_0 ... P_{k-1}) P^-1]_{q_i}, k = 1..alpha-1
   double p_inv_p[3];         //          [P_0^-1]_{P_1}, [P_0^-1]_{P_2}, [P_1^-1]_{P_2}, balanced
   // alpha > 1: a digit's value mod target prime i of the key-switching
   // basis from its canonical mixed-radix digits (v_0, ..., v_{alpha-1}):

@@ -1026,8 +1026,8 @@ __global__ void __launch_bounds__(256) k_tensor_mac(int n, int W, size_t total, 
 // split once as v = vh 2^24 + vl (split24), so that every product is an
 // exact FMA (|vh c| <= 2^39): two exact sums per output over k <= 256
 // terms (below 2^47), combined once as Wh [2^24]_q + Wl.  For the small
-// plaintext primes' matrices (at most 16 x 16 would fill one pass) and the
-// single top term; JT: J fixed at compile time (1), or 0 for any J (a branch
+// plaintext primes' matrices (16 x 8 at t = 257: one pass), rings below 32
+// and the single top term; JT: J fixed at compile time (1), or 0 for any J (a branch
 // per output and term).
 template <int JT>
 __global__ void __launch_bounds__(256) k_lincomb(int n, int L, size_t per, int k, BabyPtrs b,
@@ -1094,11 +1094,11 @@ __device__ __forceinline__ void bytes_across(const unsigned (&w)[4], int (&o)[4]
   o[3] = (int)__builtin_amdgcn_perm(e, b, 0x07060302u);
 }
 
-// The same combinations of 256 inputs to 128 outputs, all outputs
+// The same combinations of 256 inputs to 128 outputs (t = 65537), all outputs
 // of 32 residues in one block, on the integer matrix cores.  A canonical value
 // v < 2^49 is seven signed bytes (v + 0x808080808080, bytes 0..5 XOR 0x80; byte
-// 6 is at most 2), and a coefficient's c - LC_BIAS (in [-32895, 32639] for -32768 <= c <= 32766,
-// which the host checks) exactly two.  v_mfma_i32_32x32x32_i8 sums every
+// 6 is at most 2), and a coefficient's c - LC_BIAS exactly two (the host checks
+// their range; -32768 <= c <= 32766).  v_mfma_i32_32x32x32_i8 sums every
 // byte product of equal weight 2^(8s), s < 8, in 32 bits (|A_s| <= 2 256 2^14 =
 // 2^23), and
 //   sum_t c_t v_t = sum_s 2^(8s) A_s + LC_BIAS sum_t v_t
