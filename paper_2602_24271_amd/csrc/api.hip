@@ -1905,7 +1905,7 @@ static int rotate_ext(nshe_ctx* c, const Ws& w, int n_ct, uint32_t g, const doub
     Prof pf(c, K_AUTOMORPH, st, 2.0 * n_ct * c->L * c->n);
     const DigitSrc ds = digit_src(c, w);
     HIPCHK(run_automorph(dims(c, n_ct), inv_mod_2n(c, g), w.ext, w.dt, c->tb, st, ds.p, ds.stride,
-                         ds.split));
+                         ds.split, md.kind == MD_SUM || md.kind == MD_SUM_I64));
   }
   md.one_e = 1;
   return relin(c, w, n_ct, st, key, md);

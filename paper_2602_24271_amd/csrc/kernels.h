@@ -271,11 +271,12 @@ hipError_t run_diff_i64(const Dims& d, const int64_t* x, const int64_t* y, int y
 // rotations: the rotation digits of ext's component 1 (into its limbs
 // L..2L-1), and the automorphism of component 0 into dt's and of the digits
 // into the digit source (ciphertext ct at src + ct src_stride; src_split: by
-// coefficient parity, as run_scale)
+// coefficient parity, as run_scale); sum: component 0 plus its rotation, for
+// the running sum's mod-down
 hipError_t run_rotation_digits(const Dims& d, double* ext, const Tables& tb, hipStream_t st);
 hipError_t run_automorph(const Dims& d, unsigned ginv, const double* ext, double* dt,
                          const Tables& tb, hipStream_t st, double* src, size_t src_stride,
-                         int src_split);
+                         int src_split, int sum);
 // alpha primes per digit (alpha > 1): canonical residues of the digit
 // source (limbs 0..L-1 of ciphertext ct at src + ct src_stride, any
 // coefficient order) into each digit's canonical mixed-radix digits, in place

@@ -686,15 +686,17 @@ __device__ __forceinline__ double rotation_digit(double o, int m, double (&v)[A]
 // 0.9 q_i (operands below 2 q_i: P_k may exceed q_i, all lie below 2^49), so a
 // sum stays below 4.2 q_i.  What becomes of the result z (OUT):
 //   MD_EXT   stored in ext (limbs 0..L-1);
-//   MD_SUM   added to what ext holds there, and component 1's rotation digits
-//            (see rotated_digit) stored in its limbs L..2L-1;
+//   MD_SUM   a rotation's, in a running sum: stored in ext as MD_EXT, and component
+//            1's rotation digits (see rotated_digit) in its limbs L..2L-1.  e_0 holds the
+//            sum's component 0 and its rotation already (k_automorph), e_1 is what
+//            ext holds;
 //   MD_LIFT  stored in ext and lifted (limbs L..2L) for the squaring that
 //            follows: the next level of a chain lifts exactly this;
 //   MD_I64   canonical residues in the int64 output, with finish the mask's
 //            (Delta, 0) - z; wt (table not null): a batched wave's ciphertexts,
 //            written through the table's out pointers;
-//   MD_SUM_I64  ext's residues plus z in the int64 output.
-// one_e: component 1's e is zero (a rotation's), not read.
+//   MD_SUM_I64  MD_SUM's z in the int64 output.
+// one_e: component 1's e is zero (a rotation's), not read; SUM kinds: read in ext.
 // FUSED: acc holds the split inverse's in-place half outputs of a 2^15-point
 // limb (U of pair c at (c / 512) 1024 + c mod 512, V 512 further; see
 // k_ntt_inv_half): lanes l and l + 32 of a wave hold the two coefficients of a
@@ -714,8 +716,6 @@ k_moddown(int n, size_t n_poly, const double* __restrict__ acc, const double* __
   constexpr int K = L + A;
   constexpr int W = 2 * L + 1;
   constexpr bool SUM = OUT == MD_SUM || OUT == MD_SUM_I64, I64 = OUT == MD_I64 || OUT == MD_SUM_I64;
-  // the running sum's limbs are loaded up front where the registers allow
-  constexpr bool PRE = SUM && K + 2 * L <= 52;
   __shared__ v4i tab[OUT == MD_LIFT ? conv_entries(L, L + 1) : 1];
   __shared__ double kl[2 * K];   // NP_inv_q's and ninv_P's two rows, limb i's at 2 i
   const int t = (int)threadIdx.x, lane = t & 63;
@@ -737,18 +737,17 @@ k_moddown(int n, size_t n_poly, const double* __restrict__ acc, const double* __
     const int b = (int)(cb & 1);
     const auto ra = make_rsrc(acc + cb * (size_t)K * n, (unsigned)(K * n * 8));
     // (an empty buffer reads as zeros)
-    const auto re = make_rsrc(dt + (ct * 3 + b) * (size_t)W * n,
-                              one_e && b ? 0u : (unsigned)(L * n * 8));
+    const double* eb = SUM && b ? ext + cb * (size_t)W * n : dt + (ct * 3 + b) * (size_t)W * n;
+    const auto re = make_rsrc(eb, !SUM && one_e && b ? 0u : (unsigned)(L * n * 8));
     const auto rs = make_rsrc(ext + cb * (size_t)W * n, (unsigned)(W * n * 8));
     // every load is issued before the first use
-    double xa[K], e[L], sum[PRE ? L : 1];
+    double xa[K], e[L];
 #pragma unroll
     for (int m = 0; m < A; ++m) xa[L + m] = buf_load(ra, pos, (L + m) * ls);
 #pragma unroll
     for (int i = 0; i < L; ++i) {
       xa[i] = buf_load(ra, pos, i * ls);
       e[i] = buf_load(re, vo, i * ls);
-      if constexpr (PRE) sum[i] = buf_load(rs, vo, i * ls);
     }
     loads_issued();
     if (first) {
@@ -794,11 +793,7 @@ k_moddown(int n, size_t n_poly, const double* __restrict__ acc, const double* __
           // finish: -z, plus Delta at coefficient 0 of c0
           if (finish) r = b == 0 && c == 0 ? cld(tb.delta_q, i) - r : -r;
         }
-        double z = reduce_bal(r, q, qinv);
-        if constexpr (SUM) {
-          if constexpr (PRE) z = reduce_bal(sum[i] + z, q, qinv);
-          else z = reduce_bal(buf_load(rs, vo, i * ls) + z, q, qinv);
-        }
+        const double z = reduce_bal(r, q, qinv);
         if constexpr (I64) {
           if (pb.ok) o64[(size_t)i * n] = to_i64(z, q);
         } else {
@@ -1277,12 +1272,14 @@ struct RotLimb {
   bool digit;      // a digit limb (else c0's, balanced)
   bool lowest;     // its group's first
   bool split;      // stored by coefficient parity
+  bool add;        // c0's limb itself is added (a running sum)
   double q;
 };
 
 __device__ __forceinline__ RotLimb rot_limb(size_t item, int n, int L, int alpha,
                                             const double* ext, double* dt, double* dsrc,
-                                            size_t dsrc_stride, int split, const Tables& tb) {
+                                            size_t dsrc_stride, int split, int sum,
+                                            const Tables& tb) {
   const size_t W = (size_t)2 * L + 1;
   const size_t ct = item / (2 * L);
   const int r = (int)(item - ct * 2 * L), i = r < L ? r : r - L;
@@ -1292,6 +1289,7 @@ __device__ __forceinline__ RotLimb rot_limb(size_t item, int n, int L, int alpha
   l.dst = l.digit ? dsrc + ct * dsrc_stride + (size_t)i * n : dt + (ct * 3 * W + i) * n;
   l.lowest = i % alpha == 0;
   l.split = l.digit && split;
+  l.add = !l.digit && sum;
   l.q = cld(tb.p, i);
   return l;
 }
@@ -1302,19 +1300,22 @@ __device__ __forceinline__ double rot_value(const RotLimb& l, double x, bool neg
 
 // The automorphism into the key-switching input layout: sigma(c0) into dt's
 // component 0 (component 1 is zero and not written: the mod-down's one_e), the
-// digits of sigma(c1) into the digit source.  Each value is read where it lies.
+// digits of sigma(c1) into the digit source.  sum: c0 + sigma(c0) (unreduced) in place of
+// sigma(c0), so that the running sum's mod-down reads one addend per component.
+// Each value is read where it lies.
 __global__ void __launch_bounds__(256) k_automorph(int n, int L, int alpha, int n_ct,
                                                    unsigned ginv, const double* ext, double* dt,
                                                    double* dsrc, size_t dsrc_stride, int split,
-                                                   Tables tb) {
+                                                   int sum, Tables tb) {
   const size_t gid = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (gid >= (size_t)n_ct * 2 * L * n) return;
   const size_t item = gid / n;
   const int j = (int)(gid - item * n);
-  const RotLimb l = rot_limb(item, n, L, alpha, ext, dt, dsrc, dsrc_stride, split, tb);
+  const RotLimb l = rot_limb(item, n, L, alpha, ext, dt, dsrc, dsrc_stride, split, sum, tb);
   const unsigned s = ((unsigned)j * ginv) & (2u * n - 1u);
+  const double own = l.add ? l.src[j] : 0.0;
   l.dst[l.split ? (j & 1) * (n >> 1) + (j >> 1) : j] =
-      rot_value(l, l.src[s & (unsigned)(n - 1)], s >= (unsigned)n);
+      rot_value(l, l.src[s & (unsigned)(n - 1)], s >= (unsigned)n) + own;
 }
 
 // The same, one workgroup of 1024 threads per limb (N = 1024 E), staged through
@@ -1322,17 +1323,20 @@ __global__ void __launch_bounds__(256) k_automorph(int n, int L, int alpha, int 
 // permutation's reads, a stride of g^-1 (odd) words apart, meet no bank twice.
 // Reading each value where it lies touches a cache line per value: 220 us for
 // the column's 32 ciphertexts (15 + 3 primes) and 40 more for the digits, which
-// followed the permutation; staged, with the digits formed before, 118 us
+// followed the permutation; staged, with the digits formed before, 119 us
 // (0.5 GB, bound by memory traffic).  Used from 90 limbs on: below that too few
-// CUs hold a workgroup.
+// CUs hold a workgroup.  The sum costs it nothing (a limb's own values stay in
+// registers and LDS; read again they cost what the mod-down saves) and takes 15
+// limbs per ciphertext off the mod-down, 203 -> 172 us: the column's SUM 14.14 ->
+// 13.90 ms, of three ciphertexts 1.95 -> 1.88.
 template <int E>
 __global__ void __launch_bounds__(1024) k_automorph_lds(int L, int alpha, unsigned ginv,
                                                         const double* ext, double* dt,
                                                         double* dsrc, size_t dsrc_stride,
-                                                        int split, Tables tb) {
+                                                        int split, int sum, Tables tb) {
   constexpr int n = 1024 * E;
   __shared__ uint32_t lds[n];
-  const RotLimb l = rot_limb(blockIdx.x, n, L, alpha, ext, dt, dsrc, dsrc_stride, split, tb);
+  const RotLimb l = rot_limb(blockIdx.x, n, L, alpha, ext, dt, dsrc, dsrc_stride, split, sum, tb);
   const int tid = threadIdx.x;
   // (opaque per pass: no element's addresses stay in registers between passes)
   unsigned s0 = (unsigned)tid * ginv;
@@ -1340,28 +1344,44 @@ __global__ void __launch_bounds__(1024) k_automorph_lds(int L, int alpha, unsign
   const auto rs = make_rsrc(l.src, n * 8), rd = make_rsrc(l.dst, n * 8);
   const unsigned vo = (l.split ? (tid & 1) * (n >> 1) + (tid >> 1) : tid) * 8;
   const unsigned eo = l.split ? 4096 : 8192;   // bytes between a thread's elements
-  uint32_t lo[E], hi[E];
+  const uint32_t mask = l.add ? ~0u : 0u;
+  uint32_t lo[E], hi[E], own[E];   // own: the low half in order, for the sum
 #pragma unroll
   for (int e = 0; e < E; ++e) {
     const unsigned long long v = __double_as_longlong(buf_load(rs, tid * 8, e * 8192));
     lo[e] = (uint32_t)v;
     hi[e] = (uint32_t)(v >> 32);
   }
+  loads_issued();
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    // (own registers: as halves of the loaded pairs they spill 42)
+    asm volatile("v_mov_b32 %0, %1" : "=v"(lo[e]) : "v"(lo[e]));
+    asm volatile("v_mov_b32 %0, %1" : "=v"(hi[e]) : "v"(hi[e]));
+  }
 #pragma unroll
   for (int e = 0; e < E; ++e) lds[e * 1024 + tid] = lo[e];
   __syncthreads();
 #pragma unroll
-  for (int e = 0; e < E; ++e) lo[e] = lds[(s0 + e * step) & (n - 1)];
+  for (int e = 0; e < E; ++e) {
+    own[e] = lo[e] & mask;
+    lo[e] = lds[(s0 + e * step) & (n - 1)];
+    if (e % 8 == 7) loads_issued();
+  }
   __syncthreads();
 #pragma unroll
   for (int e = 0; e < E; ++e) lds[e * 1024 + tid] = hi[e];
   __syncthreads();
+  loads_issued();
   asm volatile("" : "+v"(s0));
 #pragma unroll
   for (int e = 0; e < E; ++e) {
     const unsigned s = (s0 + e * step) & (2 * n - 1);
     const unsigned long long v = ((unsigned long long)lds[s & (n - 1)] << 32) | lo[e];
-    buf_store(rot_value(l, __longlong_as_double(v), s >= (unsigned)n), rd, vo, e * eo);
+    double x = rot_value(l, __longlong_as_double(v), s >= (unsigned)n);
+    x += __longlong_as_double(((unsigned long long)(lds[e * 1024 + tid] & mask) << 32) | own[e]);
+    buf_store(x, rd, vo, e * eo);
+    if (e % 4 == 3) loads_issued();
   }
 }
 
@@ -1941,20 +1961,20 @@ hipError_t run_rotation_digits(const Dims& d, double* ext, const Tables& tb, hip
 
 hipError_t run_automorph(const Dims& d, unsigned ginv, const double* ext, double* dt,
                          const Tables& tb, hipStream_t st, double* src, size_t src_stride,
-                         int src_split) {
+                         int src_split, int sum) {
   const size_t items = (size_t)d.n_ct * 2 * d.L;
   const dim3 grid((unsigned)items);
 #define C_(E_)                                                                                  \
   case 1024 * E_:                                                                               \
     hipLaunchKernelGGL(k_automorph_lds<E_>, grid, dim3(1024), 0, st, d.L, d.alpha, ginv, ext, dt, \
-                       src, src_stride, src_split, tb);                                         \
+                       src, src_stride, src_split, sum, tb);                                    \
     return hipGetLastError();
   if (items >= 90) {
     switch (d.n) { C_(1) C_(2) C_(4) C_(8) C_(16) C_(32) }
   }
 #undef C_
   hipLaunchKernelGGL(k_automorph, grid_for(items * d.n), dim3(256), 0, st, d.n, d.L, d.alpha,
-                     d.n_ct, ginv, ext, dt, src, src_stride, src_split, tb);
+                     d.n_ct, ginv, ext, dt, src, src_stride, src_split, sum, tb);
   return hipGetLastError();
 }
 
