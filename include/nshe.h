@@ -51,6 +51,14 @@
  * Streams: `stream` is a hipStream_t (NULL = the null stream).  All work is
  * enqueued asynchronously; results are valid after the stream synchronises.
  *
+ * Overlap: an output may lie on inputs of nshe_square_relin, nshe_mul_relin,
+ * nshe_eq_mask and nshe_sum_slots, ciphertext on ciphertext or shifted: each
+ * reads all it was given before it overwrites any of it (a call with one
+ * half's output on the other half's input is not split over two streams).
+ * nshe_eq_mask_batched does so wave by wave: items whose outputs lie on other
+ * items' operands or outputs run in waves one after the other, a later wave
+ * reading what an earlier one wrote.  No buffer may lie in the workspace.
+ *
  * Errors: every int-returning call returns NSHE_OK (0) or a negative code;
  * nshe_last_error() gives a message for the calling thread.  Arguments are
  * validated on the host before any work is enqueued (null pointers, sizes,
@@ -239,7 +247,7 @@ int nshe_relinearize(nshe_ctx* ctx, const int64_t* in3_dev, int64_t* out_dev,
 /* EQ(x, y) = 1 - (x - y)^(t-1) (Eq. eq:equality) for n_ct ciphertexts:
  * x is [n_ct][2][L][N]; y is the same shape, or one ciphertext broadcast to
  * every x when y_broadcast != 0 (an encrypted predicate constant).  Requires
- * t - 1 = 2^k (k squarings).  out may alias x (not y when broadcast).
+ * t - 1 = 2^k (k squarings).  out may alias x or y.
  * From two ciphertexts on (four with alpha = 1; 2^15 coefficients in smaller
  * rings), the call runs its two halves on two streams (tuning streams, see
  * nshe_tuning); it stays ordered on `stream`. */

@@ -5,7 +5,6 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
-#include <functional>
 #include <map>
 #include <mutex>
 #include <string>
@@ -766,6 +765,106 @@ static int scratch_address(int device, void** out) {
   return NSHE_OK;
 }
 
+// ------------------------------------------------------------ two streams
+
+// Whether st is known not to be capturing into a graph (a second stream
+// joins only then).
+static bool stream_idle_capture(hipStream_t st) {
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &cs) != hipSuccess) return false;
+  return cs == hipStreamCaptureStatusNone;
+}
+
+// Whether a call over n_ct ciphertexts runs as two halves on two streams
+// (tuning streams = 2): not while profiling (each launch's own time), not the
+// no-allocation scratch, not while st is being captured, and only where the
+// second half's share of the workspace starts 256-byte aligned.  From two
+// ciphertexts on (four with one digit per data prime, whose key, read by both
+// halves, is 160 MB): one half's kernels fill the CUs that the other's leave
+// idle.  EQ at N = 2^15, one stream against two, ms: three-prime digits 2
+// ciphertexts 2.63 / 2.61, 3: 3.62 / 3.24, 5: 5.31 / 4.72, 8: 7.59 / 7.15, 16:
+// 14.3 / 13.4; two-prime 2: 3.16 / 2.90, 8: 9.07 / 8.26; one-prime 3: 5.37 /
+// 5.59, 4: 6.75 / 6.40, 8: 12.1 / 11.7.  (Three and four streams: 8
+// ciphertexts 7.06 and 8.23.)  Rings below 2^15 from 2^15 coefficients on:
+// below that the launches themselves are what the GPU waits for (2^10, 2
+// ciphertexts: 0.65 / 0.98 ms).
+static int halves_from(const nshe_ctx* c) { return c->alpha == 1 ? 4 : 2; }
+
+// A call's input as the halves' streams read it: ciphertext i of the call reads
+// ciphertext i of p, or the one ciphertext at p (bcast).
+struct HalfIn {
+  const int64_t* p;
+  bool bcast = false;
+};
+
+static bool overlap(const int64_t* a, size_t an, const int64_t* b, size_t bn) {
+  const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+  return x < y + bn * sizeof(int64_t) && y < x + an * sizeof(int64_t);
+}
+
+// Whether one half of a call's output lies on what the other half reads (out
+// shifted against an input, or on a broadcast one).  On one stream every input
+// is read before the first result is written; on two, one half could overwrite
+// what the other has still to read, so such a call stays on one.
+static bool halves_cross(const nshe_ctx* c, int n_ct, const int64_t* out,
+                         std::initializer_list<HalfIn> ins) {
+  const size_t ctw = (size_t)2 * c->L * c->n, n = n_ct * ctw, h = n_ct / 2 * ctw;
+  for (const HalfIn& in : ins) {
+    if (in.bcast ? overlap(out, n, in.p, ctw)
+                 : overlap(out, h, in.p + h, n - h) || overlap(out + h, n - h, in.p, h))
+      return true;
+  }
+  return false;
+}
+
+static bool two_halves(nshe_ctx* c, int n_ct, int from, const void* ws, hipStream_t st) {
+  if (c->tune.streams != 2 || n_ct < from || (size_t)n_ct * c->n < (1u << 15) || c->prof ||
+      ws == c->scratch)
+    return false;
+  if (ws_doubles(c, n_ct / 2) * sizeof(double) % 256) return false;
+  return stream_idle_capture(st);
+}
+
+// The context's second stream and its fork and join events, made on first use.
+static int half_stream_ready(nshe_ctx* c) {
+  if (!c->half_stream) HIPCHK(hipStreamCreateWithFlags(&c->half_stream, hipStreamNonBlocking));
+  if (!c->half_fork) HIPCHK(hipEventCreateWithFlags(&c->half_fork, hipEventDisableTiming));
+  if (!c->half_join) HIPCHK(hipEventCreateWithFlags(&c->half_join, hipEventDisableTiming));
+  return NSHE_OK;
+}
+
+// The ciphertexts of a call, in `steps` steps run(step, first ciphertext,
+// count, workspace share, stream): all of them on st, or (two) in two halves,
+// the first on st, the second on the context's
+// second stream, each in its own share of the workspace (the workspace is
+// linear in n_ct, so the two shares fill it).  The second stream starts
+// after the work already on st, and st waits for it at the end.  The halves'
+// steps are enqueued in turn, so that the second stream starts with the first
+// and not after all of its launches (a lone call over three ciphertexts would
+// wait 0.3 ms for them).
+template <class F>
+static int run_halves(nshe_ctx* c, int n_ct, bool two, int steps, void* ws, hipStream_t st,
+                      const F& run) {
+  if (!two) {
+    int rc = NSHE_OK;
+    for (int k = 0; k < steps && !rc; ++k) rc = run(k, 0, n_ct, ws, st);
+    return rc;
+  }
+  const int h = n_ct / 2;
+  int rc = half_stream_ready(c);
+  if (rc) return rc;
+  void* const ws2 = static_cast<double*>(ws) + ws_doubles(c, h);
+  HIPCHK(hipEventRecord(c->half_fork, st));
+  HIPCHK(hipStreamWaitEvent(c->half_stream, c->half_fork, 0));
+  for (int k = 0; k < steps && !rc; ++k) {
+    rc = run(k, 0, h, ws, st);
+    if (!rc) rc = run(k, h, n_ct - h, ws2, c->half_stream);
+  }
+  HIPCHK(hipEventRecord(c->half_join, c->half_stream));
+  HIPCHK(hipStreamWaitEvent(st, c->half_join, 0));
+  return rc;
+}
+
 // =================================================================== ABI
 
 extern "C" {
@@ -1418,10 +1517,6 @@ static int common_checks(nshe_ctx* c, int n_ct, void* ws, size_t ws_bytes, bool 
   return NSHE_OK;
 }
 
-using HalfStep = std::function<int(int, int, int, void*, hipStream_t)>;
-static int run_halves(nshe_ctx* c, int n_ct, int from, int steps, void* ws, hipStream_t st,
-                      const HalfStep& run);
-
 // A single product runs as two halves from eight ciphertexts on: below that
 // the fork and join (two events, twice the launches) cost what they save (2
 // ciphertexts 225 us on one stream, 256 on two; 8: 650 and 624).
@@ -1437,7 +1532,9 @@ int nshe_square_relin(nshe_ctx* c, const int64_t* in, int64_t* out, int n_ct, vo
   hipStream_t st = static_cast<hipStream_t>(stream);
   if ((rc = check_inputs(c, st, {{in, (size_t)n_ct * 2}}))) return rc;
   const size_t ctw = (size_t)2 * c->L * c->n;
-  return run_halves(c, n_ct, PRODUCT_HALVES_FROM, 1, ws, st,
+  const bool two =
+      two_halves(c, n_ct, PRODUCT_HALVES_FROM, ws, st) && !halves_cross(c, n_ct, out, {{in}});
+  return run_halves(c, n_ct, two, 1, ws, st,
                     [&](int, int c0, int cnt, void* wsh, hipStream_t s) {
     Ws w = carve(c, wsh, cnt);
     int r = prepare_i64(c, in + c0 * ctw, w.ext, w.fx, cnt, s);
@@ -1473,7 +1570,9 @@ int nshe_mul_relin(nshe_ctx* c, const int64_t* a, const int64_t* b, int64_t* out
   hipStream_t st = static_cast<hipStream_t>(stream);
   if ((rc = check_inputs(c, st, {{a, (size_t)n_ct * 2}, {b, (size_t)n_ct * 2}}))) return rc;
   const size_t ctw = (size_t)2 * c->L * c->n;
-  return run_halves(c, n_ct, PRODUCT_HALVES_FROM, 1, ws, st,
+  const bool two =
+      two_halves(c, n_ct, PRODUCT_HALVES_FROM, ws, st) && !halves_cross(c, n_ct, out, {{a}, {b}});
+  return run_halves(c, n_ct, two, 1, ws, st,
                     [&](int, int c0, int cnt, void* wsh, hipStream_t s) {
     Ws w = carve(c, wsh, cnt);
     int r = load_two(c, w, a + c0 * ctw, b + c0 * ctw, cnt, s);
@@ -1535,77 +1634,6 @@ static int eq_level(nshe_ctx* c, const Ws& w, int n_ct, int k, hipStream_t st,
   return square_level(c, w, n_ct, st, true, md, last ? tab : nullptr);
 }
 
-// Whether st is known not to be capturing into a graph (a second stream
-// joins only then).
-static bool stream_idle_capture(hipStream_t st) {
-  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(st, &cs) != hipSuccess) return false;
-  return cs == hipStreamCaptureStatusNone;
-}
-
-// Whether a call over n_ct ciphertexts runs as two halves on two streams
-// (tuning streams = 2): not while profiling (each launch's own time), not the
-// no-allocation scratch, not while st is being captured, and only where the
-// second half's share of the workspace starts 256-byte aligned.  From two
-// ciphertexts on (four with one digit per data prime, whose key, read by both
-// halves, is 160 MB): one half's kernels fill the CUs that the other's leave
-// idle.  EQ at N = 2^15, one stream against two, ms: three-prime digits 2
-// ciphertexts 2.63 / 2.61, 3: 3.62 / 3.24, 5: 5.31 / 4.72, 8: 7.59 / 7.15, 16:
-// 14.3 / 13.4; two-prime 2: 3.16 / 2.90, 8: 9.07 / 8.26; one-prime 3: 5.37 /
-// 5.59, 4: 6.75 / 6.40, 8: 12.1 / 11.7.  (Three and four streams: 8
-// ciphertexts 7.06 and 8.23.)  Rings below 2^15 from 2^15 coefficients on:
-// below that the launches themselves are what the GPU waits for (2^10, 2
-// ciphertexts: 0.65 / 0.98 ms).
-static int halves_from(const nshe_ctx* c) { return c->alpha == 1 ? 4 : 2; }
-
-static bool two_halves(nshe_ctx* c, int n_ct, int from, const void* ws, hipStream_t st) {
-  if (c->tune.streams != 2 || n_ct < from || (size_t)n_ct * c->n < (1u << 15) || c->prof ||
-      ws == c->scratch)
-    return false;
-  if (ws_doubles(c, n_ct / 2) * sizeof(double) % 256) return false;
-  return stream_idle_capture(st);
-}
-
-// The context's second stream and its fork and join events, made on first use.
-static int half_stream_ready(nshe_ctx* c) {
-  if (!c->half_stream) HIPCHK(hipStreamCreateWithFlags(&c->half_stream, hipStreamNonBlocking));
-  if (!c->half_fork) HIPCHK(hipEventCreateWithFlags(&c->half_fork, hipEventDisableTiming));
-  if (!c->half_join) HIPCHK(hipEventCreateWithFlags(&c->half_join, hipEventDisableTiming));
-  return NSHE_OK;
-}
-
-// The ciphertexts of a call, in `steps` steps run(step, first ciphertext,
-// count, workspace share, stream): all of them on st, or in two halves from
-// `from` ciphertexts on, the first half on st,
-// the second half on the context's
-// second stream, each in its own share of the workspace (the workspace is
-// linear in n_ct, so the two shares fill it).  The second stream starts
-// after the work already on st, and st waits for it at the end.  The halves'
-// steps are enqueued in turn, so that the second stream starts with the first
-// and not after all of its launches (a lone call over three ciphertexts would
-// wait 0.3 ms for them).
-static int run_halves(nshe_ctx* c, int n_ct, int from, int steps, void* ws, hipStream_t st,
-                      const HalfStep& run) {
-  if (!two_halves(c, n_ct, from, ws, st)) {
-    int rc = NSHE_OK;
-    for (int k = 0; k < steps && !rc; ++k) rc = run(k, 0, n_ct, ws, st);
-    return rc;
-  }
-  const int h = n_ct / 2;
-  int rc = half_stream_ready(c);
-  if (rc) return rc;
-  void* const ws2 = static_cast<double*>(ws) + ws_doubles(c, h);
-  HIPCHK(hipEventRecord(c->half_fork, st));
-  HIPCHK(hipStreamWaitEvent(c->half_stream, c->half_fork, 0));
-  for (int k = 0; k < steps && !rc; ++k) {
-    rc = run(k, 0, h, ws, st);
-    if (!rc) rc = run(k, h, n_ct - h, ws2, c->half_stream);
-  }
-  HIPCHK(hipEventRecord(c->half_join, c->half_stream));
-  HIPCHK(hipStreamWaitEvent(st, c->half_join, 0));
-  return rc;
-}
-
 static int eq_mask_impl(nshe_ctx* c, const int64_t* x, const int64_t* y, int64_t* out,
                         int n_ct, int y_broadcast, void* ws, size_t ws_bytes, void* stream) {
   int rc = common_checks(c, n_ct, ws, ws_bytes, true);
@@ -1621,7 +1649,9 @@ static int eq_mask_impl(nshe_ctx* c, const int64_t* x, const int64_t* y, int64_t
   // the chain: the subtraction also lifts (the first squaring's operand), like
   // every level's mod-down but the last
   const size_t ctw = (size_t)2 * c->L * c->n;
-  return run_halves(c, n_ct, halves_from(c), 1 + c->squarings, ws, st,
+  const bool two = two_halves(c, n_ct, halves_from(c), ws, st) &&
+                   !halves_cross(c, n_ct, out, {{x}, {y, y_broadcast != 0}});
+  return run_halves(c, n_ct, two, 1 + c->squarings, ws, st,
                     [&](int k, int c0, int cnt, void* wsh, hipStream_t s) -> int {
     Ws w = carve(c, wsh, cnt);
     if (k > 0) return eq_level(c, w, cnt, k - 1, s, out + c0 * ctw);
@@ -1679,6 +1709,44 @@ static BatchArea batch_area(const nshe_ctx* c, void* ws, int wave_ct, long long 
   const size_t cts = (ws_doubles(c, wave_ct) * sizeof(double) + 255) & ~(size_t)255;
   (void)total;
   return BatchArea{reinterpret_cast<CtPtrs*>(p + cts + 256), reinterpret_cast<int*>(p + cts)};
+}
+
+// Whether an item's output lies on another item's input or output, or shifted
+// on its own input (items whose output is their own input, ciphertext for
+// ciphertext, are apart): the waves then run in order on one stream, where a
+// wave has read its inputs before it writes and a later wave sees what an
+// earlier one wrote.
+static bool items_cross(const nshe_ctx* c, const nshe_item* items, int n_items) {
+  struct Span {
+    uintptr_t lo, hi;
+    bool out;
+  };
+  const size_t cb = (size_t)2 * c->L * c->n * sizeof(int64_t);
+  std::vector<Span> spans;
+  spans.reserve((size_t)n_items * 3);
+  for (int i = 0; i < n_items; ++i) {
+    const nshe_item& it = items[i];
+    if (it.n_ct == 0) continue;
+    auto add = [&](const int64_t* p, int n, bool out) {
+      const uintptr_t lo = reinterpret_cast<uintptr_t>(p);
+      spans.push_back(Span{lo, lo + n * cb, out});
+    };
+    add(it.out_dev, it.n_ct, true);
+    if (it.x_dev != it.out_dev) add(it.x_dev, it.n_ct, false);
+    if (it.y_broadcast && it.n_ct > 1)
+      add(it.y_dev, 1, false);
+    else if (it.y_dev != it.out_dev)
+      add(it.y_dev, it.n_ct, false);
+  }
+  std::sort(spans.begin(), spans.end(),
+            [](const Span& a, const Span& b) { return a.lo < b.lo; });
+  uintptr_t any = 0, outs = 0;   // how far the spans, and the outputs, reach so far
+  for (const Span& s : spans) {
+    if (s.lo < (s.out ? any : outs)) return true;
+    any = std::max(any, s.hi);
+    if (s.out) outs = std::max(outs, s.hi);
+  }
+  return false;
 }
 
 // One wave of cnt ciphertexts: x - y, the 16 levels and the mask's finish,
@@ -1757,7 +1825,8 @@ int nshe_eq_mask_batched(nshe_ctx* c, const nshe_item* items, int n_items, int w
   const int first = total <= wave_ct ? (int)((total + 1) / 2) : hw;   // share 0's ciphertexts
   const bool two = c->tune.streams == 2 && total >= halves_from(c) && hw >= 1 &&
                    (size_t)wave_ct * c->n >= (1u << 15) && !c->prof &&
-                   ws_doubles(c, first) * sizeof(double) % 256 == 0 && stream_idle_capture(st);
+                   ws_doubles(c, first) * sizeof(double) % 256 == 0 && stream_idle_capture(st) &&
+                   !items_cross(c, items, n_items);
   int unit = two ? first : wave_ct;
   const int n_seq = two ? 2 : 1;
   long long n_units = (total + unit - 1) / unit;
@@ -1987,7 +2056,9 @@ int nshe_sum_slots(nshe_ctx* c, const int64_t* in, int64_t* out, int n_ct, void*
   // (with one digit per data prime the keys, 160 MB each, are most of what a
   // rotation reads: 4 ciphertexts 4.41 ms on one stream, 4.57 on two)
   const size_t ctw = (size_t)2 * c->L * c->n;
-  return run_halves(c, n_ct, c->alpha == 1 ? 8 : 2, 1 + (int)els.size(), ws, st,
+  const bool two =
+      two_halves(c, n_ct, c->alpha == 1 ? 8 : 2, ws, st) && !halves_cross(c, n_ct, out, {{in}});
+  return run_halves(c, n_ct, two, 1 + (int)els.size(), ws, st,
                     [&](int k, int c0, int cnt, void* wsh, hipStream_t s) -> int {
     Ws w = carve(c, wsh, cnt);
     if (k > 0) return sum_step(c, w, cnt, els, keys, k - 1, out + c0 * ctw, s);
@@ -2329,7 +2400,8 @@ static int mul_shared(nshe_ctx* c, const CmpArea& a, const int64_t* x, const int
     const int64_t* yj = y + j * a.U;
     int64_t* oj = out + j * a.U;
     const int cts = std::min(a.batch, count - j) * n_ct;
-    rc = run_halves(c, cts, PRODUCT_HALVES_FROM, 1, a.mws, st,
+    // (the products' slots follow their operands' in the area)
+    rc = run_halves(c, cts, two_halves(c, cts, PRODUCT_HALVES_FROM, a.mws, st), 1, a.mws, st,
                     [&](int, int c0, int cnt, void* wsh, hipStream_t s) {
       Ws w = carve(c, wsh, cnt);
       int r = prepare_i64(c, yj + c0 * ctw, w.dig, fx_second(c, w, cnt), cnt, s);
