@@ -248,9 +248,9 @@ int nshe_relinearize(nshe_ctx* ctx, const int64_t* in3_dev, int64_t* out_dev,
  * x is [n_ct][2][L][N]; y is the same shape, or one ciphertext broadcast to
  * every x when y_broadcast != 0 (an encrypted predicate constant).  Requires
  * t - 1 = 2^k (k squarings).  out may alias x or y.
- * From two ciphertexts on (four with alpha = 1; 2^15 coefficients in smaller
- * rings), the call runs its two halves on two streams (tuning streams, see
- * nshe_tuning); it stays ordered on `stream`. */
+ * Where that pays (from two ciphertexts on at the paper's parameters, four
+ * with alpha = 1) the call runs its two halves on two streams (tuning streams,
+ * see nshe_tuning); it stays ordered on `stream`. */
 int nshe_eq_mask(nshe_ctx* ctx, const int64_t* x_dev, const int64_t* y_dev,
                  int64_t* out_dev, int n_ct, int y_broadcast, void* ws_dev,
                  size_t ws_bytes, void* stream);
@@ -427,9 +427,8 @@ int nshe_join_sum(nshe_ctx* ctx, const int64_t* a_key_dev, const int64_t* b_key_
  * swap): every slot of the result holds the sum of all slots.  COUNT is
  * nshe_sum_slots of a 0/1 mask, SUM nshe_sum_slots of a column times the
  * mask (nshe_mul_relin).  Workspace: nshe_workspace_bytes(ctx, n_ct).
- * NSHE_ENOKEY names a missing Galois key.  nshe_sum_slots runs the two
- * halves of two or more ciphertexts (eight with alpha = 1) on two streams
- * (tuning streams). */
+ * NSHE_ENOKEY names a missing Galois key.  nshe_sum_slots runs its two
+ * halves on two streams where that pays (tuning streams). */
 int nshe_set_galois_key(nshe_ctx* ctx, uint32_t g, const int64_t* key_dev, size_t n_words,
                         void* stream);
 int nshe_galois_elements(const nshe_ctx* ctx, uint32_t* out_host, int max_out, int* n_out_host);
@@ -460,11 +459,11 @@ int nshe_sum_slots(nshe_ctx* ctx, const int64_t* in_dev, int64_t* out_dev, int n
  *                  product runs fused with the digit transforms (one
  *                  kernel; the digits' transforms are never written),
  *                  0: digit transforms, then the product (two kernels);
- *   streams        2: nshe_eq_mask and nshe_sum_slots over two or more
- *                  ciphertexts (four and eight with alpha = 1),
- *                  nshe_mul_relin and nshe_square_relin over eight or
- *                  more (all: 2^15 coefficients or more), run the first half
- *                  of them on `stream` and the second half on a second
+ *   streams        2: nshe_eq_mask, nshe_sum_slots, nshe_mul_relin and
+ *                  nshe_square_relin over enough ciphertexts, primes and
+ *                  coefficients for it to pay (at the paper's parameters with
+ *                  alpha = 3 from 2, 3, 8 and 8 ciphertexts on) run the first
+ *                  half of them on `stream` and the second half on a second
  *                  stream the context owns (non-blocking, default priority),
  *                  each in its own half of the workspace, so that one half's
  *                  kernels fill the GPU while the other's drain;

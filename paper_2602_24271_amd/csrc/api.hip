@@ -775,21 +775,6 @@ static bool stream_idle_capture(hipStream_t st) {
   return cs == hipStreamCaptureStatusNone;
 }
 
-// Whether a call over n_ct ciphertexts runs as two halves on two streams
-// (tuning streams = 2): not while profiling (each launch's own time), not the
-// no-allocation scratch, not while st is being captured, and only where the
-// second half's share of the workspace starts 256-byte aligned.  From two
-// ciphertexts on (four with one digit per data prime, whose key, read by both
-// halves, is 160 MB): one half's kernels fill the CUs that the other's leave
-// idle.  EQ at N = 2^15, one stream against two, ms: three-prime digits 2
-// ciphertexts 2.63 / 2.61, 3: 3.62 / 3.24, 5: 5.31 / 4.72, 8: 7.59 / 7.15, 16:
-// 14.3 / 13.4; two-prime 2: 3.16 / 2.90, 8: 9.07 / 8.26; one-prime 3: 5.37 /
-// 5.59, 4: 6.75 / 6.40, 8: 12.1 / 11.7.  (Three and four streams: 8
-// ciphertexts 7.06 and 8.23.)  Rings below 2^15 from 2^15 coefficients on:
-// below that the launches themselves are what the GPU waits for (2^10, 2
-// ciphertexts: 0.65 / 0.98 ms).
-static int halves_from(const nshe_ctx* c) { return c->alpha == 1 ? 4 : 2; }
-
 // A call's input as the halves' streams read it: ciphertext i of the call reads
 // ciphertext i of p, or the one ciphertext at p (bcast).
 struct HalfIn {
@@ -817,10 +802,61 @@ static bool halves_cross(const nshe_ctx* c, int n_ct, const int64_t* out,
   return false;
 }
 
-static bool two_halves(nshe_ctx* c, int n_ct, int from, const void* ws, hipStream_t st) {
-  if (c->tune.streams != 2 || n_ct < from || (size_t)n_ct * c->n < (1u << 15) || c->prof ||
-      ws == c->scratch)
-    return false;
+// What two streams have to share of a call: the limbs one level's transforms
+// pass over per ciphertext, the levels in a row, and the fewest ciphertexts.
+struct HalvesRule {
+  int from, limbs, levels;
+};
+
+static int switch_limbs(const nshe_ctx* c) { return (c->dnum + 2) * KS_of(c); }
+
+// A second stream pays where one half's kernels fill the CUs that the other's
+// leave idle; it costs twice the launches a level, a fork and a join, and a
+// second read of the key.  So the calls that split are those whose levels pass
+// over enough values (limbs N n_ct: 12 million from 2^14 coefficients on, 6
+// million in smaller rings, whose launches are cheaper to fill) for longer than
+// both halves' launches take, and over 64 million in all levels together.  One
+// stream against two, us:
+//   EQ, 2^15, 15 + 3 primes, 2 ciphertexts (18 million) 2657 / 2610, 3: 3567 /
+//     3225, 8: 7445 / 6971; 16 + 2, 2 (23): 3170 / 2929; 12 + 3, 2 (14): 2211 /
+//     2243; 8 + 2, 2 (9.5): 902 / 1060; 4 + 2, 4 levels, 4 (9): 456 / 549, 8
+//     (18): 624 / 623; 2 + 1, one level, 8 (9.7): 134 / 188
+//   EQ, 2^13, 15 + 3, 2 (4.6): 1311 / 1485, 3 (6.9): 1571 / 1551, 8: 2347 / 2198;
+//     2^12, 17 + 1, 8 (17): 2104 / 2048; 2^10, 15 + 3, 2 (0.6): 682 / 915
+//   one product, 2^15, 15 + 3, 4 (45): 365 / 375, 6 (67): 507 / 477, 8: 626 / 614;
+//     2^13, 3 + 3, 8 (8.8): 110 / 154, 16 + 2, 8 (27): 237 / 261
+//   SUM, 2^15, 15 + 3, 2 (8.3): 1502 / 1559, 3 (12.4): 1952 / 1912, 8: 3833 / 3562;
+//     2^14, 4 (8.3): 1311 / 1389, 6 (12.4): 1711 / 1637; 2^13, 8 (8.3): 1125 / 1032
+// Fewest ciphertexts: two for EQ, four with one digit per data prime (its 160
+// MB key, 3 ciphertexts 5240 / 5460, 4: 6596 / 6312); eight for a product; three
+// for SUM, eight with one- and two-prime digits, whose keys are most of what a
+// rotation reads (16 + 2, 4: 2731 / 2918, 8: 4741 / 4498; 17 + 1, 4: 4084 / 4390,
+// 8: 7565 / 7460).  (Three and four streams: EQ of 8 ciphertexts 7.06 and 8.23
+// ms, two 7.15 then.)
+static HalvesRule eq_halves(const nshe_ctx* c) {
+  return {c->alpha == 1 ? 4 : 2, 5 * W_of(c) + switch_limbs(c), c->squarings};
+}
+
+static HalvesRule product_halves(const nshe_ctx* c, int in_a_row = 1) {
+  return {8, 7 * W_of(c) + switch_limbs(c), in_a_row};
+}
+
+static HalvesRule sum_halves(const nshe_ctx* c) {
+  return {c->alpha == 3 ? 3 : 8, switch_limbs(c), c->log2n};
+}
+
+static bool halves_pay(const nshe_ctx* c, int n_ct, const HalvesRule& r) {
+  const double values = (double)n_ct * r.limbs * c->n;
+  return n_ct >= r.from && values >= (c->log2n >= 14 ? 12e6 : 6e6) && values * r.levels >= 64e6;
+}
+
+// Whether a call over n_ct ciphertexts runs as two halves on two streams
+// (tuning streams = 2): not while profiling (each launch's own time), not the
+// no-allocation scratch, not while st is being captured, and only where the
+// second half's share of the workspace starts 256-byte aligned.
+static bool two_halves(nshe_ctx* c, int n_ct, const HalvesRule& r, const void* ws,
+                       hipStream_t st) {
+  if (c->tune.streams != 2 || !halves_pay(c, n_ct, r) || c->prof || ws == c->scratch) return false;
   if (ws_doubles(c, n_ct / 2) * sizeof(double) % 256) return false;
   return stream_idle_capture(st);
 }
@@ -1517,11 +1553,6 @@ static int common_checks(nshe_ctx* c, int n_ct, void* ws, size_t ws_bytes, bool 
   return NSHE_OK;
 }
 
-// A single product runs as two halves from eight ciphertexts on: below that
-// the fork and join (two events, twice the launches) cost what they save (2
-// ciphertexts 225 us on one stream, 256 on two; 8: 650 and 624).
-constexpr int PRODUCT_HALVES_FROM = 8;
-
 int nshe_square_relin(nshe_ctx* c, const int64_t* in, int64_t* out, int n_ct, void* ws,
                       size_t ws_bytes, void* stream) {
   int rc = common_checks(c, n_ct, ws, ws_bytes, true);
@@ -1533,7 +1564,7 @@ int nshe_square_relin(nshe_ctx* c, const int64_t* in, int64_t* out, int n_ct, vo
   if ((rc = check_inputs(c, st, {{in, (size_t)n_ct * 2}}))) return rc;
   const size_t ctw = (size_t)2 * c->L * c->n;
   const bool two =
-      two_halves(c, n_ct, PRODUCT_HALVES_FROM, ws, st) && !halves_cross(c, n_ct, out, {{in}});
+      two_halves(c, n_ct, product_halves(c), ws, st) && !halves_cross(c, n_ct, out, {{in}});
   return run_halves(c, n_ct, two, 1, ws, st,
                     [&](int, int c0, int cnt, void* wsh, hipStream_t s) {
     Ws w = carve(c, wsh, cnt);
@@ -1571,7 +1602,7 @@ int nshe_mul_relin(nshe_ctx* c, const int64_t* a, const int64_t* b, int64_t* out
   if ((rc = check_inputs(c, st, {{a, (size_t)n_ct * 2}, {b, (size_t)n_ct * 2}}))) return rc;
   const size_t ctw = (size_t)2 * c->L * c->n;
   const bool two =
-      two_halves(c, n_ct, PRODUCT_HALVES_FROM, ws, st) && !halves_cross(c, n_ct, out, {{a}, {b}});
+      two_halves(c, n_ct, product_halves(c), ws, st) && !halves_cross(c, n_ct, out, {{a}, {b}});
   return run_halves(c, n_ct, two, 1, ws, st,
                     [&](int, int c0, int cnt, void* wsh, hipStream_t s) {
     Ws w = carve(c, wsh, cnt);
@@ -1649,7 +1680,7 @@ static int eq_mask_impl(nshe_ctx* c, const int64_t* x, const int64_t* y, int64_t
   // the chain: the subtraction also lifts (the first squaring's operand), like
   // every level's mod-down but the last
   const size_t ctw = (size_t)2 * c->L * c->n;
-  const bool two = two_halves(c, n_ct, halves_from(c), ws, st) &&
+  const bool two = two_halves(c, n_ct, eq_halves(c), ws, st) &&
                    !halves_cross(c, n_ct, out, {{x}, {y, y_broadcast != 0}});
   return run_halves(c, n_ct, two, 1 + c->squarings, ws, st,
                     [&](int k, int c0, int cnt, void* wsh, hipStream_t s) -> int {
@@ -1823,8 +1854,8 @@ int nshe_eq_mask_batched(nshe_ctx* c, const nshe_item* items, int n_items, int w
   // 10 instead of 16, 16 and 8).
   const int hw = wave_ct / 2;
   const int first = total <= wave_ct ? (int)((total + 1) / 2) : hw;   // share 0's ciphertexts
-  const bool two = c->tune.streams == 2 && total >= halves_from(c) && hw >= 1 &&
-                   (size_t)wave_ct * c->n >= (1u << 15) && !c->prof &&
+  const bool two = c->tune.streams == 2 && hw >= 1 && halves_pay(c, wave_ct, eq_halves(c)) &&
+                   !c->prof &&
                    ws_doubles(c, first) * sizeof(double) % 256 == 0 && stream_idle_capture(st) &&
                    !items_cross(c, items, n_items);
   int unit = two ? first : wave_ct;
@@ -2053,11 +2084,9 @@ int nshe_sum_slots(nshe_ctx* c, const int64_t* in, int64_t* out, int n_ct, void*
   if (rc) return rc;
   hipStream_t st = static_cast<hipStream_t>(stream);
   if ((rc = check_inputs(c, st, {{in, (size_t)n_ct * 2}}))) return rc;
-  // (with one digit per data prime the keys, 160 MB each, are most of what a
-  // rotation reads: 4 ciphertexts 4.41 ms on one stream, 4.57 on two)
   const size_t ctw = (size_t)2 * c->L * c->n;
   const bool two =
-      two_halves(c, n_ct, c->alpha == 1 ? 8 : 2, ws, st) && !halves_cross(c, n_ct, out, {{in}});
+      two_halves(c, n_ct, sum_halves(c), ws, st) && !halves_cross(c, n_ct, out, {{in}});
   return run_halves(c, n_ct, two, 1 + (int)els.size(), ws, st,
                     [&](int k, int c0, int cnt, void* wsh, hipStream_t s) -> int {
     Ws w = carve(c, wsh, cnt);
@@ -2400,8 +2429,10 @@ static int mul_shared(nshe_ctx* c, const CmpArea& a, const int64_t* x, const int
     const int64_t* yj = y + j * a.U;
     int64_t* oj = out + j * a.U;
     const int cts = std::min(a.batch, count - j) * n_ct;
-    // (the products' slots follow their operands' in the area)
-    rc = run_halves(c, cts, two_halves(c, cts, PRODUCT_HALVES_FROM, a.mws, st), 1, a.mws, st,
+    // (the products' slots follow their operands' in the area; one batch's
+    // launches hide behind the batch before it, so half a lone product's work
+    // is enough: 16 products at 2^12, 17 + 1 primes, 285 us / 276 in a row)
+    rc = run_halves(c, cts, two_halves(c, cts, product_halves(c, 2), a.mws, st), 1, a.mws, st,
                     [&](int, int c0, int cnt, void* wsh, hipStream_t s) {
       Ws w = carve(c, wsh, cnt);
       int r = prepare_i64(c, yj + c0 * ctw, w.dig, fx_second(c, w, cnt), cnt, s);

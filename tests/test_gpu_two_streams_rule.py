@@ -1,0 +1,63 @@
+"""Calls too short for a second stream run on one: few primes, few squarings or
+small rings, where the second stream's launches, fork and join cost more than
+it saves.  The default must not be slower than one stream by more than the
+noise of single calls (a wrong choice costs 1.2 to 1.9 times here)."""
+import time
+
+import pytest
+import torch
+
+import synth
+from paper_2602_24271_amd import Context
+from paper_2602_24271_amd.params import modulus_chain
+from tests.gpu_common import require_gpu
+
+pytestmark = pytest.mark.gpu
+
+NOISE = 1.12
+
+
+def context(log2_n, L, alpha, t):
+    require_gpu()
+    q, P = modulus_chain(log_qp=int(48.94 * (L + alpha)), n_primes=L + alpha, n_special=alpha)
+    c = Context(log2_n, t, q, P, 0)
+    key = synth.uniform_device_residues((c.dnum, 2), c.moduli_pq, c.n, 1, c.device)
+    c.set_relin_key(key)
+    for g in c.galois_elements():
+        c.set_galois_key(g, key)
+    return c
+
+
+def shortest(f):
+    """The shortest lone call of 40."""
+    best = 1e9
+    for _ in range(40):
+        torch.cuda.synchronize()
+        t = time.perf_counter()
+        f()
+        torch.cuda.synchronize()
+        best = min(best, time.perf_counter() - t)
+    return best
+
+
+@pytest.mark.parametrize("log2_n,L,alpha,t,n,op", [
+    (13, 2, 1, 3, 8, "eq"), (15, 2, 1, 3, 8, "eq"), (15, 3, 3, 3, 4, "eq"), (13, 4, 2, 17, 8, "eq"),
+    (14, 8, 2, 257, 2, "eq"), (13, 2, 2, 3, 8, "product"), (13, 3, 1, 3, 8, "product"),
+    (12, 17, 1, 65537, 8, "product"), (14, 3, 3, 65537, 16, "sum"), (14, 15, 3, 65537, 2, "sum"),
+    (15, 4, 2, 17, 3, "batched")])
+def test_short_calls_stay_on_one_stream(log2_n, L, alpha, t, n, op):
+    c = context(log2_n, L, alpha, t)
+    x = synth.uniform_device_residues((n, 2), c.q, c.n, 2, c.device)
+    y = synth.uniform_device_residues((n, 2), c.q, c.n, 3, c.device)
+    f = {"eq": lambda: c.eq_mask(x, y), "product": lambda: c.mul_relin(x, y),
+         "sum": lambda: c.sum_slots(x),
+         "batched": lambda: c.eq_mask_batched([(x, y)], use_graph=False)}[op]
+    f()
+    times = {1: [], 2: []}
+    for _ in range(2):
+        for s in (1, 2):
+            c.set_tuning(streams=s)
+            f()
+            times[s].append(shortest(f))
+    c.close()
+    assert min(times[2]) <= NOISE * min(times[1]), times
