@@ -282,9 +282,9 @@ int nshe_eq_mask_noalloc(nshe_ctx* ctx, const int64_t* x_dev, const int64_t* y_d
  * in the workspace (filled by small kernels at the start of the call), so
  * one graph per wave size serves every wave and every later call with the
  * same workspace and wave size.  Capture runs on a context-owned stream and
- * the graph is launched on `stream` (with tuning streams = 2: half-waves, on
- * `stream` and the context's second stream in turn, one graph per stream and
- * half-wave size).  ws_bytes must cover
+ * the graph is launched on `stream` (with tuning streams = 2, where it pays:
+ * each wave's halves on `stream` and on the context's second stream, one graph
+ * per stream and half-wave size).  ws_bytes must cover
  * nshe_batched_workspace_bytes(ctx, wave size, total ciphertexts); with
  * wave_ct = 0 the wave is the tuned one, capped by what ws_bytes holds. */
 typedef struct {
@@ -467,9 +467,9 @@ int nshe_sum_slots(nshe_ctx* ctx, const int64_t* in_dev, int64_t* out_dev, int n
  *                  stream the context owns (non-blocking, default priority),
  *                  each in its own half of the workspace, so that one half's
  *                  kernels fill the GPU while the other's drain;
- *                  nshe_eq_mask_batched runs half-waves, taking turns
- *                  between the two streams (each with its own half of the
- *                  wave's workspace).  The second stream starts after the
+ *                  nshe_eq_mask_batched runs each wave's halves on the two
+ *                  streams (each with its own share of the wave's
+ *                  workspace).  The second stream starts after the
  *                  work already on `stream` and `stream` waits for it at the
  *                  end (events), so the call stays ordered on `stream`.  Not
  *                  while profiling, while `stream` is being captured into a

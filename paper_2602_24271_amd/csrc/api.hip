@@ -1780,22 +1780,21 @@ static bool items_cross(const nshe_ctx* c, const nshe_item* items, int n_items) 
   return false;
 }
 
-// One wave of cnt ciphertexts: x - y, the 16 levels and the mask's finish,
-// the wave's ciphertexts read and written through its table; then advance
-// the wave counter by `step` (the number of streams taking turns over the
-// table's waves).
-static int enqueue_wave(nshe_ctx* c, int cnt, int stride, int step, const BatchArea& a,
-                        const Ws& w, hipStream_t st) {
-  Dims d = dims(c, cnt);
+// Step k of a wave of cnt ciphertexts, read and written through its table: x - y
+// with the first lift (k = 0), then the squarings, the last with the mask's
+// finish and the wave counter's advance.
+static int wave_step(nshe_ctx* c, int k, int cnt, int stride, const BatchArea& a, const Ws& w,
+                     hipStream_t st) {
   const WaveTab wt{a.table, a.counter, stride};
-  d.tab = wt;
-  {
+  if (k == 0) {
+    Dims d = dims(c, cnt);
+    d.tab = wt;
     Prof pf(c, K_SUB, st, 2.0 * cnt * c->L * c->n);
     HIPCHK(run_sub_lift(d, nullptr, nullptr, 0, w.ext, c->tb, st));
+    return NSHE_OK;
   }
-  for (int k = 0; k < c->squarings; ++k)
-    if (int rc = eq_level(c, w, cnt, k, st, nullptr, &wt)) return rc;
-  HIPCHK(run_bump_counter(a.counter, step, st));
+  if (int rc = eq_level(c, w, cnt, k - 1, st, nullptr, &wt)) return rc;
+  if (k == c->squarings) HIPCHK(run_bump_counter(a.counter, 1, st));
   return NSHE_OK;
 }
 
@@ -1843,36 +1842,30 @@ int nshe_eq_mask_batched(nshe_ctx* c, const nshe_item* items, int n_items, int w
   const BatchArea area = batch_area(c, ws, wave_ct, total);
   const size_t ctw = (size_t)2 * c->L * c->n;
 
-  // Two streams (tuning streams = 2): half-waves alternate between st and the
-  // context's second stream.  Each stream has its own share of the wave's
-  // ciphertext area (the two shares fill it) and its own wave counter (128
-  // bytes apart), which starts at the stream's first wave and steps by two, so
-  // that one stream's kernels and graphs never touch the other's.  (Units: the
-  // waves the table is laid out in, half-waves with two streams.)  A single
-  // wave is halved evenly; a few half-waves are evened out where an odd one
-  // would run alone at the end (40 ciphertexts in waves of 32: four units of
-  // 10 instead of 16, 16 and 8).
-  const int hw = wave_ct / 2;
-  const int first = total <= wave_ct ? (int)((total + 1) / 2) : hw;   // share 0's ciphertexts
-  const bool two = c->tune.streams == 2 && hw >= 1 && halves_pay(c, wave_ct, eq_halves(c)) &&
-                   !c->prof &&
-                   ws_doubles(c, first) * sizeof(double) % 256 == 0 && stream_idle_capture(st) &&
+  // Two streams (tuning streams = 2): each wave's first half on st, its second
+  // half on the context's second stream, every stream with its own share of
+  // the wave's ciphertext area (the two fill it), its own wave counter (128
+  // bytes apart) and its own column of the table, so that one stream's kernels
+  // and graphs never touch the other's.  An odd wave's first half is the
+  // larger by one: halves of equal size would leave a third of a wave of three
+  // unused (12 ciphertexts of 2^15, 15 + 3 primes, in waves of 3: 15.3 ms in
+  // halves of one, 13.0 in 2 + 1).  A few waves are evened out, so that no
+  // short one runs at the end alone (40 ciphertexts in waves of 32: two of 20).
+  // The halves' steps are enqueued in turn (see run_halves).
+  const long long few = (total + wave_ct - 1) / wave_ct;
+  const int half = few < 4 ? (int)((total + 2 * few - 1) / (2 * few)) : (wave_ct + 1) / 2;
+  const int even = std::min(2 * half, wave_ct);   // the wave of two such halves
+  const bool two = c->tune.streams == 2 && halves_pay(c, even, eq_halves(c)) && !c->prof &&
+                   ws_doubles(c, half) * sizeof(double) % 256 == 0 && stream_idle_capture(st) &&
                    !items_cross(c, items, n_items);
-  int unit = two ? first : wave_ct;
-  const int n_seq = two ? 2 : 1;
-  long long n_units = (total + unit - 1) / unit;
-  if (two && n_units > 2 && n_units < 8 && n_units % 2) {
-    ++n_units;
-    unit = (int)((total + n_units - 1) / n_units);
-    n_units = (total + unit - 1) / unit;
-  }
-  const BatchArea seq[2] = {area, BatchArea{area.table, area.counter + 32}};
+  const int wave = two ? even : wave_ct, first = two ? half : wave, n_seq = two ? 2 : 1;
+  const BatchArea seq[2] = {area, BatchArea{area.table + first, area.counter + 32}};
   char* const share[2] = {static_cast<char*>(ws),
                           static_cast<char*>(ws) + ws_doubles(c, first) * sizeof(double)};
 
-  // per-ciphertext pointers, unit by unit (unit u at entries u * unit; at
-  // most total + wave_ct entries)
-  for (int q = 0; q < n_seq; ++q) HIPCHK(run_set_counter(seq[q].counter, q, st));
+  // per-ciphertext pointers, wave by wave (wave u at entries u * wave; total
+  // entries, the second share's column `first` entries on)
+  for (int q = 0; q < n_seq; ++q) HIPCHK(run_set_counter(seq[q].counter, 0, st));
   TableChunk ch{};
   ch.first = 0;
   ch.n = 0;
@@ -1905,17 +1898,26 @@ int nshe_eq_mask_batched(nshe_ctx* c, const nshe_item* items, int n_items, int w
     HIPCHK(hipEventRecord(c->half_fork, st));
     HIPCHK(hipStreamWaitEvent(c->half_stream, c->half_fork, 0));
   }
-  for (long long u = 0; u < n_units && !rc; ++u) {
+  const long long n_waves = (total + wave - 1) / wave;
+  // share q's ciphertexts of wave u
+  auto count = [&](long long u, int q) {
+    const int left = (int)std::min<long long>(wave, total - u * wave);
+    return q ? std::max(left - first, 0) : std::min(first, left);
+  };
+  for (long long u = 0; u < n_waves && !use_graph && !rc; ++u)
+    for (int k = 0; k <= c->squarings && !rc; ++k)
+      for (int q = 0; q < n_seq && !rc; ++q)
+        if (const int cnt = count(u, q))
+          rc = wave_step(c, k, cnt, wave, seq[q], carve(c, share[q], cnt),
+                         q ? c->half_stream : st);
+  for (long long u = 0; u < n_waves * n_seq && use_graph && !rc; ++u) {
     const int q = (int)(u % n_seq);
     hipStream_t su = q ? c->half_stream : st;
-    const int cnt = (int)std::min<long long>(unit, total - u * unit);
-    Ws w = carve(c, share[q], cnt);
-    if (!use_graph) {
-      rc = enqueue_wave(c, cnt, unit, n_seq, seq[q], w, su);
-      continue;
-    }
+    const int cnt = count(u / n_seq, q);
+    if (cnt == 0) continue;
+    const Ws w = carve(c, share[q], cnt);
     const std::vector<uintptr_t> key = {reinterpret_cast<uintptr_t>(share[q]), (uintptr_t)cnt,
-                                        (uintptr_t)unit, (uintptr_t)n_seq,
+                                        (uintptr_t)wave, (uintptr_t)n_seq,
                                         reinterpret_cast<uintptr_t>(seq[q].counter)};
     const bool prof_saved = c->prof;
     c->prof = false;  // no event records inside a captured graph
@@ -1941,7 +1943,8 @@ int nshe_eq_mask_batched(nshe_ctx* c, const nshe_item* items, int n_items, int w
         rc = fail(NSHE_EDEVICE, std::string("capture: ") + hipGetErrorString(e));
         break;
       }
-      rc = enqueue_wave(c, cnt, unit, n_seq, seq[q], w, c->cap_stream);
+      for (int k = 0; k <= c->squarings && !rc; ++k)
+        rc = wave_step(c, k, cnt, wave, seq[q], w, c->cap_stream);
       e = hipStreamEndCapture(c->cap_stream, &g);
       if (rc) {
         if (g) (void)hipGraphDestroy(g);

@@ -28,10 +28,10 @@ def context(log2_n, L, alpha, t):
     return c
 
 
-def shortest(f):
-    """The shortest lone call of 40."""
+def shortest(f, calls=40):
+    """The shortest of lone calls."""
     best = 1e9
-    for _ in range(40):
+    for _ in range(calls):
         torch.cuda.synchronize()
         t = time.perf_counter()
         f()
@@ -61,3 +61,21 @@ def test_short_calls_stay_on_one_stream(log2_n, L, alpha, t, n, op):
             times[s].append(shortest(f))
     c.close()
     assert min(times[2]) <= NOISE * min(times[1]), times
+
+
+@pytest.mark.parametrize("total,wave", [(9, 3), (20, 5), (21, 7)])
+def test_odd_waves_fill_their_workspace(total, wave):
+    """Both halves of an odd wave together hold the whole wave: not slower
+    than the wave on one stream, which runs it whole."""
+    c = context(15, 15, 3, 65537)
+    items = [(synth.uniform_device_residues((total, 2), c.q, c.n, 2, c.device),
+              synth.uniform_device_residues((1, 2), c.q, c.n, 3, c.device))]
+    f = lambda: c.eq_mask_batched(items, wave_ct=wave, use_graph=False)
+    want, times = [], {1: [], 2: []}
+    for s in (1, 2, 1, 2):
+        c.set_tuning(streams=s)
+        want.append(f()[0])
+        times[s].append(shortest(f, 10))
+    c.close()
+    assert all(torch.equal(w, want[0]) for w in want[1:])
+    assert min(times[2]) <= 1.02 * min(times[1]), times
