@@ -79,3 +79,26 @@ def test_odd_waves_fill_their_workspace(total, wave):
     c.close()
     assert all(torch.equal(w, want[0]) for w in want[1:])
     assert min(times[2]) <= 1.02 * min(times[1]), times
+
+
+def test_sizes_in_turn_keep_their_graphs():
+    """Twelve sizes of the batched call in turn, over and over: from the second
+    round on no half-wave is captured again (a capture is some 0.3 ms of host
+    time, a launch of a captured one a tenth)."""
+    c = context(15, 15, 3, 65537)
+    items = [[(synth.uniform_device_residues((n, 2), c.q, c.n, n, c.device),
+               synth.uniform_device_residues((1, 2), c.q, c.n, 50 + n, c.device))]
+             for n in range(3, 15)]
+    c.eq_mask_batched(items[-1])      # (the workspace)
+    rounds = []
+    for _ in range(4):
+        host = 0.0
+        for it in items:
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            c.eq_mask_batched(it)
+            host += time.perf_counter() - t
+        rounds.append(host)
+    torch.cuda.synchronize()
+    c.close()
+    assert min(rounds[1:]) <= 0.5 * rounds[0], rounds
