@@ -861,7 +861,9 @@ static bool two_halves(nshe_ctx* c, int n_ct, const HalvesRule& r, const void* w
   return stream_idle_capture(st);
 }
 
-// The context's second stream and its fork and join events, made on first use.
+// The context's second stream and its fork and join events, made with the
+// context: a process's first further stream takes 3.5 ms (its hardware queue;
+// later ones 20 us), more than a whole EQ over two ciphertexts.
 static int half_stream_ready(nshe_ctx* c) {
   if (!c->half_stream) HIPCHK(hipStreamCreateWithFlags(&c->half_stream, hipStreamNonBlocking));
   if (!c->half_fork) HIPCHK(hipEventCreateWithFlags(&c->half_fork, hipEventDisableTiming));
@@ -1350,6 +1352,11 @@ int nshe_ctx_create(const nshe_params* pr, int hip_device, nshe_ctx** out) {
     (void)hipFree(c->dev_tables);
     delete c;
     return rc;
+  }
+  // (where it fails the first call that needs it tries again and reports it)
+  if (half_stream_ready(c)) {
+    g_err.clear();
+    (void)hipGetLastError();
   }
   *out = c;
   return rc;

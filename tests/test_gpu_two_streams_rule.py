@@ -2,6 +2,9 @@
 small rings, where the second stream's launches, fork and join cost more than
 it saves.  The default must not be slower than one stream by more than the
 noise of single calls (a wrong choice costs 1.2 to 1.9 times here)."""
+import os
+import subprocess
+import sys
 import time
 
 import pytest
@@ -102,3 +105,39 @@ def test_sizes_in_turn_keep_their_graphs():
     torch.cuda.synchronize()
     c.close()
     assert min(rounds[1:]) <= 0.5 * rounds[0], rounds
+
+
+FIRST_CALL = """
+import time, torch, synth
+from paper_2602_24271_amd import Context
+c = Context.paper(13, alpha=3)
+c.set_relin_key(synth.uniform_device_residues((c.dnum, 2), c.moduli_pq, c.n, 1, c.device))
+x = synth.uniform_device_residues((8, 2), c.q, c.n, 2, c.device)
+def call():
+    torch.cuda.synchronize()
+    t = time.perf_counter()
+    c.eq_mask(x, x)
+    torch.cuda.synchronize()
+    return time.perf_counter() - t
+c.set_tuning(streams=1)
+for n in (4, 8):     # every kernel of the halves and of the whole, on one stream
+    c.eq_mask(x[:n].clone(), x[:n].clone())
+call()
+c.set_tuning(streams=2)
+first = call()
+print("first %.6f later %.6f" % (first, min(call() for _ in range(5))))
+"""
+
+
+def test_first_call_makes_no_stream():
+    """In a process of its own: the first call on two streams is not some
+    milliseconds longer than the next (the second stream is made with the
+    context)."""
+    require_gpu()
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    out = subprocess.run([sys.executable, "-c", FIRST_CALL], cwd=root, capture_output=True,
+                         text=True, timeout=120)
+    assert out.returncode == 0, out.stderr
+    words = out.stdout.split()
+    first, later = float(words[1]), float(words[3])
+    assert first - later < 1.5e-3, out.stdout
