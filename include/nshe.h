@@ -479,8 +479,8 @@ int nshe_sum_slots(nshe_ctx* ctx, const int64_t* in_dev, int64_t* out_dev, int n
  *
  * nshe_autotune measures, on the caller's sample ciphertexts (int64
  * [n_sample][2][L][N], repeated cyclically to fill larger trials), squaring
- * levels of the EQ chain with HIP events: first ks_chunk, split_forward,
- * ks_fused and ew_block one at a time (each judged by the event time of the
+ * levels of the EQ chain (each lifts its result for the next) with HIP events:
+ * first split_forward, ks_chunk, ks_fused and ew_block one at a time (each judged by the event time of the
  * kernels it shapes, on min(32, wave limit) ciphertexts), then the per-ciphertext
  * time of a level at 1, 2, 4, ... ciphertexts up to the wave limit
  * (max_wave_ct if > 0, and what ws_bytes holds), keeping the smallest wave

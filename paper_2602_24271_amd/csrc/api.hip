@@ -369,19 +369,6 @@ static int ntt_job_ks(nshe_ctx* c, double* base, double* out, int npoly, int dir
   return NSHE_OK;
 }
 
-// Lift the ciphertexts held in ext (limbs 0..L-1) and transform all limbs
-// into fx.
-// (lifted: the mod-down that wrote ext already lifted it)
-static int prepare_operand(nshe_ctx* c, double* ext, double* fx, int n_ct, hipStream_t st,
-                           bool lifted = false) {
-  Dims d = dims(c, n_ct);
-  if (!lifted) {
-    Prof pf(c, K_LIFT, st, 2.0 * n_ct * c->n);
-    HIPCHK(run_lift(d, ext, c->tb, st));
-  }
-  return ntt_job_ext(c, ext, fx, n_ct * 2, 0, st);
-}
-
 // fx (NTT domain, operands; the first in fx_a when given, else w.fx; the
 // second in fx_b, or squaring) -> dt limbs 0..L-1 of the 3 components:
 // [round(t d_k / Q)]_Q, coefficient domain; the third as the
@@ -545,11 +532,11 @@ static int prepare_i64(nshe_ctx* c, const int64_t* in, double* ext, double* fx, 
   return ntt_job_ext(c, ext, fx, n_ct * 2, 0, st);
 }
 
-// One squaring level on the ciphertexts in ext (lifted: already lifted by
-// the kernel that wrote them), its result left as `md` says.
-static int square_level(nshe_ctx* c, const Ws& w, int n_ct, hipStream_t st, bool lifted,
-                        const ModDownOut& md, const WaveTab* tab = nullptr) {
-  int rc = prepare_operand(c, w.ext, w.fx, n_ct, st, lifted);
+// One squaring level on the ciphertexts in ext, lifted by the kernel that
+// wrote them, its result left as `md` says.
+static int square_level(nshe_ctx* c, const Ws& w, int n_ct, hipStream_t st, const ModDownOut& md,
+                        const WaveTab* tab = nullptr) {
+  int rc = ntt_job_ext(c, w.ext, w.fx, n_ct * 2, 0, st);
   if (rc) return rc;
   rc = tensor_scale(c, w, nullptr, n_ct, st);
   if (rc) return rc;
@@ -1669,7 +1656,7 @@ static int eq_level(nshe_ctx* c, const Ws& w, int n_ct, int k, hipStream_t st,
   md.ext = w.ext;
   md.out = finish_out;
   md.finish = 1;
-  return square_level(c, w, n_ct, st, true, md, last ? tab : nullptr);
+  return square_level(c, w, n_ct, st, md, last ? tab : nullptr);
 }
 
 static int eq_mask_impl(nshe_ctx* c, const int64_t* x, const int64_t* y, int64_t* out,
@@ -2747,17 +2734,24 @@ static int drain_records(nshe_ctx* c, double ms[K_COUNT]) {
   return NSHE_OK;
 }
 
-// Fill the first n_ct ciphertext slots of ext from the sample, cyclically.
+// Fill the first n_ct ciphertext slots of ext from the sample, cyclically,
+// lifted: what a level of the chain reads.
 static int load_sample(nshe_ctx* c, const Ws& w, const int64_t* sample, int n_sample, int n_ct,
                        hipStream_t st) {
-  const size_t W = W_of(c), N = c->n, ctw = (size_t)2 * c->L * N;
+  const size_t W = W_of(c), N = c->n;
   for (int k = 0; k < n_ct; k += n_sample) {
     const int m = std::min(n_sample, n_ct - k);
-    HIPCHK(run_i64_to_polys(dims(c, m), sample, 2, w.ext + (size_t)k * 2 * W * N, 2 * W * N,
-                            W * N, 2, c->tb, st));
+    HIPCHK(run_i64_lift(dims(c, m), sample, w.ext + (size_t)k * 2 * W * N, c->tb, st));
   }
-  (void)ctw;
   return NSHE_OK;
+}
+
+// A level inside the chain: its mod-down lifts the result for the next.
+static ModDownOut chain_out(const Ws& w) {
+  ModDownOut md;
+  md.kind = MD_LIFT;
+  md.ext = w.ext;
+  return md;
 }
 
 // Per-kind times of `reps` squaring levels on n_ct ciphertexts (after one
@@ -2766,13 +2760,12 @@ static int time_kinds(nshe_ctx* c, const nshe_tuning& t, const Ws& w, int n_ct, 
                       hipStream_t st, double ms[K_COUNT]) {
   c->tune = t;
   c->prof = false;
-  ModDownOut md;
-  md.ext = w.ext;
-  int rc = square_level(c, w, n_ct, st, false, md);
+  const ModDownOut md = chain_out(w);
+  int rc = square_level(c, w, n_ct, st, md);
   if (rc) return rc;
   c->prof = true;
   for (int i = 0; i < reps; ++i) {
-    rc = square_level(c, w, n_ct, st, false, md);
+    rc = square_level(c, w, n_ct, st, md);
     if (rc) return rc;
   }
   c->prof = false;
@@ -2781,14 +2774,13 @@ static int time_kinds(nshe_ctx* c, const nshe_tuning& t, const Ws& w, int n_ct, 
 
 // Wall time of one squaring level on n_ct ciphertexts (after one untimed).
 static int time_level(nshe_ctx* c, const Ws& w, int n_ct, hipStream_t st, double* ms) {
-  ModDownOut md;
-  md.ext = w.ext;
-  int rc = square_level(c, w, n_ct, st, false, md);
+  const ModDownOut md = chain_out(w);
+  int rc = square_level(c, w, n_ct, st, md);
   if (rc) return rc;
   hipEvent_t a = take_event(c), b = take_event(c);
   if (!a || !b) return fail(NSHE_EDEVICE, "event creation failed");
   HIPCHK(hipEventRecord(a, st));
-  rc = square_level(c, w, n_ct, st, false, md);
+  rc = square_level(c, w, n_ct, st, md);
   if (rc) return rc;
   HIPCHK(hipEventRecord(b, st));
   HIPCHK(hipEventSynchronize(b));
@@ -2845,27 +2837,30 @@ int nshe_autotune(nshe_ctx* c, const int64_t* sample, int n_sample, int max_wave
   if (rc) { c->tune = start; return rc; }
   nshe_tuning best = start;
   double ms[K_COUNT];
-  {
-    const int cand[] = {4, 8, 16, 32};
-    double tbest = 1e300;
-    for (int v : cand) {
-      nshe_tuning t = best;
-      t.ks_chunk = v;
-      rc = time_kinds(c, t, w, n_t, 2, st, ms);
-      if (rc) { c->tune = start; return rc; }
-      if (ms[K_KS_MAC] < tbest) { tbest = ms[K_KS_MAC]; best.ks_chunk = v; }
-    }
-  }
   if (c->log2n == 15) {
     double tbest = 1e300;
     for (int v = 0; v < 2; ++v) {
       nshe_tuning t = best;
+      t.ks_fused = 0;
       t.split_forward = v;
       rc = time_kinds(c, t, w, n_t, 2, st, ms);
       if (rc) { c->tune = start; return rc; }
       // the split changes the key-switch product too (parity digits)
       const double tt = ms[K_NTT_FWD] + ms[K_NTT_DIGIT] + ms[K_KS_MAC];
       if (tt < tbest) { tbest = tt; best.split_forward = v; }
+    }
+  }
+  {
+    // (at most 16 wide with digit transforms by parity: 32 is the same kernel)
+    const int widest = c->log2n == 15 && best.split_forward ? 16 : 32;
+    double tbest = 1e300;
+    for (int v = 4; v <= widest; v *= 2) {
+      nshe_tuning t = best;
+      t.ks_fused = 0;
+      t.ks_chunk = v;
+      rc = time_kinds(c, t, w, n_t, 2, st, ms);
+      if (rc) { c->tune = start; return rc; }
+      if (ms[K_KS_MAC] < tbest) { tbest = ms[K_KS_MAC]; best.ks_chunk = v; }
     }
   }
   // (the fused key switch exists for one-prime digits only)
@@ -2888,7 +2883,7 @@ int nshe_autotune(nshe_ctx* c, const int64_t* sample, int n_sample, int max_wave
       t.ew_block = v;
       rc = time_kinds(c, t, w, n_t, 2, st, ms);
       if (rc) { c->tune = start; return rc; }
-      const double tt = ms[K_LIFT] + ms[K_SCALE] + ms[K_MODDOWN];
+      const double tt = ms[K_SCALE] + ms[K_MODDOWN_LIFT];
       if (tt < tbest) { tbest = tt; best.ew_block = v; }
     }
   }

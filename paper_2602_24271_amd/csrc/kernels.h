@@ -208,7 +208,6 @@ struct Dims {
   WaveTab tab;
 };
 
-hipError_t run_lift(const Dims& d, double* ext, const Tables& tb, hipStream_t st);
 // digit_pairs: write the third component as the digits' mixed-radix digits
 // (the relinearization digit source with alpha > 1) instead of canonical
 // residues.  src (not null): write the third component (the digit source)
@@ -220,10 +219,10 @@ hipError_t run_scale(const Dims& d, double* dt, const Tables& tb, hipStream_t st
 hipError_t run_ks_mac(const Dims& d, const double* dig, const double* evk, double* acc,
                       const Tables& tb, hipStream_t st);
 // What a mod-down's result becomes (see k_moddown).
-enum ModDownKind { MD_EXT = 0, MD_SUM = 1, MD_LIFT = 2, MD_I64 = 3, MD_SUM_I64 = 4 };
+enum ModDownKind { MD_SUM = 0, MD_LIFT = 1, MD_I64 = 2, MD_SUM_I64 = 3 };
 struct ModDownOut {
-  ModDownKind kind = MD_EXT;
-  double* ext = nullptr;    // MD_EXT, MD_SUM, MD_LIFT, MD_SUM_I64
+  ModDownKind kind = MD_LIFT;
+  double* ext = nullptr;    // MD_SUM, MD_LIFT, MD_SUM_I64
   int64_t* out = nullptr;   // MD_I64, MD_SUM_I64 (unless the wave's table names it)
   int finish = 0;           // MD_I64: the mask's (Delta, 0) - z
   int one_e = 0;            // component 1 of dt is zero and not read

@@ -199,43 +199,6 @@ __device__ __forceinline__ void lift_tail(const double (&o)[L], const v4i (&g0)[
   }
 }
 
-// ext: [n_poly][L+LB][N]; limbs 0..L-1 (balanced, coefficient domain) are
-// lifted to limbs L..L+LB-1 (the extension basis) in place.
-template <int L>
-__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4)))
-k_lift(int n, size_t n_poly, double* ext, Tables tb) {
-  constexpr int LB = L + 1;
-  __shared__ v4i tab[conv_entries(L, LB)];
-  bool first = true;
-  const unsigned nb = poly_blocks(n, n_poly);
-  for (unsigned bk = blockIdx.x; bk < nb; bk += gridDim.x) {
-    const PolyBlock pb = poly_block(n, bk);
-    const auto rs = make_rsrc(ext + pb.pc * (size_t)(L + LB) * n, (unsigned)((L + LB) * n * 8));
-    const unsigned vo = (unsigned)pb.c * 8;
-    const unsigned ls = (unsigned)n * 8;   // bytes per limb
-    double o[L], y[L];
-    double S = 0.0;
-#pragma unroll
-    for (int i = 0; i < L; ++i) o[i] = buf_load(rs, vo, i * ls);
-    loads_issued();
-    lift_setup<L>(tab, tb, first);
-    v4i g0[conv_steps(L)], g1[conv_steps(L)];
-#pragma unroll
-    for (int s = 0; s < conv_steps(L); ++s) {
-      const double* kq = step_consts(tb.kq, s);
-#pragma unroll
-      for (int j = 0; j < 4 && 4 * s + j < L; ++j) {
-        const int i = 4 * s + j;
-        const double qinv = cld(kq, 4 * j + 1);
-        y[i] = mul_bal(o[i], cld(kq, 4 * j + 2), cld(kq, 4 * j), qinv);
-        S += y[i] * qinv;
-      }
-      pack_step<L>(y, s, g0[s], g1[s]);
-    }
-    lift_tail<L, MARGIN_LIFT>(o, g0, g1, S, rs, vo, ls, pb.ok, tab, tb);
-  }
-}
-
 // ------------------------------------------------- inverse-transform output ---
 
 // Where a per-coefficient kernel reads coefficient c of a limb written by an
@@ -685,8 +648,7 @@ __device__ __forceinline__ double rotation_digit(double o, int m, double (&v)[A]
 // k_m times [(P_0 ... P_{m-1}) P^-1]_{q_i}.  Each lazy product is below
 // 0.9 q_i (operands below 2 q_i: P_k may exceed q_i, all lie below 2^49), so a
 // sum stays below 4.2 q_i.  What becomes of the result z (OUT):
-//   MD_EXT   stored in ext (limbs 0..L-1);
-//   MD_SUM   a rotation's, in a running sum: stored in ext as MD_EXT, and component
+//   MD_SUM   a rotation's, in a running sum: stored in ext (limbs 0..L-1), and component
 //            1's rotation digits (see rotated_digit) in its limbs L..2L-1.  e_0 holds the
 //            sum's component 0 and its rotation already (k_automorph), e_1 is what
 //            ext holds;
@@ -823,7 +785,7 @@ k_moddown(int n, size_t n_poly, const double* __restrict__ acc, const double* __
 // Subtraction z = [x - y]_Q of two ciphertexts (int64, canonical; y one
 // ciphertext broadcast when y_bcast) into ext limbs 0..L-1, followed by the
 // lift of z (limbs L..2L): the first level of the chain, one kernel.  One
-// thread per coefficient of each (ct, b) polynomial, blocks as in k_lift.
+// thread per coefficient of each (ct, b) polynomial, in blocks (PolyBlock).
 // wt (table not null): a batched wave's ciphertexts, x and y read through
 // the table (a broadcast y is every entry's y).
 template <int L, int SITE>
@@ -882,7 +844,7 @@ k_sub_lift(int n, size_t n_poly, const int64_t* __restrict__ xs, const int64_t* 
 
 // Canonical int64 residues of n_poly polynomials ([n_poly][L][N]) into ext
 // limbs 0..L-1 (balanced) and their lift into limbs L..2L: the conversion
-// (k_i64_to_polys) and k_lift in one pass, the same arithmetic.  The first
+// (k_i64_to_polys) and the lift in one pass.  The first
 // n_first polynomials come from in, the others from in2 (a product's two
 // operands in one launch).
 template <int L>
@@ -1590,18 +1552,6 @@ static inline dim3 grid_for(size_t total, int block = 256) {
 #define NSHE_L2_CASES(X) X(2) X(4) X(8) X(16)
 #define NSHE_L3_CASES(X) X(3) X(12) X(15)
 
-hipError_t run_lift(const Dims& d, double* ext, const Tables& tb, hipStream_t st) {
-  const size_t np = (size_t)d.n_ct * 2;
-  switch (d.L) {
-#define C_(L_) \
-  case L_: hipLaunchKernelGGL(k_lift<L_>, poly_grid(d, np), dim3(poly_threads(d)), 0, st, d.n, np, ext, tb); break;
-    NSHE_L_CASES(C_)
-#undef C_
-    default: return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
-}
-
 // f(L, alpha) as integral constants, for the decompositions built.
 template <class F>
 static hipError_t for_digits(int L, int alpha, F f) {
@@ -1643,7 +1593,6 @@ static hipError_t launch_moddown(const Dims& d, const double* acc, const double*
 hipError_t run_moddown(const Dims& d, const double* acc, const double* dt, const ModDownOut& o,
                        const Tables& tb, hipStream_t st) {
   switch (o.kind) {
-    case MD_EXT: return launch_moddown<MD_EXT>(d, acc, dt, o.ext, nullptr, 0, o.one_e, tb, st);
     case MD_SUM: return launch_moddown<MD_SUM>(d, acc, dt, o.ext, nullptr, 0, o.one_e, tb, st);
     case MD_LIFT: return launch_moddown<MD_LIFT>(d, acc, dt, o.ext, nullptr, 0, o.one_e, tb, st);
     case MD_I64:
