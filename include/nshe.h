@@ -441,9 +441,11 @@ int nshe_sum_slots(nshe_ctx* ctx, const int64_t* in_dev, int64_t* out_dev, int n
  * (every kernel computes the same exact integers); only the speed does.
  *   ks_chunk       ciphertexts accumulated per pass over the relinearization
  *                  key in the key-switch inner product: 4, 8, 16 or 32
- *                  (at most 16 are used with digit transforms by parity;
- *                  fewer ciphertexts, and equal shares of more, take the
- *                  narrowest width that holds them, down to one);
+ *                  (fewer ciphertexts take the narrowest power of two that
+ *                  holds them; with digit transforms by parity at most 16
+ *                  are used, and any number of ciphertexts is shared out
+ *                  over as few passes, each of the narrowest of 1, 2, 3, 4,
+ *                  6, 8, 12 and 16 that holds its share);
  *   split_forward  1: each 2^15-point forward transform runs as two
  *                  workgroups: one per output half, and for the key-switch
  *                  digits one per coefficient parity (two 2^14-point

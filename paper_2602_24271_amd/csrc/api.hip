@@ -398,9 +398,10 @@ static bool parity_digits(const nshe_ctx* c) {
 // key-switch product) by coefficient parity, c at (c mod 2) N/2 + c/2, so
 // that each parity's transform reads its half contiguously.  In place, that
 // order would overwrite values the scale-and-round's other waves have still
-// to read; with 16 or 17 data primes the scale-and-round's extra destination
-// spills its scalar registers (measured slower), so one- and two-prime
-// digits stay in place and the transform reads every second value.
+// to read.  One- and two-prime digits stay in place and the transform reads
+// every second value: with 16 or 17 data primes the extra destination spilled
+// scalar registers and was slower while the scale-and-round formed its sums on
+// the FP64 VALU; on the matrix cores it has not been measured.
 struct DigitSrc {
   double* p;       // ciphertext 0's limb 0
   size_t stride;   // doubles between ciphertexts

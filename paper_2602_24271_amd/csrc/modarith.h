@@ -99,6 +99,12 @@ __device__ __forceinline__ const double* opaque_row(const double* p, int off) {
   asm volatile("" : "+s"(r));
   return r;
 }
+// y = yh 2^24 + yl, |yl| <= 2^23 (exact for integers |y| < 2^53).
+__device__ __forceinline__ void split24(double y, double& yh, double& yl) {
+  yh = __builtin_rint(y * 0x1p-24);
+  yl = __builtin_fma(-yh, 0x1p24, y);
+}
+
 // The loads above are issued before anything below: the scheduler otherwise
 // sinks them to their uses, one memory latency each.
 __device__ __forceinline__ void loads_issued() { __builtin_amdgcn_sched_barrier(0); }
