@@ -464,7 +464,7 @@ int nshe_sum_slots(nshe_ctx* ctx, const int64_t* in_dev, int64_t* out_dev, int n
  *   streams        2: nshe_eq_mask, nshe_sum_slots, nshe_mul_relin and
  *                  nshe_square_relin over enough ciphertexts, primes and
  *                  coefficients for it to pay (at the paper's parameters with
- *                  alpha = 3 from 2, 3, 8 and 8 ciphertexts on) run the first
+ *                  alpha = 3 from 2, 2, 8 and 8 ciphertexts on) run the first
  *                  half of them on `stream` and the second half on a second
  *                  stream the context owns (non-blocking, default priority),
  *                  each in its own half of the workspace, so that one half's

@@ -791,9 +791,11 @@ static bool halves_cross(const nshe_ctx* c, int n_ct, const int64_t* out,
 }
 
 // What two streams have to share of a call: the limbs one level's transforms
-// pass over per ciphertext, the levels in a row, and the fewest ciphertexts.
+// pass over per ciphertext, the levels in a row, the fewest ciphertexts and the
+// fewest values a level.
 struct HalvesRule {
   int from, limbs, levels;
+  double values;
 };
 
 static int switch_limbs(const nshe_ctx* c) { return (c->dnum + 2) * KS_of(c); }
@@ -801,41 +803,45 @@ static int switch_limbs(const nshe_ctx* c) { return (c->dnum + 2) * KS_of(c); }
 // A second stream pays where one half's kernels fill the CUs that the other's
 // leave idle; it costs twice the launches a level, a fork and a join, and a
 // second read of the key.  So the calls that split are those whose levels pass
-// over enough values (limbs N n_ct: 12 million from 2^14 coefficients on, 6
-// million in smaller rings, whose launches are cheaper to fill) for longer than
-// both halves' launches take, and over 64 million in all levels together.  One
-// stream against two, us:
+// over enough values (limbs N n_ct: 12 million from 2^14 coefficients on, 8 for
+// a rotation of 2^15, 6 in smaller rings, whose launches are cheaper to fill)
+// for longer than both halves' launches take, and over 40 million in all levels
+// together.  One stream against two, us:
 //   EQ, 2^15, 15 + 3 primes, 2 ciphertexts (18 million) 2657 / 2610, 3: 3567 /
 //     3225, 8: 7445 / 6971; 16 + 2, 2 (23): 3170 / 2929; 12 + 3, 2 (14): 2211 /
 //     2243; 8 + 2, 2 (9.5): 902 / 1060; 4 + 2, 4 levels, 4 (9): 456 / 549, 8
 //     (18): 624 / 623; 2 + 1, one level, 8 (9.7): 134 / 188
 //   EQ, 2^13, 15 + 3, 2 (4.6): 1311 / 1485, 3 (6.9): 1571 / 1551, 8: 2347 / 2198;
 //     2^12, 17 + 1, 8 (17): 2104 / 2048; 2^10, 15 + 3, 2 (0.6): 682 / 915
-//   one product, 2^15, 15 + 3, 4 (45): 365 / 375, 6 (67): 507 / 477, 8: 626 / 614;
-//     2^13, 3 + 3, 8 (8.8): 110 / 154, 16 + 2, 8 (27): 237 / 261
-//   SUM, 2^15, 15 + 3, 2 (8.3): 1502 / 1559, 3 (12.4): 1952 / 1912, 8: 3833 / 3562;
-//     2^14, 4 (8.3): 1311 / 1389, 6 (12.4): 1711 / 1637; 2^13, 8 (8.3): 1125 / 1032
+//   one product, 2^15, 15 + 3, 8 (90): 626 / 614; 2^14, 8 (45): alone 362 / 374,
+//     in a row 3% faster; 2^13, 16 + 2, 8 (27): 237 / 261; 3 + 3, 8 (8.8): 110 / 154
+//   SUM, 2^15, 15 + 3, 2 (8.3): in a row 1489 / 1473, alone 1519 / 1585; 3
+//     (12.4): 1952 / 1912, 8: 3833 / 3562; 12 + 3, 2 (5.9): 1194 / 1377; 2^14, 4
+//     (8.3): 1311 / 1389, 6 (12.4): 1711 / 1637; 2^13, 8 (8.3): 1125 / 1032
 // Fewest ciphertexts: two for EQ, four with one digit per data prime (its 160
-// MB key, 3 ciphertexts 5240 / 5460, 4: 6596 / 6312); eight for a product; three
-// for SUM, eight with one- and two-prime digits, whose keys are most of what a
-// rotation reads (16 + 2, 4: 2731 / 2918, 8: 4741 / 4498; 17 + 1, 4: 4084 / 4390,
-// 8: 7565 / 7460).  (Three and four streams: EQ of 8 ciphertexts 7.06 and 8.23
+// MB key, 3 ciphertexts 5240 / 5460, 4: 6596 / 6312); eight for a product; two
+// for SUM, six and eight with two- and one-prime digits, whose keys are most of
+// what a rotation reads (16 + 2, 4: 2731 / 2918, 8: 4741 / 4498; 17 + 1, 4: 4084 /
+// 4390, 8: 7565 / 7460).  (Three and four streams: EQ of 8 ciphertexts 7.06 and 8.23
 // ms, two 7.15 then.)
+static double level_values(const nshe_ctx* c) { return c->log2n >= 14 ? 12e6 : 6e6; }
+
 static HalvesRule eq_halves(const nshe_ctx* c) {
-  return {c->alpha == 1 ? 4 : 2, 5 * W_of(c) + switch_limbs(c), c->squarings};
+  return {c->alpha == 1 ? 4 : 2, 5 * W_of(c) + switch_limbs(c), c->squarings, level_values(c)};
 }
 
 static HalvesRule product_halves(const nshe_ctx* c, int in_a_row = 1) {
-  return {8, 7 * W_of(c) + switch_limbs(c), in_a_row};
+  return {8, 7 * W_of(c) + switch_limbs(c), in_a_row, level_values(c)};
 }
 
 static HalvesRule sum_halves(const nshe_ctx* c) {
-  return {c->alpha == 3 ? 3 : 8, switch_limbs(c), c->log2n};
+  return {c->alpha == 3 ? 2 : c->alpha == 2 ? 6 : 8, switch_limbs(c), c->log2n,
+          c->log2n == 15 ? 8e6 : level_values(c)};
 }
 
 static bool halves_pay(const nshe_ctx* c, int n_ct, const HalvesRule& r) {
   const double values = (double)n_ct * r.limbs * c->n;
-  return n_ct >= r.from && values >= (c->log2n >= 14 ? 12e6 : 6e6) && values * r.levels >= 64e6;
+  return n_ct >= r.from && values >= r.values && values * r.levels >= 40e6;
 }
 
 // Whether a call over n_ct ciphertexts runs as two halves on two streams
