@@ -219,7 +219,7 @@ hipError_t run_scale(const Dims& d, double* dt, const Tables& tb, hipStream_t st
 hipError_t run_ks_mac(const Dims& d, const double* dig, const double* evk, double* acc,
                       const Tables& tb, hipStream_t st);
 // What a mod-down's result becomes (see k_moddown).
-enum ModDownKind { MD_SUM = 0, MD_LIFT = 1, MD_I64 = 2, MD_SUM_I64 = 3 };
+enum ModDownKind { MD_SUM = 1, MD_LIFT = 2, MD_I64 = 3, MD_SUM_I64 = 4 };
 struct ModDownOut {
   ModDownKind kind = MD_LIFT;
   double* ext = nullptr;    // MD_SUM, MD_LIFT, MD_SUM_I64
