@@ -487,7 +487,7 @@ int nshe_sum_slots(nshe_ctx* ctx, const int64_t* in_dev, int64_t* out_dev, int n
  * time of a level at 1, 2, 4, ... ciphertexts up to the wave limit
  * (max_wave_ct if > 0, and what ws_bytes holds), keeping the smallest wave
  * within 1% of the best rate (with streams = 2, at least 32 where that many
- * fit: the batched call's half-waves).  The result becomes the context's tuning and
+ * fit: halves of 16 or more).  The result becomes the context's tuning and
  * is copied to *out_host (if not NULL); *ms_per_ct_host (if not NULL)
  * receives the best per-ciphertext level time in ms.  Needs the relin key.
  * The workspace contents are overwritten; the sample is only read.  The

@@ -108,29 +108,30 @@ class Context:
             self._ws = torch.empty(need, dtype=torch.uint8, device=self.device)
         return self._ws
 
-    # A wide workspace (room for a comparison's or join's batches) is taken where
-    # it leaves seven eighths of the free memory to the GPU's other tenants: the
-    # context keeps it, up to 5 GB more than the call's smallest.
+    # What a wide workspace (room for a comparison's or join's batches, up to 5 GB
+    # more than the call's smallest) adds is taken where it leaves seven eighths of
+    # the memory that is free beside the smallest to the GPU's other tenants: the
+    # context keeps it.
     WIDE_SHARE = 8
 
     def _workspace_wide(self, want: int, need: int) -> torch.Tensor:
-        """`want` bytes, or the call's smallest workspace, `need`, where `want`
-        would take too much of the memory that is free."""
+        """`want` bytes, or the call's smallest workspace, `need`, where the
+        rest would take too much of the memory that is free."""
         held = 0 if self._ws is None else self._ws.numel()
-        if held < want and want > need and not self._room(want, held):
+        if held < want and want > need and not self._room(want, need, held):
             return self._workspace_bytes(need)
         try:
             return self._workspace_bytes(want)
         except torch.OutOfMemoryError:
             return self._workspace_bytes(need)
 
-    def _room(self, want: int, held: int) -> bool:
+    def _room(self, want: int, need: int, held: int) -> bool:
         # (a capture's allocations stay with its graph)
         if torch.cuda.is_current_stream_capturing():
             return False
         free = torch.cuda.mem_get_info(self.device)[0]
         cached = torch.cuda.memory_reserved(self.device) - torch.cuda.memory_allocated(self.device)
-        return want <= (free + cached + held) // self.WIDE_SHARE
+        return want - need <= (free + cached + held - need) // self.WIDE_SHARE
 
     def _check_ct(self, x: torch.Tensor, comps: int = 2) -> int:
         if x.dtype != torch.int64 or x.device != self.device or not x.is_contiguous():

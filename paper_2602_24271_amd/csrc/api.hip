@@ -2915,7 +2915,7 @@ int nshe_autotune(nshe_ctx* c, const int64_t* sample, int n_sample, int max_wave
   for (auto& r : rates)
     if (r.second <= 1.01 * rbest) { best.wave_ct = r.first; break; }
   // two streams: waves of at least 32 where the workspace holds them, so
-  // that the batched call's half-waves (16 or more) take turns on them
+  // that a wave's halves are 16 or more
   if (best.streams == 2 && fit >= 32) best.wave_ct = std::max(best.wave_ct, 32);
   drop_graphs(c);
   c->tune = best;

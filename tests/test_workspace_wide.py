@@ -29,11 +29,16 @@ def ctx(monkeypatch):
 
 
 @pytest.mark.parametrize("free,cached,capturing,got", [
-    (200 * GB, 0, False, 3 * GB), (24 * GB, 0, False, 3 * GB), (23 * GB, 0, False, GB),
-    (4 * GB, 0, False, GB), (4 * GB, 20 * GB, False, 3 * GB), (200 * GB, 0, True, GB)])
+    (200 * GB, 0, False, 3 * GB), (17 * GB, 0, False, 3 * GB), (16 * GB, 0, False, GB),
+    (4 * GB, 0, False, GB), (4 * GB, 13 * GB, False, 3 * GB), (200 * GB, 0, True, GB)])
 def test_wide_leaves_the_free_memory(ctx, free, cached, capturing, got):
     ctx.state.update(free=free, cached=cached, capturing=capturing)
     assert ctx._workspace_wide(3 * GB, GB).numel() == got
+
+
+def test_a_large_call_still_takes_what_little_its_batches_add(ctx):
+    ctx.state.update(free=200 * GB)
+    assert ctx._workspace_wide(56 * GB, 54 * GB).numel() == 56 * GB
 
 
 def test_held_and_failing(ctx):
