@@ -293,9 +293,13 @@ __device__ __forceinline__ void scale_out(const v4i (&h0)[conv_steps(L + 1)],
 // the same conversions as split FP64 FMAs (4 per term, on the VALU) took 380.
 // Every limb is loaded at the block's start: loaded as they were needed, the
 // waits of the second half's limbs alone made it 310.  At one ciphertext 20 us
-// (29): there it is latency, six waves per CU.
+// (29): there it is latency, six waves per CU.  From 17 primes on the tables in
+// LDS (52 KB and more a workgroup of four waves) leave three waves per SIMD or
+// fewer, and the registers of the fourth hold the limbs: bounded to four, 17
+// primes spilled 3 of them and 20 primes 12 (24 ciphertexts 225 us, now 212,
+// and 325, now 276).
 template <int L, bool FUSED, int A>
-__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4)))
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(L > 17 ? 2 : L > 16 ? 3 : 4)))
 k_scale(int n, size_t n_poly, double* dt, Tables tb) {
   constexpr int LB = L + 1, W = L + LB;
   __shared__ v4i tab1[conv_entries(L, LB)];
